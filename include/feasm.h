@@ -239,7 +239,7 @@ typedef struct {
     int32_t outer_iterations;  /* refinement steps (mixed); 1 for FE_FP64 */
     double rel_residual;       /* ||r||/||b|| from the recurrence (FP64 outer residual in mixed) */
     double true_rel_residual;  /* ||b - A x||/||b|| recomputed in FP64 */
-    int32_t symmetric_spmv;    /* 1: the FP64 iterations ran the symmetric SpMV (see fe_cg_solve), else 0 */
+    int32_t symmetric_spmv;    /* 1: the matrix passed the symmetric-pair check (see fe_cg_solve), else 0 */
 } fe_cg_info;
 
 /*
@@ -256,7 +256,16 @@ typedef struct {
  * The first FP64 solve on a mesh builds the symmetric map on the host and
  * keeps it, with a packed copy of the values, on the device (about 8
  * bytes per nonzero; without room for them the general SpMV runs).
- * The two SpMVs round differently; the true residual is always computed
+ * A matrix that passed the check and fits the device's registers (rows of
+ * at most 27 entries: up to ~393,000 nodes, ~590,000 where rows hold at most
+ * 16) is solved in one launch that reads each value once; FE_MIXED runs its
+ * FP32 solves so up to ~655,000 (~786,000) nodes.  The launch needs a plan of
+ * the pattern (about 2 bytes per nonzero and 4 MB on the device, built by
+ * the first such solve) and most of the device's CUs at once: when other
+ * work holds them for more than 50 ms the solve runs in the general form, as
+ * do this mesh's later ones.  Such solves of one process run one after the
+ * other per device.
+ * The forms round differently; the true residual is always computed
  * with `values` as given.  Returns FE_ENOCONV (x written) at max_iter,
  * FE_EBREAKDOWN on p.Ap <= 0 or non-finite scalars.  info may be NULL.
  */
@@ -466,7 +475,7 @@ void fe_serve_destroy(fe_server server);
 /* ---- measurement hooks --------------------------------------------------------
  * With profiling on, the library brackets its launches with HIP events on the
  * context's stream: slot 0 = the SpMV launch of one PCG iteration (fused with
- * p.Ap), slot 1 = one fe_assemble call (all colours), slot 2 = the vector
+ * p.Ap; a solve that runs in one launch is one interval), slot 1 = one fe_assemble call (all colours), slot 2 = the vector
  * updates of one PCG iteration, slot 3 = fe_apply_dirichlet, slot 4 = one
  * element-vector pass (fe_residual, fe_gradient, fe_divergence and those of
  * fe_fractional_step).

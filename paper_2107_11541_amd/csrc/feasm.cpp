@@ -425,6 +425,7 @@ void mesh_release(fe_mesh_s *m)
     m->allocs.clear();
     m->cg = CGWork();
     m->sym = fe_mesh_s::SymState();
+    m->resident = fe_mesh_s::ResidentState();
     m->step_work = nullptr;
     m->scalar_work = nullptr;
     m->wall = DevWall();
@@ -765,6 +766,105 @@ static fe_status ensure_sym(fe_mesh_s *m)
     return FE_OK;
 }
 
+// Solves that run in one launch hold most of the device's CUs until they end,
+// and two of them at once could each hold CUs that the other waits for: they
+// run one after the other per device (a solve is synchronous to its caller).
+constexpr int kResidentDevices = 64;
+static std::mutex g_resident_mu[kResidentDevices];
+// Longest wait of such a solve's groups for each other, in 10 ns: 50 ms, far
+// beyond any iteration (~10 us), short for a caller that then runs the solve
+// in the general form.
+constexpr unsigned long long kResidentLimit = 5000000;
+
+// The plan of the mesh's one-launch solves, built on first use.  A pattern
+// that does not fit, or a device without room for the plan, leaves state -1.
+static fe_status ensure_resident(fe_mesh_s *m)
+{
+    fe_mesh_s::ResidentState &Y = m->resident;
+    if (Y.state != 0) return FE_OK;
+    fe_ctx_s *c = m->ctx;
+    const DevMesh &d = m->dm;
+    fe_mesh_s::ResidentState N;
+    N.state = -1;
+    if (c->device >= kResidentDevices || !resident_shape(4, d.N, d.max_row, c->cus, N.G, N.R)) {
+        Y = N;
+        return FE_OK;
+    }
+    const size_t ow = resident_off_words(N.G, N.R, d.max_row) * sizeof(uint32_t);
+    const size_t hw = ((size_t)N.G * kResidentHalo + N.G) * sizeof(int32_t);
+    const size_t sw = kResidentSlots * sizeof(unsigned long long);
+    void *p = nullptr;
+    fe_status s = mesh_alloc(m, &p, ow + sw + hw + sizeof(ResidentOut));
+    if (s == FE_ENOMEM) {
+        Y = N;
+        return FE_OK;
+    }
+    if (s != FE_OK) return s;
+    N.slots = (unsigned long long *)p;
+    N.out = (ResidentOut *)(N.slots + kResidentSlots);
+    N.plan.off = (uint32_t *)(N.out + 1);
+    N.plan.hcol = (int32_t *)((char *)N.plan.off + ow);
+    N.plan.nh = N.plan.hcol + (size_t)N.G * kResidentHalo;
+    int32_t bad = 0;
+    HIPCALL(c, hipMemsetAsync(N.out, 0, sizeof(ResidentOut), c->stream));
+    HIPCALL(c, launch_resident_plan(d, N.plan, N.G, N.R, &N.out->abandoned, c->stream));
+    HIPCALL(c, hipMemcpyAsync(c->host, &N.out->abandoned, sizeof bad, hipMemcpyDeviceToHost, c->stream));
+    if ((s = sync(c)) != FE_OK) return s;
+    memcpy(&bad, c->host, sizeof bad);
+    if (bad) {
+        mesh_free_ptr(m, p);
+        N = fe_mesh_s::ResidentState();
+        N.state = -1;
+    } else {
+        N.state = 1;
+    }
+    Y = N;
+    return FE_OK;
+}
+
+// Whether a solve in precision T of this mesh fits the one-launch form.
+template <class T>
+static bool resident_fits(const fe_mesh_s *m)
+{
+    int G, R;
+    return m->resident.state == 1 && resident_shape(sizeof(T), m->dm.N, m->dm.max_row, m->ctx->cus, G, R);
+}
+
+// Runs the one-launch form (resident.hip) of a PCG solve of `values` in
+// precision T (resident_fits).  ran: it did, o holds its outcome; else the
+// general form has to run, on the x that was passed in (o.abandoned == 0:
+// the pair check behind `bad` failed).  Synchronises the stream.
+template <class T>
+static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, const T *b, T *x, double rtol,
+                              int max_iter, bool x_zero, const int32_t *bad, ResidentOut &o, bool &ran)
+{
+    fe_ctx_s *c = m->ctx;
+    const DevMesh &d = m->dm;
+    const fe_mesh_s::ResidentState &Y = m->resident;
+    constexpr bool f64 = sizeof(T) == 8;
+    T *z = f64 ? (T *)w.z : (T *)w.z32, *x0 = f64 ? (T *)w.q : (T *)w.q32;
+    ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, Y.out, bad, rtol, kResidentLimit,
+                   (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
+    {
+        std::lock_guard<std::mutex> lk(g_resident_mu[c->device]);
+        {
+            ProfScope ps(c, 0);
+            HIPCALL(c, launch_resident<T>(A, d.max_row, Y.G, c->stream));
+        }
+        HIPCALL(c, hipMemcpyAsync(c->host, Y.out, sizeof o, hipMemcpyDeviceToHost, c->stream));
+        const fe_status s = sync(c);
+        if (s != FE_OK) return s;
+    }
+    memcpy(&o, c->host, sizeof o);
+    ran = o.ran != 0 && !o.abandoned;
+    if (o.abandoned) {
+        m->resident.state = -1;
+        if (o.wrote_x && !x_zero)
+            HIPCALL(c, hipMemcpyAsync(x, x0, (size_t)d.N * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
+    }
+    return FE_OK;
+}
+
 // Chooses the SpMV of an FP64 solve of `values` on w: the symmetric one when
 // the mesh has its map and every mirrored pair of values agrees (see
 // launch_sym_pack; the packed copy then holds the stored entry of each
@@ -787,13 +887,42 @@ static fe_status select_sym(fe_mesh_s *m, CGWork &w, const double *values)
 // FP64 Jacobi-PCG on the work buffers w: fills the iteration count and the
 // recursive residual of inf, and the outcome of the solve in result
 // (FE_OK, FE_ENOCONV or FE_EBREAKDOWN).  use_sym: run the symmetric SpMV
-// when the matrix allows it (select_sym), else the general one.
+// when the matrix allows it (select_sym), else the general one.  finished:
+// the true residual of inf is filled too (the one-launch form computes it).
 fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *rhs, double *x, double rtol,
-                   int max_iter, bool allow_graphs, fe_cg_info &inf, fe_status &result, bool use_sym)
+                   int max_iter, bool allow_graphs, fe_cg_info &inf, fe_status &result, bool use_sym, bool &finished)
 {
+    finished = false;
     fe_ctx_s *c = m->ctx;
     int32_t fl[4];
-    fe_status s = use_sym ? select_sym(m, w, values) : FE_OK;
+    fe_status s = FE_OK;
+    bool refused = false;
+    if (use_sym) {
+        // the whole solve in one launch where the matrix fits the registers
+        if ((s = ensure_sym(m)) != FE_OK) return s;
+        if (m->sym.state == 1 && (s = ensure_resident(m)) != FE_OK) return s;
+        if (m->sym.state == 1 && resident_fits<double>(m)) {
+            fe_mesh_s::SymState &Y = m->sym;
+            HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, nullptr, Y.bad, c->stream));
+            ResidentOut o;
+            bool ran;
+            s = resident_pcg<double>(m, w, values, rhs, x, rtol, max_iter, false, Y.bad, o, ran);
+            if (s != FE_OK) return s;
+            if (ran) {
+                inf.symmetric_spmv = 1;
+                inf.iterations = o.iterations;
+                inf.outer_iterations = 1;
+                inf.rel_residual = o.bb > 0 ? std::sqrt(o.rr / o.bb) : std::sqrt(o.rr);
+                inf.true_rel_residual = o.bb > 0 ? std::sqrt(o.true_rr / o.bb) : std::sqrt(o.true_rr);
+                if (o.status == FE_EBREAKDOWN) result = FE_EBREAKDOWN;
+                else if (rtol > 0.0 && !o.done) result = FE_ENOCONV;
+                finished = true;
+                return FE_OK;
+            }
+            refused = !o.abandoned;
+        }
+    }
+    if (use_sym && !refused) s = select_sym(m, w, values);
     if (s != FE_OK) return s;
     s = run_pcg<double>(m, w, values, rhs, x, rtol, max_iter, false, fl, allow_graphs);
     inf.symmetric_spmv = w.sym.vals ? 1 : 0;
@@ -812,17 +941,19 @@ fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *
     return FE_OK;
 }
 
-// The true residual ||b - A x|| / ||b|| in FP64 (w.d64 and w.part as work),
-// then the solve's status and info.
+// The true residual ||b - A x|| / ||b|| in FP64 (w.d64 and w.part as work)
+// unless it is known, then the solve's status and info.
 fe_status pcg_finish(fe_mesh_s *m, CGWork &w, const double *values, const double *rhs, const double *x, int max_iter,
-                     fe_cg_info &inf, fe_status result, fe_cg_info *info)
+                     fe_cg_info &inf, fe_status result, fe_cg_info *info, bool finished)
 {
     fe_ctx_s *c = m->ctx;
-    HIPCALL(c, residual_f64(m->dm, values, rhs, x, w.d64, w.part, c->scratch + 2048, c->stream));
-    HIPCALL(c, hipMemcpyAsync(c->host, c->scratch + 2048, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
-    fe_status s = sync(c);
-    if (s != FE_OK) return s;
-    inf.true_rel_residual = c->host[1] > 0 ? std::sqrt(c->host[0] / c->host[1]) : std::sqrt(c->host[0]);
+    if (!finished) {
+        HIPCALL(c, residual_f64(m->dm, values, rhs, x, w.d64, w.part, c->scratch + 2048, c->stream));
+        HIPCALL(c, hipMemcpyAsync(c->host, c->scratch + 2048, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        fe_status s = sync(c);
+        if (s != FE_OK) return s;
+        inf.true_rel_residual = c->host[1] > 0 ? std::sqrt(c->host[0] / c->host[1]) : std::sqrt(c->host[0]);
+    }
     if (info) *info = inf;
     if (result == FE_EBREAKDOWN) return fail(c, FE_EBREAKDOWN, "CG breakdown (p.Ap <= 0 or non-finite)");
     if (result == FE_ENOCONV) return fail(c, FE_ENOCONV, "CG did not reach rtol in %d iterations", max_iter);
@@ -890,8 +1021,11 @@ fe_status fe_ctx_create(int device, void *hip_stream, fe_ctx *out)
     if (hipSetDevice(device) != hipSuccess) return FE_EDEVICE;
     if (init_spmv_grid(device) != hipSuccess) return FE_EDEVICE;
     if (noalloc_init(device) != hipSuccess) return FE_EDEVICE;
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return FE_EDEVICE;
     auto *c = new fe_ctx_s();
     c->device = device;
+    c->cus = cus;
     c->stream = (hipStream_t)hip_stream;
     if (hipMalloc((void **)&c->scratch, (2048 + 64) * sizeof(double)) != hipSuccess ||
         hipHostMalloc((void **)&c->host, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
@@ -1193,10 +1327,12 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
     const DevMesh &d = m->dm;
     fe_cg_info inf{};
     fe_status result = FE_OK;
+    bool finished = false;
     if (prec == FE_FP64) {
-        if ((s = pcg_fp64(m, w, values, rhs, x, rtol, max_iter, true, inf, result, true)) != FE_OK) return s;
+        if ((s = pcg_fp64(m, w, values, rhs, x, rtol, max_iter, true, inf, result, true, finished)) != FE_OK) return s;
     } else {
-        HIPCALL(c, cast_f64_f32(d.nnz, values, w.v32, c->stream));
+        if ((s = ensure_resident(m)) != FE_OK) return s;
+        bool cast = false;   // w.v32 holds the values in FP32 (the general form's)
         int used = 0, outer = 0;
         double rel = 0.0;
         result = FE_ENOCONV;
@@ -1221,8 +1357,20 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
             const double tol_in = std::max(0.5 * need, 1e-5);
             HIPCALL(c, scale_f64_to_f32(d.N, 1.0 / rn, w.d64, w.r32, c->stream));
             int32_t fl[4];
-            s = run_pcg<float>(m, m->cg, w.v32, w.r32, w.x32, tol_in, max_iter - used, true, fl);
-            if (s != FE_OK) return s;
+            ResidentOut o;
+            bool ran = false;
+            if (resident_fits<float>(m)) {
+                s = resident_pcg<float>(m, w, values, w.r32, w.x32, tol_in, max_iter - used, true, nullptr, o, ran);
+                if (s != FE_OK) return s;
+            }
+            if (ran) {
+                fl[2] = o.iterations;
+            } else {
+                if (!cast) HIPCALL(c, cast_f64_f32(d.nnz, values, w.v32, c->stream));
+                cast = true;
+                s = run_pcg<float>(m, m->cg, w.v32, w.r32, w.x32, tol_in, max_iter - used, true, fl);
+                if (s != FE_OK) return s;
+            }
             used += fl[2];
             HIPCALL(c, add_f32_to_f64(d.N, rn, w.x32, x, c->stream));
             if (fl[2] == 0) break;   // no progress possible (e.g. immediate breakdown)
@@ -1231,7 +1379,7 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
         inf.outer_iterations = outer + (result == FE_OK ? 0 : 1);
         inf.rel_residual = rel;
     }
-    return pcg_finish(m, w, values, rhs, x, max_iter, inf, result, info);
+    return pcg_finish(m, w, values, rhs, x, max_iter, inf, result, info, finished);
 }
 
 fe_status fe_cg_solve_noalloc(fe_mesh m, const double *values, const double *rhs, double *x, double rtol,
@@ -1260,9 +1408,10 @@ fe_status fe_cg_solve_noalloc(fe_mesh m, const double *values, const double *rhs
     noalloc_layout(base, m->dm.N, max_iter, w);
     fe_cg_info inf{};
     fe_status result = FE_OK;
-    fe_status s = pcg_fp64(m, w, values, rhs, x, rtol, max_iter, false, inf, result, false);
+    bool finished;
+    fe_status s = pcg_fp64(m, w, values, rhs, x, rtol, max_iter, false, inf, result, false, finished);
     if (s != FE_OK) return s;
-    return pcg_finish(m, w, values, rhs, x, max_iter, inf, result, info);
+    return pcg_finish(m, w, values, rhs, x, max_iter, inf, result, info, finished);
 }
 
 // ---- explicit step ----------------------------------------------------------

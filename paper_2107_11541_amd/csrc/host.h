@@ -52,6 +52,7 @@ struct ProfSlot {
 
 struct fe_ctx_s {
     int device = 0;
+    int cus = 0;                  // compute units of the device
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;   // private stream that PCG graphs are recorded on (never run on)
     std::string err;
@@ -95,6 +96,15 @@ struct fe_mesh_s {
         int32_t *bad = nullptr;  // the symmetric-pair check word
         int64_t n_packed = 0;
     } sym;
+    // one-launch solves (resident.hip): their plan of the pattern, built on
+    // first use (state 0: not built, 1: built, -1: none, or a solve was
+    // abandoned because other work held the CUs)
+    struct ResidentState {
+        int state = 0, G = 0, R = 0;
+        feasm::ResidentPlan plan;
+        unsigned long long *slots = nullptr;   // the groups' meeting slots
+        feasm::ResidentOut *out = nullptr;
+    } resident;
 };
 
 namespace feasm {

@@ -117,7 +117,7 @@ struct SymSpmv {
 // map (mstart: its per-row mirror-run starts) and sets *bad to 1 when a
 // mirror entry a_ij differs from the stored a_ji by more than 2^-40
 // max(|a_ij|, |a_ji|, sqrt|a_ii a_jj|) (or either is not finite).  *bad is
-// set to 0 first.
+// set to 0 first.  packed null: the check alone.
 hipError_t launch_sym_pack(const DevMesh &m, const SymSpmv &map, const uint8_t *mstart, const double *vals,
                            double *packed, int32_t *bad, hipStream_t s);
 
@@ -194,6 +194,48 @@ struct DevRowPlan {
 hipError_t launch_assemble_block(const DevMesh &m, const DevRowPlan &r, int form, double dt, const double *u,
                                  const double *rho, const double *mu, double *values, double *rhs,
                                  AsmStatus *status, hipStream_t s);
+
+// A whole Jacobi-PCG solve in one launch with the matrix in registers
+// (resident.hip): up to resident_rows() rows of at most 27 entries per
+// thread, 256 threads per group, one group per CU.
+constexpr int kResidentThreads = 256, kResidentMaxGroups = 256, kResidentCopies = 8;
+constexpr int kResidentHalo = 4096;      // columns outside a group's rows
+constexpr size_t kResidentSlots = (size_t)3 * kResidentCopies * 2 * kResidentMaxGroups;
+struct ResidentOut {
+    int32_t ran, abandoned, wrote_x, done, status, iterations;
+    double rr, bb, true_rr;      // recursive ||r||^2, ||b||^2, (FP64) ||b - A x||^2
+};
+// The groups' windows (k_resident_plan): halo columns [G][kResidentHalo],
+// their number [G], and the window places of the entries.
+struct ResidentPlan {
+    uint32_t *off = nullptr;
+    int32_t *hcol = nullptr, *nh = nullptr;
+};
+struct ResidentArgs {
+    ResidentPlan plan;
+    const int32_t *rowptr, *diagpos;
+    const double *vals;          // converted to T as they are read
+    const void *b;               // T [N]
+    void *x, *z, *x0;            // T [N]: solution (in: first guess unless x_zero), exchange, copy of the guess
+    unsigned long long *slots;   // kResidentSlots
+    ResidentOut *out;
+    const int32_t *bad;          // nothing runs when *bad != 0 (null: no such word)
+    double rtol;
+    unsigned long long limit;    // longest wait, in 10 ns
+    int N, R, max_iter, x_zero;  // R: rows per group
+};
+// Entries per row that the kernel is built for, 0 for longer rows; rows per
+// thread that then fit the registers (a row takes W values and W / 2 words).
+constexpr int resident_width(int max_row) { return max_row <= 16 ? 16 : max_row <= 27 ? 27 : 0; }
+constexpr int resident_rows(size_t elem_bytes, int W) { return W == 27 ? (elem_bytes == 8 ? 6 : 10) : (elem_bytes == 8 ? 9 : 12); }
+// Groups and rows per group for N rows on a device of `cus` CUs; false: the
+// matrix does not fit.
+bool resident_shape(int elem_bytes, int64_t N, int max_row, int cus, int &G, int &R);
+size_t resident_off_words(int G, int R, int max_row);
+// Fills the plan; *bad = 1 when a group's halo does not fit.
+hipError_t launch_resident_plan(const DevMesh &m, const ResidentPlan &P, int G, int R, int32_t *bad, hipStream_t s);
+template <class T>
+hipError_t launch_resident(const ResidentArgs &A, int max_row, int G, hipStream_t s);
 
 // Solver launchers (solver_kernels.hip).
 struct CGWork {

@@ -951,7 +951,8 @@ __global__ void __launch_bounds__(kTB) k_sym_pack(SymSpmv sm, const int32_t *__r
             }
         }
         __syncthreads();
-        for (int t = tid; t < ns; t += kTB) packed[(int64_t)d0.y + t] = win[shift + t];
+        if (packed)
+            for (int t = tid; t < ns; t += kTB) packed[(int64_t)d0.y + t] = win[shift + t];
         if (row < R) {
             for (int m = sub; m < ml; m += kTPR) {
                 const double a = vals[p0 + ms + m];
