@@ -305,7 +305,10 @@ fe_status fe_cg_solve_noalloc(fe_mesh mesh, const double *values, const double *
  * stages use the operator of fe_assemble(MOMENTUM) without its mass term,
  * applied to the velocity element by element (no matrix is formed).  All
  * arrays are device, mesh numbering, [k][n_nodes] rows, FP64.  Each call
- * synchronises the stream and fails with FE_EBADELEM on det J <= 0. */
+ * synchronises the stream and fails with FE_EBADELEM on det J <= 0.  The
+ * passes keep a work array on the mesh from their first call on (32 bytes
+ * per row of every element block, about 62 bytes per HEX08 element; without
+ * room for it they run colour by colour). */
 
 /* Scalar transport (the heat and species equations, which the paper
  * advances with the same Runge-Kutta stages and no algebraic solver,

@@ -1034,6 +1034,382 @@ void launch_type(const AsmLaunch &L, const KArgs &k, int op, bool mixed, hipStre
     }
 }
 
+// ---- HEX08 by sums over one direction at a time ------------------------------
+// The trilinear basis and its 2x2x2 rule are products of the two-point rule of
+// a line, L0, L1 = (1 -+ t)/2 at t = -+1/sqrt3, so interpolating to the points
+// and adding up over them go direction by direction: 3 operations per pair of
+// values and direction instead of 8 products per point and field.
+constexpr double kHexP = 0.5 * (1.0 + Hex::kG);   // L0 at the first point = L1 at the second
+
+// Values at the ends of a line (a, b) -> at its two points.
+__device__ __forceinline__ void line_points(double a, double b, double &p0, double &p1)
+{
+    const double d = a - b;
+    p0 = fma(kHexP, d, b);
+    p1 = fma(-kHexP, d, a);
+}
+// Sums over a line's two points (p0, p1) weighted with L0 and L1 (the
+// transpose of line_points, which is symmetric).
+__device__ __forceinline__ void line_nodes(double p0, double p1, double &a, double &b) { line_points(p0, p1, a, b); }
+
+// Local node of tensor position (ix, iy, iz).
+__host__ __device__ constexpr int hex_node(int ix, int iy, int iz) { return 4 * iz + (iy ? (ix ? 2 : 3) : ix); }
+
+// A nodal field on the slab of Gauss points zeta = z: its values (f) and zeta
+// derivatives (h) at the four lines (ix, iy).
+__device__ __forceinline__ void hex_slab(const double *f, const int (&ln)[8], double z, double (&v)[2][2],
+                                         double (&h)[2][2])
+{
+#pragma unroll
+    for (int ix = 0; ix < 2; ++ix)
+#pragma unroll
+        for (int iy = 0; iy < 2; ++iy) {
+            const double a = f[ln[hex_node(ix, iy, 0)]], b = f[ln[hex_node(ix, iy, 1)]];
+            h[ix][iy] = 0.5 * (b - a);
+            v[ix][iy] = fma(z, h[ix][iy], 0.5 * (a + b));
+        }
+}
+// Lines (ix, iy) -> the slab's points (gx, gy).
+__device__ __forceinline__ void hex_points(const double (&v)[2][2], double (&p)[2][2])
+{
+    double t[2][2];
+#pragma unroll
+    for (int iy = 0; iy < 2; ++iy) line_points(v[0][iy], v[1][iy], t[0][iy], t[1][iy]);
+#pragma unroll
+    for (int gx = 0; gx < 2; ++gx) line_points(t[gx][0], t[gx][1], p[gx][0], p[gx][1]);
+}
+// Reference gradient of a field on the slab: d/dxi at (gy), d/deta at (gx),
+// d/dzeta at (gx, gy).
+struct SlabGrad {
+    double x[2], y[2], z[2][2];
+};
+__device__ __forceinline__ void hex_grad(const double (&v)[2][2], const double (&h)[2][2], SlabGrad &g)
+{
+    line_points(0.5 * (v[1][0] - v[0][0]), 0.5 * (v[1][1] - v[0][1]), g.x[0], g.x[1]);
+    line_points(0.5 * (v[0][1] - v[0][0]), 0.5 * (v[1][1] - v[1][0]), g.y[0], g.y[1]);
+    hex_points(h, g.z);
+}
+// Cofactors C of the Jacobian at the slab's point (gx, gy): C[j] = det J times
+// the physical gradient of reference coordinate j; det J is returned.
+__device__ __forceinline__ double hex_cofactors(const SlabGrad (&X)[3], int gx, int gy, double (&C)[3][3])
+{
+    double c0[3], c1[3], c2[3];
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        c0[i] = X[i].x[gy];
+        c1[i] = X[i].y[gx];
+        c2[i] = X[i].z[gx][gy];
+    }
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        const int j = (i + 1) % 3, k = (i + 2) % 3;
+        C[0][i] = c1[j] * c2[k] - c1[k] * c2[j];
+        C[1][i] = c2[j] * c0[k] - c2[k] * c0[j];
+        C[2][i] = c0[j] * c1[k] - c0[k] * c1[j];
+    }
+    return c0[0] * C[0][0] + c0[1] * C[0][1] + c0[2] * C[0][2];
+}
+
+// An element-vector pass on one HEX08 element (FP64; the terms of
+// element_vector_point, fields in LDS as there): per component a source s
+// tested with N_a and a flux q tested with the reference gradient of N_a.
+// One slab of four points after the other (a rolled loop: both unrolled do
+// not fit 256 registers).
+template <int OP, int FORM>
+__device__ __forceinline__ void hex_vector(const double *nd, int T, const int (&ln0)[8],
+                                           double (&B)[OpTraits<OP>::NRHS][8], double &mindet, double inv_dt, double Dk)
+{
+    constexpr int NRHS = OpTraits<OP>::NRHS;
+    constexpr int NQ = OP == OP_RES ? 3 : OP == OP_GRD ? 0 : 1;       // components with a flux
+    constexpr int NS = OP == OP_DIV ? 0 : NRHS;                       // components with a source
+    constexpr int NG = OP == OP_RES ? 3 : OP == OP_DIV ? 0 : 1;       // fields whose gradient is needed
+    constexpr bool FULL = (FORM & FE_FORM_FULL_STRESS) != 0, EMAC = (FORM & FE_FORM_EMAC) != 0;
+    int ln[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) ln[a] = ln0[a];
+#pragma unroll 1
+    for (int gz = 0; gz < 2; ++gz) {
+        const double z = gz ? Hex::kG : -Hex::kG;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) asm volatile("" : "+v"(ln[a]));   // fields are read again, not kept
+        SlabGrad X[3], G[NG ? NG : 1];
+        double up[3][2][2], rp[2][2], mp[2][2], v[2][2], h[2][2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            hex_slab(nd + i * T, ln, z, v, h);
+            hex_grad(v, h, X[i]);
+        }
+        if constexpr (OP != OP_GRD) {
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                hex_slab(nd + (3 + i) * T, ln, z, v, h);
+                if constexpr (OP == OP_RES) hex_grad(v, h, G[i]);
+                hex_points(v, up[i]);
+            }
+            hex_slab(nd + 6 * T, ln, z, v, h);
+            hex_points(v, rp);
+        }
+        if constexpr (OP == OP_RES) {
+            hex_slab(nd + 7 * T, ln, z, v, h);
+            hex_points(v, mp);
+        }
+        if constexpr (OP == OP_GRD || OP == OP_SRS) {
+            hex_slab(nd + (OP == OP_GRD ? 3 : 7) * T, ln, z, v, h);
+            hex_grad(v, h, G[0]);
+        }
+        double s[NS ? NS : 1][2][2], q0[NQ ? NQ : 1][2] = {}, q1[NQ ? NQ : 1][2] = {}, q2[NQ ? NQ : 1][2][2];
+#pragma unroll
+        for (int gx = 0; gx < 2; ++gx)
+#pragma unroll
+            for (int gy = 0; gy < 2; ++gy) {
+                double C[3][3];
+                const double det = hex_cofactors(X, gx, gy, C);
+                mindet = fmin(mindet, det);
+                double uh[3];   // det J times the velocity's reference components
+                if constexpr (OP != OP_GRD) {
+#pragma unroll
+                    for (int j = 0; j < 3; ++j)
+                        uh[j] = C[j][0] * up[0][gx][gy] + C[j][1] * up[1][gx][gy] + C[j][2] * up[2][gx][gy];
+                }
+                if constexpr (OP == OP_GRD) {
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+                        s[i][gx][gy] = C[0][i] * G[0].x[gy] + C[1][i] * G[0].y[gx] + C[2][i] * G[0].z[gx][gy];
+                } else if constexpr (OP == OP_DIV) {
+                    const double w = rp[gx][gy] * inv_dt;
+                    q0[0][gy] += w * uh[0];
+                    q1[0][gx] += w * uh[1];
+                    q2[0][gx][gy] = w * uh[2];
+                } else {
+                    const double r = rp[gx][gy];
+                    // viscosity (or rho D) over det J
+                    const double k = (OP == OP_RES ? mp[gx][gy] : r * Dk) / det;
+                    double D[3][3];   // k C C^T: flux j = sum_l D[j][l] d/dxi_l
+                    if constexpr (!FULL) {
+#pragma unroll
+                        for (int j = 0; j < 3; ++j)
+#pragma unroll
+                            for (int l = j; l < 3; ++l)
+                                D[j][l] = D[l][j] = k * (C[j][0] * C[l][0] + C[j][1] * C[l][1] + C[j][2] * C[l][2]);
+                    }
+                    double gp[3][3], div = 0.0;   // det J times du_i / dx_j
+                    if constexpr (OP == OP_RES && (FULL || EMAC)) {
+#pragma unroll
+                        for (int i = 0; i < 3; ++i)
+#pragma unroll
+                            for (int j = 0; j < 3; ++j)
+                                gp[i][j] = C[0][j] * G[i].x[gy] + C[1][j] * G[i].y[gx] + C[2][j] * G[i].z[gx][gy];
+                        div = gp[0][0] + gp[1][1] + gp[2][2];
+                    }
+#pragma unroll
+                    for (int i = 0; i < NG; ++i) {
+                        const double g0 = G[i].x[gy], g1 = G[i].y[gx], g2 = G[i].z[gx][gy];
+                        double adv = uh[0] * g0 + uh[1] * g1 + uh[2] * g2;
+                        if constexpr (EMAC) adv += div * up[i][gx][gy];
+                        s[i][gx][gy] = -r * adv;
+                        double f[3];
+                        if constexpr (FULL) {
+                            double t[3];
+#pragma unroll
+                            for (int j = 0; j < 3; ++j) t[j] = k * (gp[i][j] + gp[j][i]);
+#pragma unroll
+                            for (int j = 0; j < 3; ++j) f[j] = C[j][0] * t[0] + C[j][1] * t[1] + C[j][2] * t[2];
+                        } else {
+#pragma unroll
+                            for (int j = 0; j < 3; ++j) f[j] = D[j][0] * g0 + D[j][1] * g1 + D[j][2] * g2;
+                        }
+                        q0[i][gy] -= f[0];
+                        q1[i][gx] -= f[1];
+                        q2[i][gx][gy] = -f[2];
+                    }
+                    s[NG][gx][gy] = r * det;   // lumped mass
+                }
+            }
+        // to the nodes: the slab's share of (ix, iy, iz)
+        const double L[2] = {0.5 * (1.0 - z), 0.5 * (1.0 + z)};
+#pragma unroll
+        for (int c = 0; c < NRHS; ++c) {
+            double n0[2] = {}, n1[2] = {};   // xi flux by iy (halved at ix), eta flux by ix
+            if (c < NQ) {
+                line_nodes(q0[c < NQ ? c : 0][0], q0[c < NQ ? c : 0][1], n0[0], n0[1]);
+                line_nodes(q1[c < NQ ? c : 0][0], q1[c < NQ ? c : 0][1], n1[0], n1[1]);
+            }
+#pragma unroll
+            for (int iz = 0; iz < 2; ++iz) {
+                double t[2][2], w[2][2];
+#pragma unroll
+                for (int gx = 0; gx < 2; ++gx) {
+                    double m[2];
+#pragma unroll
+                    for (int gy = 0; gy < 2; ++gy) {
+                        m[gy] = c < NS ? L[iz] * s[c < NS ? c : 0][gx][gy] : 0.0;
+                        if (c < NQ) m[gy] += (iz ? 0.5 : -0.5) * q2[c < NQ ? c : 0][gx][gy];
+                    }
+                    line_nodes(m[0], m[1], t[gx][0], t[gx][1]);
+                }
+#pragma unroll
+                for (int iy = 0; iy < 2; ++iy) line_nodes(t[0][iy], t[1][iy], w[0][iy], w[1][iy]);
+#pragma unroll
+                for (int ix = 0; ix < 2; ++ix)
+#pragma unroll
+                    for (int iy = 0; iy < 2; ++iy) {
+                        double x = w[ix][iy];
+                        if (c < NQ) x += L[iz] * ((ix ? 0.5 : -0.5) * n0[iy] + (iy ? 0.5 : -0.5) * n1[ix]);
+                        B[c][hex_node(ix, iy, iz)] += x;
+                    }
+            }
+        }
+    }
+}
+
+// ---- element-vector passes in one launch per element type ---------------------
+// One wave = one block of <= 64 elements, one element per lane.  The block's
+// fields are staged in LDS, the lanes add their vectors into the LDS sums of
+// the block's nodes in phase order, and the sums go to the block's own places
+// of a work array (no other block writes them, so no colours); k_vec_gather
+// then adds each node's block sums in block order.  The order of every sum is
+// fixed by the plan.
+template <class EL, int OP, int FORM>
+__global__ void __launch_bounds__(64, 2) k_vec(KArgs k, double *__restrict__ work, int64_t VT)
+{
+    constexpr int NEN = EL::NEN, NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
+    extern __shared__ double lds[];
+    const int blk = k.color_blk[k.blk_offset + xcd_item(blockIdx.x, gridDim.x)];
+    const int e0 = k.blk_elem_ptr[blk], ne = k.blk_elem_ptr[blk + 1] - e0;
+    const int n0 = k.blk_node_ptr[blk], T = k.blk_node_ptr[blk + 1] - n0;
+    const int lane = threadIdx.x;
+    const int64_t N = k.N;
+    double *nd = lds, *sums = nd + NF * T;   // [NF][T] fields, [NRHS][T] sums
+    const bool act = lane < ne;
+    const int e = e0 + (act ? lane : 0);
+    int ln[NEN];
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) ln[a] = k.elem_lnode[(int64_t)a * k.E + e];
+    const int ph = act ? (int)k.elem_phase[e] : -1, nph = k.blk_nphase[blk];
+    for (int t = lane; t < T; t += 64) {
+        const int g = k.blk_nodes[n0 + t];
+        double f[NF];
+        f[0] = k.X[g];
+        f[1] = k.X[N + g];
+        f[2] = k.X[2 * N + g];
+        if constexpr (OP == OP_GRD) {
+            f[3] = k.p[g];
+        } else {
+            f[3] = k.u[g];
+            f[4] = k.u[N + g];
+            f[5] = k.u[2 * N + g];
+            f[6] = k.rho[g];
+            if constexpr (OP == OP_RES) f[7] = k.mu[g];
+            if constexpr (OP == OP_SRS) f[7] = k.Y[g];
+        }
+#pragma unroll
+        for (int q = 0; q < NF; ++q) nd[q * T + t] = f[q];
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) sums[r * T + t] = 0.0;
+    }
+    __syncthreads();
+    double B[NRHS][NEN];
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r)
+#pragma unroll
+        for (int a = 0; a < NEN; ++a) B[r][a] = 0.0;
+    double mindet = __builtin_huge_val();
+    if constexpr (NEN == 8) {
+        hex_vector<OP, FORM>(nd, T, ln, B, mindet, 1.0 / k.dt, k.Dk);
+    } else {
+        Geo<EL> GE;
+        load_geo<EL>(nd, T, ln, GE);
+        Rows<EL> rows;
+#pragma unroll
+        for (int a = 0; a < NEN; ++a) rows.v[a] = ln[a];
+        double A[NEN][NEN];   // unused: no matrix
+        gauss_loop<EL, OP, double, NEN, 0>(GE, nd, nd + 3 * T, T, rows, A, B, mindet, 1.0 / k.dt, k.Dk, FORM);
+    }
+    for (int p = 0; p < nph; ++p)
+        if (ph == p) {
+#pragma unroll
+            for (int a = 0; a < NEN; ++a)
+#pragma unroll
+                for (int r = 0; r < NRHS; ++r) lds_add(&sums[r * T + ln[a]], B[r][a]);
+        }
+    double md = act ? mindet : __builtin_huge_val();
+    long long bad = (act && !(mindet > 0.0)) ? (long long)e : (long long)0x7fffffffffffffffLL;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        md = fmin(md, __shfl_xor(md, o));
+        const long long ob = __shfl_xor(bad, o);
+        bad = ob < bad ? ob : bad;
+    }
+    if (lane == 0) {
+        k.blk_mindet[blk] = md;
+        k.blk_bad[blk] = bad == 0x7fffffffffffffffLL ? -1 : bad;
+    }
+    __syncthreads();
+    for (int t = lane; t < T; t += 64)
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) work[r * VT + n0 + t] = sums[r * T + t];
+}
+
+// out[r][i] = node i's block sums in block order, one thread per node, four
+// places at a time, so that their loads are in flight together.  (Nodes of
+// one block only, ~40 %, written by k_vec itself instead: the scattered
+// stores cost k_vec 6 us on 101^3 HEX08 and saved 3.5 us here.)
+template <int NRHS>
+__global__ void __launch_bounds__(256) k_vec_gather(int64_t N, int64_t VT, const int32_t *__restrict__ ptr,
+                                                    const int32_t *__restrict__ slot,
+                                                    const double *__restrict__ work, double *__restrict__ out)
+{
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= N) return;
+    double s[NRHS];
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r) s[r] = 0.0;
+    const int q0 = ptr[i], q1 = ptr[i + 1];
+    for (int q = q0; q < q1; q += 4) {
+        int t[4];
+        double w[4][NRHS];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) t[j] = slot[q + j < q1 ? q + j : q];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int r = 0; r < NRHS; ++r) w[j][r] = work[r * VT + t[j]];
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (q + j < q1) {
+#pragma unroll
+                for (int r = 0; r < NRHS; ++r) s[r] += w[j][r];
+            }
+    }
+#pragma unroll
+    for (int r = 0; r < NRHS; ++r) out[r * N + i] = s[r];
+}
+
+template <class EL, int OP, int FORM>
+void launch_vec_op(const AsmLaunch &L, KArgs k, double *work, int64_t VT, hipStream_t s)
+{
+    k.blk_offset = L.first;
+    hipLaunchKernelGGL((k_vec<EL, OP, FORM>), dim3(L.count), dim3(64), L.lds[OP], s, k, work, VT);
+}
+
+template <class EL>
+void launch_vec(const AsmLaunch &L, const KArgs &k, int op, double *work, int64_t VT, hipStream_t s)
+{
+    switch (op) {
+    case OP_RES:
+        switch (k.form) {
+        case 0: launch_vec_op<EL, OP_RES, 0>(L, k, work, VT, s); break;
+        case 1: launch_vec_op<EL, OP_RES, 1>(L, k, work, VT, s); break;
+        case 2: launch_vec_op<EL, OP_RES, 2>(L, k, work, VT, s); break;
+        default: launch_vec_op<EL, OP_RES, 3>(L, k, work, VT, s); break;
+        }
+        break;
+    case OP_GRD: launch_vec_op<EL, OP_GRD, 0>(L, k, work, VT, s); break;
+    case OP_SRS: launch_vec_op<EL, OP_SRS, 0>(L, k, work, VT, s); break;
+    default: launch_vec_op<EL, OP_DIV, 0>(L, k, work, VT, s); break;
+    }
+}
+
 // ---- momentum operator with the full-stress viscous term: 3x3 blocks ------
 // Eq. (1)'s viscous term -div(2 mu eps(u)) tested with N_a e_i couples the
 // velocity components.  Row (a, i), column (b, k) of the element matrix:
@@ -1542,6 +1918,31 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, m.own_G,
+                           a.status_out ? a.status_out : a.status);
+        return hipGetLastError();
+    }
+    if (a.op >= OP_RES && a.vec_work) {
+        // element-vector passes: one launch per element type, then the gather
+        k.color_blk = m.vec_blk;
+        for (const AsmLaunch &L : m.vec_launches) {
+            switch (L.nen) {
+            case 8: launch_vec<Hex>(L, k, a.op, a.vec_work, m.vec_T, s); break;
+            case 6: launch_vec<Pen>(L, k, a.op, a.vec_work, m.vec_T, s); break;
+            case 5: launch_vec<Pyr>(L, k, a.op, a.vec_work, m.vec_T, s); break;
+            case 4: launch_vec<Tet>(L, k, a.op, a.vec_work, m.vec_T, s); break;
+            default: return hipErrorInvalidValue;
+            }
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
+        const dim3 grid((unsigned)((m.N + 255) / 256)), block(256);
+        switch (a.op) {
+        case OP_RES: hipLaunchKernelGGL(k_vec_gather<4>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
+        case OP_GRD: hipLaunchKernelGGL(k_vec_gather<3>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
+        case OP_SRS: hipLaunchKernelGGL(k_vec_gather<2>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
+        default: hipLaunchKernelGGL(k_vec_gather<1>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
+        }
+        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, m.nblk,
                            a.status_out ? a.status_out : a.status);
         return hipGetLastError();
     }

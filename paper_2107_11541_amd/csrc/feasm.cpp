@@ -120,6 +120,11 @@ void for_each_array(MeshImage &I, DevMesh &d, AsmStatus **status, F f)
         v(&d.own_off, I.O.tk_off);
         v(&d.own_phase, I.O.tk_phase);
     }
+    if (d.vec_T) {
+        v(&d.vec_blk, I.vec_blk);
+        v(&d.node_slot_ptr, P.node_slot_ptr);
+        v(&d.node_slot, P.node_slot);
+    }
     v(&d.spmv_desc, I.spmv_desc);
     v(&d.spmv_roff, I.spmv_roff);
     v(&d.spmv_lidx, I.spmv_lidx);
@@ -151,6 +156,7 @@ void MeshImage::clear()
     spmv_roff.clear();
     spmv_lidx.clear();
     spmv_cols.clear();
+    vec_blk.clear();
     d = DevMesh();
 }
 
@@ -166,13 +172,14 @@ static thread_local std::vector<std::vector<int32_t>> t_spmv_stamp, t_spmv_loc; 
 
 int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double *coords, int64_t n_elems,
                  const int32_t *conn, int64_t n_dirichlet, const int32_t *dirichlet_nodes, bool renumber,
-                 MeshImage &I, std::string &err, bool owner_plan)
+                 MeshImage &I, std::string &err, bool owner_plan, bool vector_passes)
 {
     if (n_dirichlet < 0 || (n_dirichlet > 0 && !dirichlet_nodes)) {
         err = "bad Dirichlet list";
         return FE_EINVAL;
     }
     Plan &P = I.P;
+    P.want_gather = vector_passes;
     int st = build_plan(stride, types, n_nodes, coords, n_elems, conn, renumber, P, err);
     if (st != FE_OK) return st;
     I.is_dir.assign(n_nodes, 0);
@@ -368,6 +375,22 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
         }
         d.launches.push_back(L);
     }
+    // the element-vector passes: one launch per element type over its blocks
+    d.vec_launches.clear();
+    I.vec_blk.clear();
+    if (vector_passes) {
+        d.vec_T = P.blk_node_ptr.back();
+        for (int nen : {8, 6, 5, 4}) {
+            AsmLaunch L{nen, (int)I.vec_blk.size(), 0, {0, 0, 0, 0, 0, 0, 0}};
+            for (const AsmLaunch &q : d.launches)
+                if (q.nen == nen)
+                    for (int op = 0; op < kNumOps; ++op) L.lds[op] = std::max(L.lds[op], q.lds[op]);
+            for (int64_t b = 0; b < d.nblk; ++b)
+                if (P.blk_nen[b] == nen) I.vec_blk.push_back((int32_t)b);
+            L.count = (int)I.vec_blk.size() - L.first;
+            if (L.count) d.vec_launches.push_back(L);
+        }
+    }
     // the owner plan of the matrix assembly (meshes of one element type)
     I.O = OwnerPlan();
     if (owner_plan && P.etype.empty()) {
@@ -395,8 +418,10 @@ fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes)
         if (!*p) return fail(m->ctx, FE_ENOMEM, "arena: no room for %zu bytes", bytes);
     } else {
         hipError_t e = hipMalloc(p, bytes);
-        if (e != hipSuccess)
+        if (e != hipSuccess) {
+            (void)hipGetLastError();   // callers may go on without the memory
             return fail(m->ctx, FE_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
+        }
     }
     m->allocs.push_back(*p);
     m->bytes += m->arena ? DevArena::round(bytes) : bytes;
@@ -426,6 +451,7 @@ void mesh_release(fe_mesh_s *m)
     m->cg = CGWork();
     m->sym = fe_mesh_s::SymState();
     m->resident = fe_mesh_s::ResidentState();
+    m->vec_work = nullptr;
     m->step_work = nullptr;
     m->scalar_work = nullptr;
     m->wall = DevWall();
@@ -600,8 +626,18 @@ fe_status element_vectors(fe_mesh_s *m, int op, double dt, const double *u, cons
                           AsmStatus *defer = nullptr)
 {
     fe_ctx_s *c = m->ctx;
+    if (!m->vec_work && !m->vec_off && m->dm.vec_T) {
+        const fe_status s = mesh_alloc(m, (void **)&m->vec_work, 4 * (size_t)m->dm.vec_T * sizeof(double));
+        if (s == FE_ENOMEM) {
+            m->vec_work = nullptr;
+            m->vec_off = true;
+        } else if (s != FE_OK) {
+            return s;
+        }
+    }
     AsmArgs a{};
     a.m = &m->dm;
+    a.vec_work = m->vec_work;
     a.op = op;
     a.dt = dt;
     a.u = u;

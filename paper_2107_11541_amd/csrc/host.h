@@ -72,6 +72,8 @@ struct fe_mesh_s {
     size_t bytes = 0;
     feasm::AsmStatus *status = nullptr;  // + per-block scratch
     feasm::CGWork cg;
+    double *vec_work = nullptr;          // element-vector passes: [4][vec_T] block sums
+    bool vec_off = false;                // no room for vec_work: the passes run colour by colour
     double *step_work = nullptr;         // explicit step: u0 [3][N], residual + mass [4][N], f [N], g [3][N]
     feasm::DevWall wall;                 // wall faces of the wall model (F = 0: none)
     double *scalar_work = nullptr;       // explicit scalar step: Y0 [N], residual + mass [2][N]
@@ -128,6 +130,7 @@ struct MeshImage {
     std::vector<uint16_t> spmv_roff;
     std::vector<uint8_t> spmv_lidx;
     std::vector<int32_t> spmv_cols;
+    std::vector<int32_t> vec_blk;   // blocks by element type (element-vector passes)
     DevMesh d;                 // sizes filled, device pointers null
     // Device bytes of the mesh arrays (256-byte granules), without CG work.
     size_t device_bytes() const;
@@ -140,10 +143,11 @@ struct MeshImage {
 // conn [n_elems][stride]; types as for build_plan (NULL: one type, stride nodes).
 // owner_plan: build the owner plan of the HEX08 matrix assembly (the
 // serving runtime, which assembles each mesh once, skips it: its host time
-// exceeds the assembly time it saves there).
+// exceeds the assembly time it saves there).  vector_passes: build the
+// gather map of the element-vector passes (the serving runtime runs none).
 int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double *coords, int64_t n_elems,
                  const int32_t *conn, int64_t n_dirichlet, const int32_t *dirichlet_nodes, bool renumber,
-                 MeshImage &img, std::string &err, bool owner_plan = true);
+                 MeshImage &img, std::string &err, bool owner_plan = true, bool vector_passes = true);
 // Allocates (from m->arena or hipMalloc) and queues the copies of img on
 // `stream`.  img must stay alive until the copies have completed.
 fe_status mesh_commit(fe_mesh_s *m, MeshImage &img, hipStream_t stream);

@@ -33,6 +33,9 @@ struct DevMesh {
     int64_t N = 0, E = 0, nnz = 0, nblk = 0;
     int n_colors = 0, max_T = 0, max_L = 0, max_row = 0, max_phase = 0;
     std::vector<AsmLaunch> launches;    // host: launch order (colour-major, then type)
+    std::vector<AsmLaunch> vec_launches;   // host: element-vector passes, one launch per type over vec_blk
+    int64_t vec_T = 0;                  // touched rows of all blocks (0: no gather map)
+    int32_t *vec_blk = nullptr, *node_slot_ptr = nullptr, *node_slot = nullptr;
 
     double *X = nullptr;                // [3][N]
     int32_t *rowptr = nullptr, *colidx = nullptr, *diagpos = nullptr;
@@ -159,6 +162,7 @@ struct AsmArgs {
     double *values;          // operator's value array [nnz]
     double *rhs;             // first rhs row [N] (momentum: 3 rows of N; element-vector passes: their rows)
     AsmStatus *status;       // status word, followed by the per-block / per-group scratch
+    double *vec_work = nullptr;   // element-vector passes: block sums [4][vec_T] (null: colour by colour)
     AsmStatus *status_out = nullptr;   // where the reduced word goes instead of *status (null: *status)
 };
 

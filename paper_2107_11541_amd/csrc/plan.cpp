@@ -104,7 +104,7 @@ void Plan::clear()
     max_row = n_colors = max_T = max_L = max_phase = 0;
     for (auto *v : {&node_perm, &node_iperm, &elem_perm, &conn, &rowptr, &colidx, &diagpos, &blk_elem_ptr,
                     &blk_node_ptr, &blk_nodes, &blk_img, &blk_rdesc, &blk_rowstart, &blk_color, &color_ptr,
-                    &color_blk})
+                    &color_blk, &node_slot_ptr, &node_slot})
         v->clear();
     for (auto *v : {&etype, &blk_nphase, &elem_off, &blk_nen, &elem_phase}) v->clear();
     X.clear();
@@ -666,11 +666,18 @@ static int build_plan_impl(int S, const uint8_t *types, int64_t N, const double 
         for (int64_t i = 0; i < N; ++i) np[i + 1] += np[i];
         std::vector<int32_t> &nblks = t_scratch.nblks;
         nblks.resize(np[N]);
+        if (P.want_gather) {
+            P.node_slot_ptr.assign(np.begin(), np.end());
+            P.node_slot.resize(np[N]);
+        }
         {
             std::vector<int64_t> fill(np.begin(), np.end() - 1);
             for (int64_t b = 0; b < nblk; ++b)
-                for (int32_t k = P.blk_node_ptr[b]; k < P.blk_node_ptr[b + 1]; ++k)
-                    nblks[fill[P.blk_nodes[k]]++] = (int32_t)b;
+                for (int32_t k = P.blk_node_ptr[b]; k < P.blk_node_ptr[b + 1]; ++k) {
+                    const int64_t q = fill[P.blk_nodes[k]]++;
+                    nblks[q] = (int32_t)b;
+                    if (P.want_gather) P.node_slot[q] = k;
+                }
         }
         P.blk_color.assign(nblk, -1);
         std::vector<int64_t> seen;   // colour -> last block that saw it

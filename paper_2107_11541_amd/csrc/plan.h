@@ -81,6 +81,10 @@ struct Plan {
     std::vector<int32_t> color_ptr;      // [ncolor+1]
     std::vector<int32_t> color_blk;      // blocks ordered by colour, then type (type_rank)
     std::vector<AsmSeg> segs;            // launch order: colour-major, one per type present
+    // the element-vector passes' gather (want_gather): per node its places in
+    // blk_nodes, ascending, at node_slot[node_slot_ptr[i] ..]
+    bool want_gather = false;
+    std::vector<int32_t> node_slot_ptr, node_slot;
     int n_colors = 0, max_T = 0, max_L = 0, max_phase = 0;
 
     int64_t n_blocks() const { return (int64_t)blk_elem_ptr.size() - 1; }
