@@ -58,8 +58,9 @@ typedef enum { FE_OP_MOMENTUM = 0, FE_OP_SCALAR = 1, FE_OP_POISSON = 2 } fe_oper
 /* fe_mesh_upload flags */
 #define FE_UPLOAD_RENUMBER 1u   /* reorder elements along a Morton curve, nodes by first touch */
 #define FE_UPLOAD_COLOURED 2u   /* single-type meshes: assemble the matrix operators with the coloured
-                                 * element blocks (the serving runtime's form, and always that of hybrid
-                                 * meshes) instead of the owner groups; the two agree to rounding order */
+                                 * element blocks (the serving runtime's form) instead of the owner groups
+                                 * (HEX08) or the blocks with a gather (the other types; always that of
+                                 * hybrid meshes); they agree to rounding order */
 #define FE_UPLOAD_GENERAL_SPMV 4u   /* fe_cg_solve runs the general SpMV on this mesh and never builds
                                      * the symmetric one's map: for a mesh solved once or a few times,
                                      * where building the map on the host (~3 ns per nonzero on 8
@@ -409,9 +410,9 @@ fe_status fe_fractional_step(fe_mesh mesh, double dt, const double *rho, const d
  * A request's numbers do not depend on the other requests in flight: its
  * work-group counts and summation orders are the ones of a request served
  * alone (and of fe_cg_solve_noalloc on the same system, the mesh uploaded
- * with FE_UPLOAD_COLOURED: served meshes are assembled by coloured element
- * blocks, since the owner plan's host time exceeds the assembly time it saves
- * for a mesh assembled once; the batched PCG runs the general SpMV).
+ * with FE_UPLOAD_COLOURED: served single-type meshes are assembled by coloured
+ * element blocks, since the owner plan's host time exceeds the assembly time it
+ * saves for a mesh assembled once; the batched PCG runs the general SpMV).
  *
  * Host arrays of a request are borrowed from fe_serve_submit until the
  * request is reported done; they must stay valid and unchanged until then.
@@ -520,10 +521,10 @@ fe_status fe_plan_export_types(fe_plan plan, uint8_t *elem_types, uint8_t *block
 fe_status fe_plan_export_color_blocks(fe_plan plan, int32_t *color_blocks);
 /*
  * Owner plan of the matrix assembly of a single-type mesh (Section 4.2's
- * element loop regrouped by the CSR rows it writes; fe_assemble runs it for
- * MOMENTUM, SCALAR and POISSON on single-type meshes uploaded without
- * FE_UPLOAD_COLOURED, and the coloured element blocks otherwise and for
- * hybrid meshes).  Rows, in mesh numbering, are
+ * element loop regrouped by the CSR rows it writes; fe_assemble runs it, its
+ * tasks dealt to the wavefronts of each group, for MOMENTUM, SCALAR and
+ * POISSON on HEX08 meshes uploaded without FE_UPLOAD_COLOURED).  Rows, in
+ * mesh numbering, are
  * cut into groups of consecutive rows; a work-group owns one group and
  * computes every element contribution to its rows.  A task is one lane's
  * share: an element's rows that the group owns -- for HEX08 at most 4, with

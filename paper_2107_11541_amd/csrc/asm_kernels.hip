@@ -6,21 +6,24 @@
 // CSR.  Section 4.3 packs elements so that a SIMD unit processes several at
 // once.  gfx950 form:
 //
-//   * one work-group = one block of <= 64 spatially compact elements of one
-//     type; a TET04, PYR05 or PEN06 element is one lane, a HEX08 element two
-//     lanes in two waves (4 matrix rows each), which keeps a wave under 256
-//     registers so that two blocks share each SIMD and hide each other's
-//     memory latency;
-//   * the block's nodal fields are staged in LDS (structure of arrays, so that
-//     lanes reading different nodes hit different banks);
-//   * the CSR rows the block touches live in an LDS image, initialised from
-//     HBM (or zero for the first block to touch a row), accumulated with
-//     conflict-free ds_add_f64 in a fixed (phase, a, b) order, and written
-//     back once -- one coalesced read-modify-write per touched row instead of
-//     one per element entry;
-//   * blocks of one colour share no node, so a launch per (colour, element
-//     type) needs no atomics in HBM; the launch order fixes the summation
-//     order, so the result is bitwise reproducible.
+//   * matrix operators of a HEX08 mesh: owner groups (k_own), each CSR row
+//     computed whole by one work-group and written once;
+//   * matrix operators of the other meshes and the element-vector passes:
+//     blocks of <= 64 spatially compact elements of one type, a block's row
+//     images (or nodal sums) to its own place in a work array, and a gather
+//     that adds them row by row (k_part, k_vec);
+//   * without the work array, or asked for by the upload (as the serving
+//     runtime does), the coloured form (k_assemble): the CSR rows a block
+//     touches live in an LDS image, initialised from HBM (or zero for the
+//     first block to touch a row) and written back once; blocks of one colour
+//     share no node, so a launch per (colour, element type) needs no atomics
+//     in HBM.
+// In all three the nodal fields are staged in LDS (structure of arrays, so that
+// lanes reading different nodes hit different banks), a TET04, PYR05 or PEN06
+// element is one lane, a HEX08 block two waves of 4 matrix rows each (under
+// 256 registers a wave, so that two share each SIMD), and the sums in LDS run
+// conflict-free in an order that the plan fixes: results are bitwise
+// reproducible.
 //
 // Precision: FP64, or (mixed) FP32 Gauss-point products and elemental sums
 // with the Jacobian, det J, J^-1 and the CSR accumulation in FP64.
@@ -733,307 +736,6 @@ __global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_residual(KArgs k)
     assemble_block<EL, OP_RES, double, FORM>(k, blockIdx.x);
 }
 
-// ---- owner assembly of the matrix operators ---------------------------------
-// One work-group owns a group of consecutive CSR rows and computes every
-// element contribution to them, so each row is written once and never read
-// back, in a single launch (no colours).  Steps:
-//   1. stage the group's touched nodes' fields in LDS (owned rows first);
-//      zero the owned rows' image and right-hand sides;
-//   2. one task per lane: the Gauss loop of rows [0, RA) of its element,
-//      presented in the task's node order (a HEX08 element rotated so that
-//      the rows the group owns lie on its first face);
-//   3. phase by phase (a barrier between phases), add the owned rows of the
-//      tasks of that phase into LDS: the tasks of one phase hold distinct
-//      owned rows, so no two lanes add to one address and the order of the
-//      sums is fixed by the plan.  Wave-private form (PRIV, element types
-//      whose nodes lie in many elements): each wave adds into its own copy
-//      of the rows, phases within the wave, no barriers; the copies are
-//      then summed in wave order;
-//   4. write the rows (contiguous in CSR) and right-hand sides once.
-struct OArgs {
-    const double *X;
-    const int32_t *rowptr;
-    const int4 *groups;
-    const int32_t *node_ptr, *nodes, *elem;
-    const uint8_t *nphase, *off, *phase;
-    const uint16_t *ln;
-    int ln_stride, off_stride;
-    int64_t N;
-    const double *u, *rho, *mu, *Y;
-    double dt, Dk;
-    double *values, *rhs;
-    double *g_mindet;
-    long long *g_bad;
-};
-
-template <class EL> struct OwnRows { static constexpr int RA = EL::NEN == 8 ? 4 : EL::NEN; };
-
-// Work-groups are dispatched round-robin over MI355X's 8 XCDs (work-group b
-// on XCD b % 8), each with its own L2.  xcd_item maps work-group b of a
-// G-group launch to item i so that every XCD takes one contiguous range of
-// items (a bijection of [0, G)).  Consecutive owner groups cover neighbouring
-// rows and share halo nodes, so their cache lines of the nodal fields are then
-// fetched once into that XCD's L2 instead of once into each of several.
-constexpr int kAsmXcds = 8;
-__device__ inline int xcd_item(int b, int G)
-{
-    const int q = G / kAsmXcds, rem = G % kAsmXcds, x = b % kAsmXcds, slot = b / kAsmXcds;
-    return x * q + (x < rem ? x : rem) + slot;
-}
-
-template <class EL, int OP, class Q, bool PRIV>
-__global__ void __launch_bounds__(kOwnTasks, 2) k_own(OArgs k)
-{
-    constexpr int NEN = EL::NEN, RA = OwnRows<EL>::RA;
-    constexpr int NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
-    extern __shared__ double lds[];
-    const int gi = xcd_item(blockIdx.x, gridDim.x);   // this work-group's group
-    const int4 gd = k.groups[gi];   // first task, tasks, first row, rows
-    const int tid = threadIdx.x;
-    const int r0 = gd.z, nr = gd.w;
-    const int n0 = k.node_ptr[gi], T = k.node_ptr[gi + 1] - n0;
-    const int64_t v0 = k.rowptr[r0];
-    const int L = (int)(k.rowptr[r0 + nr] - v0);
-    const int64_t N = k.N;
-    constexpr int NC = PRIV ? kOwnTasks / 64 : 1;   // copies of the rows
-    // Fields of the touched nodes: x, y, z in FP64 (the geometry is FP64 in
-    // both modes), the others in the quadrature's precision (the mixed mode
-    // interpolates them in FP32, which halves their LDS traffic).
-    using FT = Q;
-    double *nd = lds;                   // [3][T] coordinates
-    FT *nf = (FT *)(nd + 3 * T);        // [NF - 3][T] u_x, u_y, u_z, rho, mu / Y
-    double *img0 = nd + 3 * T + ((NF - 3) * T * (int)sizeof(FT) + 7) / 8;   // [NC][L] the owned rows
-    double *rimg0 = img0 + NC * L;  // [NC][NRHS][nr] their right-hand sides
-    double *img = img0 + (PRIV ? (tid >> 6) * L : 0);                 // this wave's copy
-    double *rimg = rimg0 + (PRIV ? (tid >> 6) * NRHS * nr : 0);
-
-    // task data first: its loads overlap the staging below
-    const bool live = tid < gd.y;
-    const int64_t t = gd.x + (live ? tid : 0);
-    int ln[NEN];
-    {
-        const uint16_t *lp = k.ln + t * k.ln_stride;
-#pragma unroll
-        for (int a = 0; a < NEN; ++a) ln[a] = lp[a];
-    }
-    constexpr int kOffWords = (RA * NEN + 3) / 4;
-    uint32_t offw[kOffWords];
-    {
-        const uint32_t *op = (const uint32_t *)(k.off + t * k.off_stride);
-#pragma unroll
-        for (int q = 0; q < kOffWords; ++q) offw[q] = op[q];
-    }
-    const int ph = live ? (int)k.phase[t] : -1;
-    const int64_t elem = k.elem[t];
-
-    // 1. stage
-    for (int q = tid; q < T; q += kOwnTasks) {
-        const int g = k.nodes[n0 + q];
-        double f[NF];
-        f[0] = k.X[g];
-        f[1] = k.X[N + g];
-        f[2] = k.X[2 * N + g];
-        f[3] = k.u[g];
-        f[4] = k.u[N + g];
-        f[5] = k.u[2 * N + g];
-        f[6] = k.rho[g];
-        if constexpr (NF > 7) f[7] = OP == OP_MOM ? k.mu[g] : k.Y[g];
-#pragma unroll
-        for (int c = 0; c < 3; ++c) nd[c * T + q] = f[c];
-#pragma unroll
-        for (int c = 3; c < NF; ++c) nf[(c - 3) * T + q] = FT(f[c]);
-    }
-    for (int q = tid; q < NC * L; q += kOwnTasks) img0[q] = 0.0;
-    for (int q = tid; q < NC * NRHS * nr; q += kOwnTasks) rimg0[q] = 0.0;
-    __syncthreads();
-
-    // 2. this lane's rows
-    Q A[RA][NEN];
-    Q B[NRHS][RA];
-#pragma unroll
-    for (int r = 0; r < RA; ++r) {
-#pragma unroll
-        for (int b = 0; b < NEN; ++b) A[r][b] = Q(0);
-#pragma unroll
-        for (int q = 0; q < NRHS; ++q) B[q][r] = Q(0);
-    }
-    double mindet = __builtin_huge_val();
-    if (live) {
-        Geo<EL> GE;
-        load_geo<EL>(nd, T, ln, GE);
-        Rows<EL> rows;
-#pragma unroll
-        for (int a = 0; a < NEN; ++a) rows.v[a] = ln[a];
-        gauss_loop<EL, OP, Q, RA, 0, FT>(GE, nd, nf, T, rows, A, B, mindet, 1.0 / k.dt, k.Dk, 0);
-    }
-    int base[RA];
-#pragma unroll
-    for (int r = 0; r < RA; ++r) base[r] = ln[r] < nr ? (int)(k.rowptr[r0 + ln[r]] - v0) : -1;
-
-    // 3. phases
-    const int nph = k.nphase[gi];
-    for (int p = 0; p < nph; ++p) {
-        if (ph == p) {
-#pragma unroll
-            for (int r = 0; r < RA; ++r) {
-                if (base[r] < 0) continue;   // a row another group owns
-#pragma unroll
-                for (int b = 0; b < NEN; ++b) {
-                    const int idx = r * NEN + b;
-                    const int o = (offw[idx >> 2] >> (8 * (idx & 3))) & 0xff;
-                    lds_add(&img[base[r] + o], (double)A[r][b]);
-                }
-#pragma unroll
-                for (int q = 0; q < NRHS; ++q) lds_add(&rimg[q * nr + ln[r]], (double)B[q][r]);
-            }
-        }
-        if (!PRIV) __syncthreads();
-    }
-    if (PRIV) __syncthreads();
-
-    // 4. write the owned rows and right-hand sides once (the wave copies
-    //    summed in wave order)
-    for (int q = tid; q < L; q += kOwnTasks) {
-        double v = img0[q];
-#pragma unroll
-        for (int c = 1; c < NC; ++c) v += img0[c * L + q];
-        k.values[v0 + q] = v;
-    }
-    for (int q = tid; q < NRHS * nr; q += kOwnTasks) {
-        const int c = q / nr, i = q - c * nr;
-        double v = rimg0[q];
-#pragma unroll
-        for (int w = 1; w < NC; ++w) v += rimg0[w * NRHS * nr + q];
-        k.rhs[c * N + r0 + i] = v;
-    }
-    // status: the group's smallest det J and first element with det J <= 0
-    __shared__ double smd[kOwnTasks / 64];
-    __shared__ long long sbad[kOwnTasks / 64];
-    double md = live ? mindet : __builtin_huge_val();
-    long long bad = (live && !(mindet > 0.0)) ? (long long)elem : (long long)0x7fffffffffffffffLL;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        md = fmin(md, __shfl_xor(md, o));
-        const long long ob = __shfl_xor(bad, o);
-        bad = ob < bad ? ob : bad;
-    }
-    if ((tid & 63) == 0) {
-        smd[tid >> 6] = md;
-        sbad[tid >> 6] = bad;
-    }
-    __syncthreads();
-    if (tid == 0) {
-#pragma unroll
-        for (int w = 1; w < kOwnTasks / 64; ++w) {
-            md = fmin(md, smd[w]);
-            bad = sbad[w] < bad ? sbad[w] : bad;
-        }
-        k.g_mindet[gi] = md;
-        k.g_bad[gi] = bad == 0x7fffffffffffffffLL ? -1 : bad;
-    }
-}
-
-// HEX08 accumulates into one copy of the group's rows, the other types
-// wave-privately (the planner's choice, OwnerPlan::wave_private).
-template <class EL, int OP>
-void launch_own_op(const OArgs &k, int64_t G, size_t lds, bool mixed, hipStream_t s)
-{
-    constexpr bool PRIV = EL::NEN != 8;
-    if (mixed) hipLaunchKernelGGL((k_own<EL, OP, float, PRIV>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
-    else hipLaunchKernelGGL((k_own<EL, OP, double, PRIV>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
-}
-
-template <class EL>
-void launch_own(const OArgs &k, int op, int64_t G, size_t lds, bool mixed, hipStream_t s)
-{
-    switch (op) {
-    case OP_MOM: launch_own_op<EL, OP_MOM>(k, G, lds, mixed, s); break;
-    case OP_SCA: launch_own_op<EL, OP_SCA>(k, G, lds, mixed, s); break;
-    default: launch_own_op<EL, OP_POI>(k, G, lds, mixed, s); break;
-    }
-}
-
-// Reduce the per-block status into (min det, first bad mesh element): one
-// group of 1024 threads, four independent loads in flight per thread.
-constexpr int kStatusThreads = 1024;
-__global__ void __launch_bounds__(kStatusThreads) k_asm_status(const double *mindet, const long long *bad, int64_t n,
-                                                               AsmStatus *out)
-{
-    __shared__ double sd[kStatusThreads];
-    __shared__ long long sb[kStatusThreads];
-    double md = __builtin_huge_val();
-    long long b = 0x7fffffffffffffffLL;
-    const int64_t t = threadIdx.x;
-    for (int64_t i = t; i < n; i += 4 * kStatusThreads) {
-        double m4[4];
-        long long b4[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int64_t ii = i + u * kStatusThreads;
-            m4[u] = ii < n ? mindet[ii] : __builtin_huge_val();
-            b4[u] = ii < n ? bad[ii] : -1;
-        }
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            md = fmin(md, m4[u]);
-            if (b4[u] >= 0 && b4[u] < b) b = b4[u];
-        }
-    }
-    sd[t] = md;
-    sb[t] = b;
-    __syncthreads();
-    for (int s = kStatusThreads / 2; s > 0; s >>= 1) {
-        if (t < s) {
-            sd[t] = fmin(sd[t], sd[t + s]);
-            if (sb[t + s] < sb[t]) sb[t] = sb[t + s];
-        }
-        __syncthreads();
-    }
-    if (t == 0) {
-        double d = sd[0];
-        unsigned long long u;
-        __builtin_memcpy(&u, &d, 8);
-        out->min_det_key = u;
-        out->first_bad = sb[0] == 0x7fffffffffffffffLL ? -1 : sb[0];
-    }
-}
-
-template <class EL, int OP, class Q>
-void launch_one(const AsmLaunch &L, KArgs k, hipStream_t s)
-{
-    k.blk_offset = L.first;
-    hipLaunchKernelGGL((k_assemble<EL, OP, Q>), dim3(L.count), dim3(64 * Split<EL>::W), L.lds[OP], s, k);
-}
-
-template <class EL, int FORM>
-void launch_residual(const AsmLaunch &L, KArgs k, hipStream_t s)
-{
-    k.blk_offset = L.first;
-    hipLaunchKernelGGL((k_residual<EL, FORM>), dim3(L.count), dim3(64 * Split<EL>::W), L.lds[OP_RES], s, k);
-}
-
-template <class EL>
-void launch_type(const AsmLaunch &L, const KArgs &k, int op, bool mixed, hipStream_t s)
-{
-    switch (op) {
-    case OP_MOM: mixed ? launch_one<EL, OP_MOM, float>(L, k, s) : launch_one<EL, OP_MOM, double>(L, k, s); break;
-    case OP_SCA: mixed ? launch_one<EL, OP_SCA, float>(L, k, s) : launch_one<EL, OP_SCA, double>(L, k, s); break;
-    case OP_POI: mixed ? launch_one<EL, OP_POI, float>(L, k, s) : launch_one<EL, OP_POI, double>(L, k, s); break;
-    // element-vector passes are FP64 only
-    case OP_RES:
-        switch (k.form) {
-        case 0: launch_residual<EL, 0>(L, k, s); break;
-        case 1: launch_residual<EL, 1>(L, k, s); break;
-        case 2: launch_residual<EL, 2>(L, k, s); break;
-        default: launch_residual<EL, 3>(L, k, s); break;
-        }
-        break;
-    case OP_GRD: launch_one<EL, OP_GRD, double>(L, k, s); break;
-    case OP_SRS: launch_one<EL, OP_SRS, double>(L, k, s); break;
-    default: launch_one<EL, OP_DIV, double>(L, k, s); break;
-    }
-}
-
 // ---- HEX08 by sums over one direction at a time ------------------------------
 // The trilinear basis and its 2x2x2 rule are products of the two-point rule of
 // a line, L0, L1 = (1 -+ t)/2 at t = -+1/sqrt3, so interpolating to the points
@@ -1110,6 +812,782 @@ __device__ __forceinline__ double hex_cofactors(const SlabGrad (&X)[3], int gx, 
     return c0[0] * C[0][0] + c0[1] * C[0][1] + c0[2] * C[0][2];
 }
 
+// Sums over a line's two points weighted with L_a L_b: s[0] both ends at the
+// first node, s[1] one at each, s[2] both at the second.
+__device__ __forceinline__ void line_pairs(double p0, double p1, double (&s)[3])
+{
+    constexpr double Q = 1.0 - kHexP;
+    s[0] = fma(kHexP * kHexP, p0, (Q * Q) * p1);
+    s[1] = (kHexP * Q) * (p0 + p1);
+    s[2] = fma(Q * Q, p0, (kHexP * kHexP) * p1);
+}
+
+// The matrix rows of the four nodes with iz = AZ of one HEX08 element, FP64
+// (the terms of gauss_point), and their right-hand sides.  Every term is a
+// coefficient at a Gauss point (the mass m, the convection c_l, the diffusion
+// D_jl on reference coordinates) times a product of line functions of row and
+// column, so a term is first added up over zeta with its weights for the two
+// column layers bz, then over the lines of xi and eta: ~1,900 operations per
+// four rows against ~3,000 for products formed at every point.  t1 .. t8 are
+// the terms by which of row and column carries a derivative in xi or eta:
+// t1 none, t2 column xi, t3 row xi, t4 column eta, t5 row eta, t6 both xi,
+// t7 both eta, t8 row xi and column eta (and, D being symmetric, row eta and
+// column xi).  One slab of points after the other in a rolled loop.
+template <int OP, int AZ>
+__device__ __forceinline__ void hex_matrix(const double *nd, const double *nf, int T, const int (&ln0)[8],
+                                           double (&A)[4][8], double (&B)[OpTraits<OP>::NRHS][4], double &mindet,
+                                           double inv_dt, double Dk)
+{
+    constexpr bool POI = OP == OP_POI;
+    constexpr int NS = POI ? 0 : OpTraits<OP>::NRHS;   // right-hand sides from a source
+    int ln[8];
+#pragma unroll
+    for (int a = 0; a < 8; ++a) ln[a] = ln0[a];
+    double t1[2][2][2] = {}, t2[2][2][2] = {}, t3[2][2] = {}, t4[2][2][2] = {}, t5[2][2] = {}, t6[2][2] = {},
+           t7[2][2] = {}, t8[2][2][2] = {};
+    double rs[NS ? NS : 1][2][2] = {}, rx[2] = {}, ry[2] = {}, rz[2][2] = {};
+#pragma unroll 1
+    for (int gz = 0; gz < 2; ++gz) {
+        const double z = gz ? Hex::kG : -Hex::kG;
+#pragma unroll
+        for (int a = 0; a < 8; ++a) asm volatile("" : "+v"(ln[a]));   // fields are read again, not kept
+        // weights of the rows' layer and of the two column layers
+        const double Lb[2] = {0.5 * (1.0 - z), 0.5 * (1.0 + z)};
+        const double La = Lb[AZ], da = AZ ? 0.5 : -0.5;
+        SlabGrad X[3];
+        double v[2][2], h[2][2], up[3][2][2], rp[2][2], mp[2][2];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            hex_slab(nd + i * T, ln, z, v, h);
+            hex_grad(v, h, X[i]);
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            hex_slab(nf + i * T, ln, z, v, h);
+            hex_points(v, up[i]);
+        }
+        hex_slab(nf + 3 * T, ln, z, v, h);
+        hex_points(v, rp);
+        if constexpr (!POI) {
+            hex_slab(nf + 4 * T, ln, z, v, h);
+            hex_points(v, mp);   // mu or Y
+        }
+#pragma unroll
+        for (int gx = 0; gx < 2; ++gx)
+#pragma unroll
+            for (int gy = 0; gy < 2; ++gy) {
+                double C[3][3];
+                const double det = hex_cofactors(X, gx, gy, C);
+                mindet = fmin(mindet, det);
+                const double r = rp[gx][gy];
+                const double k = (POI ? 1.0 : OP == OP_MOM ? mp[gx][gy] : r * Dk) / det;
+                double c[3];   // rho det J times the velocity's reference components
+#pragma unroll
+                for (int j = 0; j < 3; ++j)
+                    c[j] = r * (C[j][0] * up[0][gx][gy] + C[j][1] * up[1][gx][gy] + C[j][2] * up[2][gx][gy]);
+                auto D = [&](int j, int l) { return k * (C[j][0] * C[l][0] + C[j][1] * C[l][1] + C[j][2] * C[l][2]); };
+                const double dzz = da * D(2, 2), dxz = D(0, 2), dyz = D(1, 2), dxy = D(0, 1);
+                const double dxx = La * D(0, 0), dyy = La * D(1, 1);
+                const double m = POI ? 0.0 : La * (r * det * inv_dt);
+#pragma unroll
+                for (int bz = 0; bz < 2; ++bz) {
+                    const double db = bz ? 0.5 : -0.5;
+                    if constexpr (POI) {
+                        if (bz == 0) t1[0][gx][gy] += dzz;
+                        t2[bz][gx][gy] += (da * Lb[bz]) * dxz;
+                        t4[bz][gx][gy] += (da * Lb[bz]) * dyz;
+                    } else {
+                        t1[bz][gx][gy] += Lb[bz] * m + db * (La * c[2] + dzz);
+                        t2[bz][gx][gy] += Lb[bz] * (La * c[0] + da * dxz);
+                        t4[bz][gx][gy] += Lb[bz] * (La * c[1] + da * dyz);
+                    }
+                    t6[bz][gy] += Lb[bz] * dxx;
+                    t7[bz][gx] += Lb[bz] * dyy;
+                    t8[bz][gx][gy] += (La * Lb[bz]) * dxy;
+                }
+                t3[gx][gy] += La * dxz;
+                t5[gx][gy] += La * dyz;
+                if constexpr (POI) {
+                    rx[gy] += La * c[0];
+                    ry[gx] += La * c[1];
+                    rz[gx][gy] += c[2];
+                } else {
+#pragma unroll
+                    for (int q = 0; q < NS; ++q)
+                        rs[q][gx][gy] += m * (OP == OP_MOM ? up[q][gx][gy] : mp[gx][gy]);
+                }
+            }
+    }
+    // over xi and eta, one column layer at a time.  sx, sy: -+1/2, the
+    // derivatives of the line functions.
+#pragma unroll
+    for (int bz = 0; bz < 2; ++bz) {
+        const double db = bz ? 0.5 : -0.5;
+        double a1[3][3], a2[2][3], a3[2][3], a4[3][2], a5[3][2], a6[3], a7[3], a8[2][2];
+        {
+            double w[3][2];
+#pragma unroll
+            for (int gy = 0; gy < 2; ++gy) {
+                double q[3];
+                if constexpr (POI) line_pairs(db * t1[0][0][gy], db * t1[0][1][gy], q);
+                else line_pairs(t1[bz][0][gy], t1[bz][1][gy], q);
+#pragma unroll
+                for (int x = 0; x < 3; ++x) w[x][gy] = q[x];
+            }
+#pragma unroll
+            for (int x = 0; x < 3; ++x) line_pairs(w[x][0], w[x][1], a1[x]);
+        }
+        {
+            double w[2][2], u[2][2];
+#pragma unroll
+            for (int gy = 0; gy < 2; ++gy) {
+                line_nodes(t2[bz][0][gy], t2[bz][1][gy], w[0][gy], w[1][gy]);
+                line_nodes(db * t3[0][gy], db * t3[1][gy], u[0][gy], u[1][gy]);
+            }
+#pragma unroll
+            for (int x = 0; x < 2; ++x) {
+                line_pairs(w[x][0], w[x][1], a2[x]);
+                line_pairs(u[x][0], u[x][1], a3[x]);
+            }
+        }
+        {
+            double w[2][2], u[2][2];
+#pragma unroll
+            for (int gx = 0; gx < 2; ++gx) {
+                line_nodes(t4[bz][gx][0], t4[bz][gx][1], w[gx][0], w[gx][1]);
+                line_nodes(db * t5[gx][0], db * t5[gx][1], u[gx][0], u[gx][1]);
+            }
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                double q[3];
+                line_pairs(w[0][y], w[1][y], q);
+#pragma unroll
+                for (int x = 0; x < 3; ++x) a4[x][y] = q[x];
+                line_pairs(u[0][y], u[1][y], q);
+#pragma unroll
+                for (int x = 0; x < 3; ++x) a5[x][y] = q[x];
+            }
+        }
+        line_pairs(t6[bz][0], t6[bz][1], a6);
+        line_pairs(t7[bz][0], t7[bz][1], a7);
+        {
+            double w[2][2];
+#pragma unroll
+            for (int gx = 0; gx < 2; ++gx) line_nodes(t8[bz][gx][0], t8[bz][gx][1], w[gx][0], w[gx][1]);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) line_nodes(w[0][y], w[1][y], a8[0][y], a8[1][y]);
+        }
+#pragma unroll
+        for (int ax = 0; ax < 2; ++ax)
+#pragma unroll
+            for (int ay = 0; ay < 2; ++ay)
+#pragma unroll
+                for (int bx = 0; bx < 2; ++bx)
+#pragma unroll
+                    for (int by = 0; by < 2; ++by) {
+                        const double sxa = ax ? 0.5 : -0.5, sxb = bx ? 0.5 : -0.5, sya = ay ? 0.5 : -0.5,
+                                     syb = by ? 0.5 : -0.5;
+                        const int x = ax + bx, y = ay + by;
+                        double e = a1[x][y];
+                        e += sxb * a2[ax][y];
+                        e += sxa * a3[bx][y];
+                        e += syb * a4[x][ay];
+                        e += sya * a5[x][by];
+                        e += (sxa * sxb) * a6[y];
+                        e += (sya * syb) * a7[x];
+                        e += (sxa * syb) * a8[bx][ay];
+                        e += (sya * sxb) * a8[ax][by];
+                        A[hex_node(ax, ay, 0)][hex_node(bx, by, bz)] = e;
+                    }
+    }
+    if constexpr (POI) {
+        const double da = (AZ ? 0.5 : -0.5) * inv_dt;
+        double nx[2], ny[2], w[2][2], n[2][2];
+        line_nodes(rx[0], rx[1], nx[0], nx[1]);
+        line_nodes(ry[0], ry[1], ny[0], ny[1]);
+#pragma unroll
+        for (int gx = 0; gx < 2; ++gx) line_nodes(rz[gx][0], rz[gx][1], w[gx][0], w[gx][1]);
+#pragma unroll
+        for (int y = 0; y < 2; ++y) line_nodes(w[0][y], w[1][y], n[0][y], n[1][y]);
+#pragma unroll
+        for (int ax = 0; ax < 2; ++ax)
+#pragma unroll
+            for (int ay = 0; ay < 2; ++ay)
+                B[0][hex_node(ax, ay, 0)] =
+                    da * n[ax][ay] + inv_dt * ((ax ? 0.5 : -0.5) * nx[ay] + (ay ? 0.5 : -0.5) * ny[ax]);
+    } else {
+#pragma unroll
+        for (int q = 0; q < NS; ++q) {
+            double w[2][2];
+#pragma unroll
+            for (int gx = 0; gx < 2; ++gx) line_nodes(rs[q][gx][0], rs[q][gx][1], w[gx][0], w[gx][1]);
+#pragma unroll
+            for (int y = 0; y < 2; ++y) {
+                double n0, n1;
+                line_nodes(w[0][y], w[1][y], n0, n1);
+                B[q][hex_node(0, y, 0)] = n0;
+                B[q][hex_node(1, y, 0)] = n1;
+            }
+        }
+    }
+}
+
+// ---- owner assembly of the matrix operators ---------------------------------
+// HEX08.  One work-group owns a group of consecutive CSR rows and computes every
+// element contribution to them, so each row is written once and never read
+// back, in a single launch (no colours).  Steps:
+//   1. stage the group's touched nodes' fields in LDS (owned rows first);
+//      zero the owned rows' image and right-hand sides;
+//   2. one task per lane: rows 0-3 of its element, rotated so that the rows
+//      the group owns lie on its first face (FP64: hex_matrix; mixed: the
+//      FP32 Gauss loop);
+//   3. wavefront after wavefront (a barrier between them), add the owned rows
+//      into LDS, local row after local row: the plan deals the tasks so that
+//      one instruction's lanes hold distinct rows, mostly in one step, and the
+//      order of the sums is fixed.  (Phases of tasks without a common row
+//      over the whole group, ten of them with a barrier each, took 5.2 of a
+//      group's 22 us on 101^3 HEX08.)
+//   4. write the rows (contiguous in CSR) and right-hand sides once.
+// Bound by FP64 arithmetic and the staging before it (10 and 5 of a group's 22
+// us, two groups to a CU).  Whole calls, Gauss point after Gauss point with
+// phases -> direction by direction and wavefront after wavefront: momentum 10^3
+// 45 -> 33 us, 72^3 251 -> 164, 128^3 1250 -> 840; Poisson 128^3 1020 -> 694;
+// mixed (Gauss points kept, so that its FP32 results stay the same) momentum
+// 128^3 884 -> 830.
+struct OArgs {
+    const double *X;
+    const int32_t *rowptr;
+    const int4 *groups;
+    const int32_t *node_ptr, *nodes, *elem;
+    const uint8_t *nphase, *off, *phase;
+    const uint16_t *ln;
+    int ln_stride, off_stride;
+    int64_t N;
+    const double *u, *rho, *mu, *Y;
+    double dt, Dk;
+    double *values, *rhs;
+    double *g_mindet;
+    long long *g_bad;
+};
+
+// Work-groups are dispatched round-robin over MI355X's 8 XCDs (work-group b
+// on XCD b % 8), each with its own L2.  xcd_item maps work-group b of a
+// G-group launch to item i so that every XCD takes one contiguous range of
+// items (a bijection of [0, G)).  Consecutive owner groups cover neighbouring
+// rows and share halo nodes, so their cache lines of the nodal fields are then
+// fetched once into that XCD's L2 instead of once into each of several.
+constexpr int kAsmXcds = 8;
+__device__ inline int xcd_item(int b, int G)
+{
+    const int q = G / kAsmXcds, rem = G % kAsmXcds, x = b % kAsmXcds, slot = b / kAsmXcds;
+    return x * q + (x < rem ? x : rem) + slot;
+}
+
+template <int OP, class Q>
+__global__ void __launch_bounds__(kOwnTasks, 2) k_own(OArgs k)
+{
+    constexpr int NEN = 8, RA = 4;
+    constexpr int NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
+    extern __shared__ double lds[];
+    const int gi = xcd_item(blockIdx.x, gridDim.x);   // this work-group's group
+    const int4 gd = k.groups[gi];   // first task, tasks, first row, rows
+    const int tid = threadIdx.x;
+    const int r0 = gd.z, nr = gd.w;
+    const int n0 = k.node_ptr[gi], T = k.node_ptr[gi + 1] - n0;
+    const int64_t v0 = k.rowptr[r0];
+    const int L = (int)(k.rowptr[r0 + nr] - v0);
+    const int64_t N = k.N;
+    // Fields of the touched nodes: x, y, z in FP64 (the geometry is FP64 in
+    // both modes), the others in the quadrature's precision (the mixed mode
+    // interpolates them in FP32, which halves their LDS traffic).
+    using FT = Q;
+    double *nd = lds;                   // [3][T] coordinates
+    FT *nf = (FT *)(nd + 3 * T);        // [NF - 3][T] u_x, u_y, u_z, rho, mu / Y
+    double *img = nd + 3 * T + ((NF - 3) * T * (int)sizeof(FT) + 7) / 8;   // [L] the owned rows
+    double *rimg = img + L;             // [NRHS][nr] their right-hand sides
+
+    // task data first: its loads overlap the staging below
+    const bool live = tid < gd.y;
+    const int64_t t = gd.x + (live ? tid : 0);
+    int ln[NEN];
+    {
+        const uint16_t *lp = k.ln + t * k.ln_stride;
+#pragma unroll
+        for (int a = 0; a < NEN; ++a) ln[a] = lp[a];
+    }
+    constexpr int kOffWords = (RA * NEN + 3) / 4;
+    uint32_t offw[kOffWords];
+    {
+        const uint32_t *op = (const uint32_t *)(k.off + t * k.off_stride);
+#pragma unroll
+        for (int q = 0; q < kOffWords; ++q) offw[q] = op[q];
+    }
+    const int ph = live ? (int)k.phase[t] : -1;
+    const int64_t elem = k.elem[t];
+
+    // 1. stage
+    for (int q = tid; q < T; q += kOwnTasks) {
+        const int g = k.nodes[n0 + q];
+        double f[NF];
+        f[0] = k.X[g];
+        f[1] = k.X[N + g];
+        f[2] = k.X[2 * N + g];
+        f[3] = k.u[g];
+        f[4] = k.u[N + g];
+        f[5] = k.u[2 * N + g];
+        f[6] = k.rho[g];
+        if constexpr (NF > 7) f[7] = OP == OP_MOM ? k.mu[g] : k.Y[g];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nd[c * T + q] = f[c];
+#pragma unroll
+        for (int c = 3; c < NF; ++c) nf[(c - 3) * T + q] = FT(f[c]);
+    }
+    for (int q = tid; q < L; q += kOwnTasks) img[q] = 0.0;
+    for (int q = tid; q < NRHS * nr; q += kOwnTasks) rimg[q] = 0.0;
+    __syncthreads();
+
+    // 2. this lane's rows
+    Q A[RA][NEN];
+    Q B[NRHS][RA];
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) A[r][b] = Q(0);
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) B[q][r] = Q(0);
+    }
+    double mindet = __builtin_huge_val();
+    if constexpr (sizeof(Q) == 8) {
+        if (live) hex_matrix<OP, 0>(nd, nf, T, ln, A, B, mindet, 1.0 / k.dt, k.Dk);
+    } else if (live) {
+        Geo<Hex> GE;
+        load_geo<Hex>(nd, T, ln, GE);
+        Rows<Hex> rows;
+#pragma unroll
+        for (int a = 0; a < NEN; ++a) rows.v[a] = ln[a];
+        gauss_loop<Hex, OP, Q, RA, 0, FT>(GE, nd, nf, T, rows, A, B, mindet, 1.0 / k.dt, k.Dk, 0);
+    }
+    int base[RA];
+#pragma unroll
+    for (int r = 0; r < RA; ++r) base[r] = ln[r] < nr ? (int)(k.rowptr[r0 + ln[r]] - v0) : -1;
+
+    // 3. wavefront after wavefront
+    const int nph = k.nphase[gi];
+#pragma unroll 1
+    for (int w = 0; w < kOwnTasks / 64; ++w) {
+        if ((tid >> 6) == w) {
+            for (int p = 0; p < nph; ++p) {
+                if (ph != p) continue;
+#pragma unroll
+                for (int r = 0; r < RA; ++r) {
+                    if (base[r] < 0) continue;   // a row another group owns
+#pragma unroll
+                    for (int b = 0; b < NEN; ++b) {
+                        const int idx = r * NEN + b;
+                        const int o = (offw[idx >> 2] >> (8 * (idx & 3))) & 0xff;
+                        lds_add(&img[base[r] + o], (double)A[r][b]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NRHS; ++q) lds_add(&rimg[q * nr + ln[r]], (double)B[q][r]);
+                }
+            }
+        }
+        __syncthreads();
+    }
+
+    // 4. write the owned rows and right-hand sides once
+    for (int q = tid; q < L; q += kOwnTasks) k.values[v0 + q] = img[q];
+    for (int q = tid; q < NRHS * nr; q += kOwnTasks) {
+        const int c = q / nr, i = q - c * nr;
+        k.rhs[c * N + r0 + i] = rimg[q];
+    }
+    // status: the group's smallest det J and first element with det J <= 0
+    __shared__ double smd[kOwnTasks / 64];
+    __shared__ long long sbad[kOwnTasks / 64];
+    double md = live ? mindet : __builtin_huge_val();
+    long long bad = (live && !(mindet > 0.0)) ? (long long)elem : (long long)0x7fffffffffffffffLL;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        md = fmin(md, __shfl_xor(md, o));
+        const long long ob = __shfl_xor(bad, o);
+        bad = ob < bad ? ob : bad;
+    }
+    if ((tid & 63) == 0) {
+        smd[tid >> 6] = md;
+        sbad[tid >> 6] = bad;
+    }
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < kOwnTasks / 64; ++w) {
+            md = fmin(md, smd[w]);
+            bad = sbad[w] < bad ? sbad[w] : bad;
+        }
+        k.g_mindet[gi] = md;
+        k.g_bad[gi] = bad == 0x7fffffffffffffffLL ? -1 : bad;
+    }
+}
+
+template <int OP>
+void launch_own_op(const OArgs &k, int64_t G, size_t lds, bool mixed, hipStream_t s)
+{
+    if (mixed) hipLaunchKernelGGL((k_own<OP, float>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
+    else hipLaunchKernelGGL((k_own<OP, double>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
+}
+
+void launch_own(const OArgs &k, int op, int64_t G, size_t lds, bool mixed, hipStream_t s)
+{
+    switch (op) {
+    case OP_MOM: launch_own_op<OP_MOM>(k, G, lds, mixed, s); break;
+    case OP_SCA: launch_own_op<OP_SCA>(k, G, lds, mixed, s); break;
+    default: launch_own_op<OP_POI>(k, G, lds, mixed, s); break;
+    }
+}
+
+// ---- status word -----------------------------------------------------------------
+// Per-block status (smallest det J, first bad mesh element or -1) and where its
+// reduction goes: a device word, or the caller's pinned host word, which saves
+// the copy (4 us) a call would wait for.
+struct StatusArgs {
+    const double *mindet;
+    const long long *bad;
+    int64_t n;
+    AsmStatus *out;
+};
+
+// One group of NT threads reduces st, eight loads in flight per thread.
+template <int NT>
+__device__ __forceinline__ void reduce_status(const StatusArgs &st)
+{
+    constexpr long long kNone = 0x7fffffffffffffffLL;
+    __shared__ double sd[NT / 64];
+    __shared__ long long sb[NT / 64];
+    double md = __builtin_huge_val();
+    long long b = kNone;
+    const int t = threadIdx.x;
+    for (int64_t i = t; i < st.n; i += 4 * NT) {
+        double m4[4];
+        long long b4[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int64_t ii = i + u * NT < st.n ? i + u * NT : i;
+            m4[u] = st.mindet[ii];
+            b4[u] = st.bad[ii];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            md = fmin(md, m4[u]);
+            if (b4[u] >= 0 && b4[u] < b) b = b4[u];
+        }
+    }
+    const auto wave = [&] {
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            md = fmin(md, __shfl_xor(md, o));
+            const long long ob = __shfl_xor(b, o);
+            b = ob < b ? ob : b;
+        }
+    };
+    wave();
+    if (t % 64 == 0) {
+        sd[t / 64] = md;
+        sb[t / 64] = b;
+    }
+    __syncthreads();
+    if (t >= 64) return;
+    md = t < NT / 64 ? sd[t] : __builtin_huge_val();
+    b = t < NT / 64 ? sb[t] : kNone;
+    wave();
+    if (t == 0) {
+        unsigned long long u;
+        __builtin_memcpy(&u, &md, 8);
+        st.out->min_det_key = u;
+        st.out->first_bad = b == kNone ? -1 : b;
+    }
+}
+
+// ---- matrix operators by element blocks, in one launch per element type ----------
+// TET04, PEN06, PYR05 and hybrid meshes.  A block's row images start from zero
+// and go, whole, to the block's own place in a work array, its right-hand
+// sides to another; k_part_gather then writes each CSR row once, the sum of
+// its images in block order.  No colours, no row is read back, no element is
+// computed twice, and the order of every sum is fixed by the plan.  FT:
+// precision of the staged fields after x, y, z (FP32 for the mixed mode on
+// meshes of one type).
+//
+// Bound by latency, in the blocks (a 64-TET04 momentum block: staging 5 us, sums
+// 4 us, of 11) as in the gather, with 8-12 blocks to a CU; PEN06 half by FP64
+// arithmetic.  Whole calls, owner groups (each element computed by every group
+// that owns one of its rows: 1.6x) -> blocks: TET04 45^3 cubes momentum 110 -> 79
+// us, 90^3 695 -> 498; PEN06 57^3 momentum 183 -> 134, Poisson 150 -> 121; PYR05
+// 40^3 184 -> 120.  Coloured blocks (40 launches) -> blocks: hybrid 64^3 momentum
+// 816 -> 218, 20^3 680 -> 76.  A HEX08 mesh stays with owner
+// groups: k_part takes 0.42 ns per HEX08 element (65 k of the hybrid mesh) before
+// its gather, k_own as much in all (101^3).
+struct PartArgs {
+    const int32_t *img_ptr;   // [blocks + 1]
+    double *img, *sums;       // row images, [NRHS][VT] right-hand sides
+    int64_t VT;
+};
+
+template <class EL, int OP, class Q, class FT>
+__global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_part(KArgs k, PartArgs pa)
+{
+    constexpr int NEN = EL::NEN, W = Split<EL>::W, RA = NEN / W, NT = 64 * W;
+    constexpr int NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
+    extern __shared__ double lds[];
+    const int blk = k.color_blk[k.blk_offset + xcd_item(blockIdx.x, gridDim.x)];
+    const int e0 = k.blk_elem_ptr[blk], ne = k.blk_elem_ptr[blk + 1] - e0;
+    const int n0 = k.blk_node_ptr[blk], T = k.blk_node_ptr[blk + 1] - n0;
+    const int i0 = pa.img_ptr[blk], L = pa.img_ptr[blk + 1] - i0;
+    const int tid = threadIdx.x, el = tid & 63, wv = tid >> 6;
+    const int64_t N = k.N;
+    double *nd = lds;                                    // [3][T] coordinates
+    FT *nf = (FT *)(nd + 3 * T);                         // [NF - 3][T] u_x, u_y, u_z, rho, mu / Y
+    double *rimg = nd + 3 * T + ((NF - 3) * T * (int)sizeof(FT) + 7) / 8;   // [NRHS][T]
+    double *img = rimg + NRHS * T;                       // [L]
+    int *rbase = (int *)(img + L);                       // [T] row images' places in img
+    const bool act = el < ne;
+    const int e = e0 + (act ? el : 0);
+    int ln[NEN];
+#pragma unroll
+    for (int a = 0; a < NEN; ++a) ln[a] = k.elem_lnode[(int64_t)a * k.E + e];
+    constexpr int kOffWords = (RA * NEN + 3) / 4;
+    uint32_t offw[kOffWords];
+    {
+        const uint32_t *op = (const uint32_t *)(k.elem_off + (int64_t)e * k.off_stride + wv * RA * NEN);
+#pragma unroll
+        for (int q = 0; q < kOffWords; ++q) offw[q] = op[q];
+    }
+    const int ph = act ? (int)k.elem_phase[e] : -1, nph = k.blk_nphase[blk];
+    for (int t = tid; t < T; t += NT) {
+        const int g = k.blk_nodes[n0 + t];
+        rbase[t] = k.blk_rdesc[n0 + t] & 0xffff;
+        double f[NF];
+        f[0] = k.X[g];
+        f[1] = k.X[N + g];
+        f[2] = k.X[2 * N + g];
+        f[3] = k.u[g];
+        f[4] = k.u[N + g];
+        f[5] = k.u[2 * N + g];
+        f[6] = k.rho[g];
+        if constexpr (NF > 7) f[7] = OP == OP_MOM ? k.mu[g] : k.Y[g];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nd[c * T + t] = f[c];
+#pragma unroll
+        for (int c = 3; c < NF; ++c) nf[(c - 3) * T + t] = FT(f[c]);
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) rimg[r * T + t] = 0.0;
+    }
+    for (int t = tid; t < L; t += NT) img[t] = 0.0;
+    __syncthreads();
+
+    Q A[RA][NEN];
+    Q B[NRHS][RA];
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) A[r][b] = Q(0);
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) B[q][r] = Q(0);
+    }
+    double mindet = __builtin_huge_val();
+    const double inv_dt = 1.0 / k.dt;
+    if constexpr (NEN == 8 && sizeof(Q) == 8) {
+        if (wv == 0) hex_matrix<OP, 0>(nd, nf, T, ln, A, B, mindet, inv_dt, k.Dk);
+        else hex_matrix<OP, 1>(nd, nf, T, ln, A, B, mindet, inv_dt, k.Dk);
+    } else {
+        Geo<EL> GE;
+        load_geo<EL>(nd, T, ln, GE);
+        Rows<EL> rows;
+#pragma unroll
+        for (int a = 0; a < NEN; ++a) rows.v[a] = ln[a];
+        if (W == 1 || wv == 0) gauss_loop<EL, OP, Q, RA, 0, FT>(GE, nd, nf, T, rows, A, B, mindet, inv_dt, k.Dk, 0);
+        else gauss_loop<EL, OP, Q, RA, (RA % NEN), FT>(GE, nd, nf, T, rows, A, B, mindet, inv_dt, k.Dk, 0);
+    }
+    int lr[RA], base[RA];   // this lane's rows
+#pragma unroll
+    for (int r = 0; r < RA; ++r) {
+        lr[r] = W == 1 ? ln[r] : ln[r] + wv * (ln[(RA + r) % NEN] - ln[r]);   // (a select would go through scratch)
+        base[r] = rbase[lr[r]];
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+        if (wv == w) {
+            for (int p = 0; p < nph; ++p) {
+                if (ph != p) continue;
+#pragma unroll
+                for (int r = 0; r < RA; ++r) {
+#pragma unroll
+                    for (int b = 0; b < NEN; ++b) {
+                        const int idx = r * NEN + b;
+                        const int o = (offw[idx >> 2] >> (8 * (idx & 3))) & 0xff;
+                        lds_add(&img[base[r] + o], (double)A[r][b]);
+                    }
+#pragma unroll
+                    for (int q = 0; q < NRHS; ++q) lds_add(&rimg[q * T + lr[r]], (double)B[q][r]);
+                }
+            }
+        }
+        if (W > 1) __syncthreads();
+    }
+    if (wv == 0) {
+        double md = act ? mindet : __builtin_huge_val();
+        long long bad = (act && !(mindet > 0.0)) ? (long long)e : (long long)0x7fffffffffffffffLL;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            md = fmin(md, __shfl_xor(md, o));
+            const long long ob = __shfl_xor(bad, o);
+            bad = ob < bad ? ob : bad;
+        }
+        if (el == 0) {
+            k.blk_mindet[blk] = md;
+            k.blk_bad[blk] = bad == 0x7fffffffffffffffLL ? -1 : bad;
+        }
+    }
+    __syncthreads();
+    for (int t = tid; t < L; t += NT) pa.img[i0 + t] = img[t];
+    for (int t = tid; t < T; t += NT)
+#pragma unroll
+        for (int r = 0; r < NRHS; ++r) pa.sums[r * pa.VT + n0 + t] = rimg[r * T + t];
+}
+
+// 8 lanes per CSR row: lane l adds entries l, l + 8, l + 16 and l + 24 of two
+// of the row's images at a time (8 loads in flight), in block order, lane r
+// right-hand side r.  The places of eight images are read by the eight lanes
+// at once and handed round, so that a row waits for three loads in a chain
+// (its pointers, its places, its images): 43 -> 27 us on 57^3 PEN06 (195 k rows,
+// 110 MB) against 16 lanes that each read every place themselves.  Each XCD takes one contiguous range
+// of rows, as of blocks in k_part; the first group reduces the status word
+// meanwhile (the seven after it only keep the XCDs' ranges).
+constexpr int kGatherLanes = 8;
+constexpr int kGatherStatus = 8;   // leading groups
+template <int NRHS>
+__global__ void __launch_bounds__(256) k_part_gather(int64_t N, const int32_t *__restrict__ rowptr,
+                                                     const int32_t *__restrict__ ptr,
+                                                     const int32_t *__restrict__ slot,
+                                                     const int32_t *__restrict__ place, PartArgs pa,
+                                                     double *__restrict__ values, double *__restrict__ rhs,
+                                                     StatusArgs st)
+{
+    if (blockIdx.x < kGatherStatus) {
+        if (blockIdx.x == 0) reduce_status<256>(st);
+        return;
+    }
+    const int64_t i = (int64_t)xcd_item(blockIdx.x - kGatherStatus, gridDim.x - kGatherStatus) *
+                          (256 / kGatherLanes) + threadIdx.x / kGatherLanes;
+    const int lane = threadIdx.x % kGatherLanes;
+    if (i >= N) return;
+    const int r0 = rowptr[i], len = rowptr[i + 1] - r0;
+    const int q0 = ptr[i], q1 = ptr[i + 1];
+    double b = 0.0;
+    for (int j0 = 0; j0 < len; j0 += 4 * kGatherLanes) {
+        double s[4] = {0.0, 0.0, 0.0, 0.0};
+        int j[4];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            j[v] = j0 + v * kGatherLanes + lane;
+            if (j[v] >= len) j[v] = 0;
+        }
+        for (int q = q0; q < q1; q += kGatherLanes) {
+            const int qi = q + lane < q1 ? q + lane : q;
+            const int pl = place[qi], sl = slot[qi];
+            const int n = q1 - q < kGatherLanes ? q1 - q : kGatherLanes;
+            for (int u = 0; u < n; u += 2) {
+                const bool two = u + 1 < n;
+                const double *w0 = pa.img + __shfl(pl, u, kGatherLanes);
+                const double *w1 = pa.img + __shfl(pl, two ? u + 1 : u, kGatherLanes);
+                double x0[4], x1[4];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    x0[v] = w0[j[v]];
+                    x1[v] = w1[j[v]];
+                }
+                if (j0 == 0) {
+                    const int t0 = __shfl(sl, u, kGatherLanes), t1 = __shfl(sl, two ? u + 1 : u, kGatherLanes);
+                    if (lane < NRHS) {
+                        b += pa.sums[lane * pa.VT + t0];
+                        if (two) b += pa.sums[lane * pa.VT + t1];
+                    }
+                }
+#pragma unroll
+                for (int v = 0; v < 4; ++v) {
+                    s[v] += x0[v];
+                    if (two) s[v] += x1[v];
+                }
+            }
+        }
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (j0 + v * kGatherLanes + lane < len) values[r0 + j0 + v * kGatherLanes + lane] = s[v];
+    }
+    if (lane < NRHS) rhs[lane * N + i] = b;
+}
+
+template <class EL, int OP>
+void launch_part_op(const AsmLaunch &L, KArgs k, const PartArgs &pa, bool mixed, bool hybrid, hipStream_t s)
+{
+    k.blk_offset = L.first;
+    const dim3 grid(L.count), block(64 * Split<EL>::W);
+    // (a HEX08 block is one of a hybrid mesh: a mesh of HEX08 takes k_own)
+    if (!mixed) hipLaunchKernelGGL((k_part<EL, OP, double, double>), grid, block, L.lds[OP], s, k, pa);
+    else if (hybrid || EL::NEN == 8) hipLaunchKernelGGL((k_part<EL, OP, float, double>), grid, block, L.lds[OP], s, k, pa);
+    else if constexpr (EL::NEN != 8) hipLaunchKernelGGL((k_part<EL, OP, float, float>), grid, block, L.lds[OP], s, k, pa);
+}
+
+template <class EL>
+void launch_part(const AsmLaunch &L, const KArgs &k, const PartArgs &pa, int op, bool mixed, bool hybrid, hipStream_t s)
+{
+    switch (op) {
+    case OP_MOM: launch_part_op<EL, OP_MOM>(L, k, pa, mixed, hybrid, s); break;
+    case OP_SCA: launch_part_op<EL, OP_SCA>(L, k, pa, mixed, hybrid, s); break;
+    default: launch_part_op<EL, OP_POI>(L, k, pa, mixed, hybrid, s); break;
+    }
+}
+
+constexpr int kStatusThreads = 1024;
+__global__ void __launch_bounds__(kStatusThreads) k_asm_status(StatusArgs st)
+{
+    reduce_status<kStatusThreads>(st);
+}
+
+template <class EL, int OP, class Q>
+void launch_one(const AsmLaunch &L, KArgs k, hipStream_t s)
+{
+    k.blk_offset = L.first;
+    hipLaunchKernelGGL((k_assemble<EL, OP, Q>), dim3(L.count), dim3(64 * Split<EL>::W), L.lds[OP], s, k);
+}
+
+template <class EL, int FORM>
+void launch_residual(const AsmLaunch &L, KArgs k, hipStream_t s)
+{
+    k.blk_offset = L.first;
+    hipLaunchKernelGGL((k_residual<EL, FORM>), dim3(L.count), dim3(64 * Split<EL>::W), L.lds[OP_RES], s, k);
+}
+
+template <class EL>
+void launch_type(const AsmLaunch &L, const KArgs &k, int op, bool mixed, hipStream_t s)
+{
+    switch (op) {
+    case OP_MOM: mixed ? launch_one<EL, OP_MOM, float>(L, k, s) : launch_one<EL, OP_MOM, double>(L, k, s); break;
+    case OP_SCA: mixed ? launch_one<EL, OP_SCA, float>(L, k, s) : launch_one<EL, OP_SCA, double>(L, k, s); break;
+    case OP_POI: mixed ? launch_one<EL, OP_POI, float>(L, k, s) : launch_one<EL, OP_POI, double>(L, k, s); break;
+    // element-vector passes are FP64 only
+    case OP_RES:
+        switch (k.form) {
+        case 0: launch_residual<EL, 0>(L, k, s); break;
+        case 1: launch_residual<EL, 1>(L, k, s); break;
+        case 2: launch_residual<EL, 2>(L, k, s); break;
+        default: launch_residual<EL, 3>(L, k, s); break;
+        }
+        break;
+    case OP_GRD: launch_one<EL, OP_GRD, double>(L, k, s); break;
+    case OP_SRS: launch_one<EL, OP_SRS, double>(L, k, s); break;
+    default: launch_one<EL, OP_DIV, double>(L, k, s); break;
+    }
+}
+
+// ---- element-vector passes: HEX08
 // An element-vector pass on one HEX08 element (FP64; the terms of
 // element_vector_point, fields in LDS as there): per component a source s
 // tested with N_a and a flux q tested with the reference gradient of N_a.
@@ -1353,13 +1831,19 @@ __global__ void __launch_bounds__(64, 2) k_vec(KArgs k, double *__restrict__ wor
 // out[r][i] = node i's block sums in block order, one thread per node, four
 // places at a time, so that their loads are in flight together.  (Nodes of
 // one block only, ~40 %, written by k_vec itself instead: the scattered
-// stores cost k_vec 6 us on 101^3 HEX08 and saved 3.5 us here.)
+// stores cost k_vec 6 us on 101^3 HEX08 and saved 3.5 us here.)  The first
+// group reduces the status word meanwhile.
 template <int NRHS>
 __global__ void __launch_bounds__(256) k_vec_gather(int64_t N, int64_t VT, const int32_t *__restrict__ ptr,
                                                     const int32_t *__restrict__ slot,
-                                                    const double *__restrict__ work, double *__restrict__ out)
+                                                    const double *__restrict__ work, double *__restrict__ out,
+                                                    StatusArgs st)
 {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (blockIdx.x == 0) {
+        reduce_status<256>(st);
+        return;
+    }
+    const int64_t i = (int64_t)(blockIdx.x - 1) * 256 + threadIdx.x;
     if (i >= N) return;
     double s[NRHS];
 #pragma unroll
@@ -1864,8 +2348,9 @@ hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const
     // each mesh's status word from its per-block scratch (as launch_assemble)
     for (int i = 0; i < n; ++i) {
         const KArgs k = make_kargs(a[i]);
-        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, a[i].m->nblk,
-                           a[i].status_out ? a[i].status_out : a[i].status);
+        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s,
+                           StatusArgs{k.blk_mindet, k.blk_bad, a[i].m->nblk,
+                                      a[i].status_out ? a[i].status_out : a[i].status});
     }
     return hipGetLastError();
 }
@@ -1875,8 +2360,9 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
     const DevMesh &m = *a.m;
     if (a.op < 0 || a.op >= kNumOps) return hipErrorInvalidValue;
     KArgs k = make_kargs(a);
+    AsmStatus *const out = a.status_out ? a.status_out : a.status;
     if (a.op < OP_RES && m.own_G > 0) {
-        // matrix operators of a single-type mesh: the owner assembly, one launch
+        // matrix operators of a HEX08 mesh: the owner assembly, one launch
         OArgs o{};
         o.X = m.X;
         o.rowptr = m.rowptr;
@@ -1902,23 +2388,43 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
         o.g_mindet = k.blk_mindet;
         o.g_bad = k.blk_bad;
         const int nf = a.op == OP_POI ? 7 : 8, nrhs = a.op == OP_MOM ? 3 : 1;
-        const int copies = m.own_priv ? kOwnTasks / 64 : 1;
-        if ((m.own_priv != 0) != (m.nen != 8)) return hipErrorInvalidValue;   // plan and kernel disagree
+        if (m.nen != 8) return hipErrorInvalidValue;   // plan and kernel disagree
         // x, y, z in FP64, the other fields in the quadrature's precision
         const size_t fb = mixed ? sizeof(float) : sizeof(double);
         const size_t fields = 3 * (size_t)m.own_max_nodes + ((nf - 3) * (size_t)m.own_max_nodes * fb + 7) / 8;
-        const size_t lds = (fields + (size_t)copies * (m.own_max_img + nrhs * m.own_max_rows)) * sizeof(double);
-        switch (m.nen) {
-        case 8: launch_own<Hex>(o, a.op, m.own_G, lds, mixed, s); break;
-        case 6: launch_own<Pen>(o, a.op, m.own_G, lds, mixed, s); break;
-        case 5: launch_own<Pyr>(o, a.op, m.own_G, lds, mixed, s); break;
-        case 4: launch_own<Tet>(o, a.op, m.own_G, lds, mixed, s); break;
-        default: return hipErrorInvalidValue;
-        }
+        const size_t lds = (fields + (size_t)m.own_max_img + nrhs * m.own_max_rows) * sizeof(double);
+        launch_own(o, a.op, m.own_G, lds, mixed, s);
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
-        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, m.own_G,
-                           a.status_out ? a.status_out : a.status);
+        if (!a.want_status) return hipSuccess;
+        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s,
+                           StatusArgs{k.blk_mindet, k.blk_bad, m.own_G, out});
+        return hipGetLastError();
+    }
+    if (a.op < OP_RES && a.img_work) {
+        // matrix operators of the other meshes: by blocks, then the gather
+        k.color_blk = m.vec_blk;
+        const PartArgs pa{m.blk_img_ptr, a.img_work, a.img_work + m.img_total, m.vec_T};
+        for (const AsmLaunch &L : m.vec_launches) {
+            switch (L.nen) {
+            case 8: launch_part<Hex>(L, k, pa, a.op, mixed, m.hybrid, s); break;
+            case 6: launch_part<Pen>(L, k, pa, a.op, mixed, m.hybrid, s); break;
+            case 5: launch_part<Pyr>(L, k, pa, a.op, mixed, m.hybrid, s); break;
+            case 4: launch_part<Tet>(L, k, pa, a.op, mixed, m.hybrid, s); break;
+            default: return hipErrorInvalidValue;
+            }
+            const hipError_t err = hipGetLastError();
+            if (err != hipSuccess) return err;
+        }
+        const int rows = 256 / kGatherLanes;
+        const dim3 grid((unsigned)((m.N + rows - 1) / rows) + kGatherStatus), block(256);
+        const StatusArgs st{k.blk_mindet, k.blk_bad, m.nblk, out};
+        if (a.op == OP_MOM)
+            hipLaunchKernelGGL(k_part_gather<3>, grid, block, 0, s, m.N, m.rowptr, m.node_slot_ptr, m.node_slot,
+                               m.node_img, pa, a.values, a.rhs, st);
+        else
+            hipLaunchKernelGGL(k_part_gather<1>, grid, block, 0, s, m.N, m.rowptr, m.node_slot_ptr, m.node_slot,
+                               m.node_img, pa, a.values, a.rhs, st);
         return hipGetLastError();
     }
     if (a.op >= OP_RES && a.vec_work) {
@@ -1935,15 +2441,14 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
             const hipError_t err = hipGetLastError();
             if (err != hipSuccess) return err;
         }
-        const dim3 grid((unsigned)((m.N + 255) / 256)), block(256);
+        const dim3 grid((unsigned)((m.N + 255) / 256) + 1), block(256);
+        const StatusArgs st{k.blk_mindet, k.blk_bad, m.nblk, out};
         switch (a.op) {
-        case OP_RES: hipLaunchKernelGGL(k_vec_gather<4>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
-        case OP_GRD: hipLaunchKernelGGL(k_vec_gather<3>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
-        case OP_SRS: hipLaunchKernelGGL(k_vec_gather<2>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
-        default: hipLaunchKernelGGL(k_vec_gather<1>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs); break;
+        case OP_RES: hipLaunchKernelGGL(k_vec_gather<4>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs, st); break;
+        case OP_GRD: hipLaunchKernelGGL(k_vec_gather<3>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs, st); break;
+        case OP_SRS: hipLaunchKernelGGL(k_vec_gather<2>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs, st); break;
+        default: hipLaunchKernelGGL(k_vec_gather<1>, grid, block, 0, s, m.N, m.vec_T, m.node_slot_ptr, m.node_slot, a.vec_work, a.rhs, st); break;
         }
-        hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, m.nblk,
-                           a.status_out ? a.status_out : a.status);
         return hipGetLastError();
     }
     // one launch per (colour, element type), in the planned order
@@ -1959,8 +2464,9 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
     }
-    hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, k.blk_mindet, k.blk_bad, m.nblk,
-                       a.status_out ? a.status_out : a.status);
+    if (!a.want_status) return hipSuccess;
+    hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s,
+                       StatusArgs{k.blk_mindet, k.blk_bad, m.nblk, out});
     return hipGetLastError();
 }
 
@@ -1998,7 +2504,8 @@ hipError_t launch_assemble_block(const DevMesh &m, const DevRowPlan &r, int form
     }
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s, r.w_mindet, r.w_bad, r.n_waves, status);
+    hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s,
+                       StatusArgs{r.w_mindet, r.w_bad, r.n_waves, status});
     return hipGetLastError();
 }
 

@@ -125,6 +125,10 @@ void for_each_array(MeshImage &I, DevMesh &d, AsmStatus **status, F f)
         v(&d.node_slot_ptr, P.node_slot_ptr);
         v(&d.node_slot, P.node_slot);
     }
+    if (d.img_total) {
+        v(&d.blk_img_ptr, P.blk_img_ptr);
+        v(&d.node_img, P.node_img);
+    }
     v(&d.spmv_desc, I.spmv_desc);
     v(&d.spmv_roff, I.spmv_roff);
     v(&d.spmv_lidx, I.spmv_lidx);
@@ -172,14 +176,19 @@ static thread_local std::vector<std::vector<int32_t>> t_spmv_stamp, t_spmv_loc; 
 
 int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double *coords, int64_t n_elems,
                  const int32_t *conn, int64_t n_dirichlet, const int32_t *dirichlet_nodes, bool renumber,
-                 MeshImage &I, std::string &err, bool owner_plan, bool vector_passes)
+                 MeshImage &I, std::string &err, bool owner_plan, bool vector_passes, bool images)
 {
     if (n_dirichlet < 0 || (n_dirichlet > 0 && !dirichlet_nodes)) {
         err = "bad Dirichlet list";
         return FE_EINVAL;
     }
     Plan &P = I.P;
-    P.want_gather = vector_passes;
+    // HEX08 meshes assemble by owner groups, every other by element blocks
+    bool one_type = true;
+    for (int64_t e = 1; types && e < n_elems && one_type; ++e) one_type = types[e] == types[0];
+    const bool hex = one_type && (types && n_elems > 0 ? types[0] : stride) == 8;
+    P.want_images = images && !hex && (owner_plan || !one_type);
+    P.want_gather = vector_passes || P.want_images;
     int st = build_plan(stride, types, n_nodes, coords, n_elems, conn, renumber, P, err);
     if (st != FE_OK) return st;
     I.is_dir.assign(n_nodes, 0);
@@ -378,7 +387,7 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
     // the element-vector passes: one launch per element type over its blocks
     d.vec_launches.clear();
     I.vec_blk.clear();
-    if (vector_passes) {
+    if (P.want_gather) {
         d.vec_T = P.blk_node_ptr.back();
         for (int nen : {8, 6, 5, 4}) {
             AsmLaunch L{nen, (int)I.vec_blk.size(), 0, {0, 0, 0, 0, 0, 0, 0}};
@@ -391,16 +400,17 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
             if (L.count) d.vec_launches.push_back(L);
         }
     }
-    // the owner plan of the matrix assembly (meshes of one element type)
+    d.hybrid = !P.etype.empty();
+    d.img_total = P.blk_img_ptr.empty() ? 0 : P.blk_img_ptr.back();
+    // the owner plan of the matrix assembly (HEX08 meshes)
     I.O = OwnerPlan();
-    if (owner_plan && P.etype.empty()) {
+    if (owner_plan && hex) {
         st = build_owner_plan(P, I.O, err);
         if (st != FE_OK) return st;
+        arrange_waves(I.O);
         const OwnerPlan &O = I.O;
         d.own_G = (int64_t)O.groups.size();
         d.own_T = (int64_t)O.tk_elem.size();
-        d.own_ra = O.ra;
-        d.own_priv = O.wave_private ? 1 : 0;
         d.own_ln_stride = O.ln_stride;
         d.own_off_stride = O.off_stride;
         d.own_max_nodes = O.max_nodes;
@@ -452,6 +462,7 @@ void mesh_release(fe_mesh_s *m)
     m->sym = fe_mesh_s::SymState();
     m->resident = fe_mesh_s::ResidentState();
     m->vec_work = nullptr;
+    m->img_work = nullptr;
     m->step_work = nullptr;
     m->scalar_work = nullptr;
     m->wall = DevWall();
@@ -522,6 +533,10 @@ fe_status ensure_cg(fe_mesh_s *m, int max_iter, bool mixed)
     return FE_OK;
 }
 
+// The pinned word that an assembly's status reduction writes for
+// read_asm_status, so that no copy is queued behind it.
+static AsmStatus *host_status(fe_ctx_s *c) { return (AsmStatus *)c->host; }
+
 fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, double *values, double *rhs,
                          hipStream_t stream)
 {
@@ -535,6 +550,8 @@ fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, do
     a.rho = f->rho;
     a.mu = f->mu;
     a.status = m->status;
+    a.status_out = host_status(c);
+    a.img_work = m->img_work;
     const int passes = f->op == FE_OP_SCALAR ? f->n_scalars : 1;
     for (int k = 0; k < passes; ++k) {
         a.values = values + (int64_t)k * d.nnz;
@@ -543,6 +560,7 @@ fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, do
             a.Y = f->Y + (int64_t)k * d.N;
             a.Dk = f->D[k];
         }
+        a.want_status = k == passes - 1;   // every pass has the same elements, so the same word
         HIPCALL(c, launch_assemble(a, prec == FE_MIXED, stream));
     }
     return FE_OK;
@@ -588,9 +606,8 @@ fe_status sync(fe_ctx_s *c)
     return FE_OK;
 }
 
-// Reads the status word of the assembly launches queued last (synchronises)
-// and reports the first element with det J <= 0 by its user id.
-// Interprets a status word read back to the host.
+// Interprets a status word on the host: reports the first element with
+// det J <= 0 by its user id.
 static fe_status check_asm_status(fe_mesh_s *m, const AsmStatus *hs, fe_asm_info *info)
 {
     fe_ctx_s *c = m->ctx;
@@ -607,14 +624,14 @@ static fe_status check_asm_status(fe_mesh_s *m, const AsmStatus *hs, fe_asm_info
     return FE_OK;
 }
 
+// Reads the status word of the assembly launches queued last, which wrote it
+// to host_status (synchronises).
 fe_status read_asm_status(fe_mesh_s *m, fe_asm_info *info)
 {
     fe_ctx_s *c = m->ctx;
-    AsmStatus *hs = (AsmStatus *)c->host;
-    HIPCALL(c, hipMemcpyAsync(hs, m->status, sizeof(AsmStatus), hipMemcpyDeviceToHost, c->stream));
     fe_status s = sync(c);
     if (s != FE_OK) return s;
-    return check_asm_status(m, hs, info);
+    return check_asm_status(m, host_status(c), info);
 }
 
 // Queues one element-vector pass (kOpResidual, kOpGradient, kOpDivergence)
@@ -649,7 +666,7 @@ fe_status element_vectors(fe_mesh_s *m, int op, double dt, const double *u, cons
     a.form = form;
     a.rhs = out;
     a.status = m->status;
-    a.status_out = defer;
+    a.status_out = defer ? defer : host_status(c);
     {
         ProfScope ps(c, 4);
         HIPCALL(c, launch_assemble(a, false, c->stream));
@@ -1114,6 +1131,14 @@ static fe_status mesh_upload(fe_ctx c, int stride, const uint8_t *types, int64_t
     m->ctx = c;
     fe_status s = mesh_commit(m, *img, c->stream);
     if (s == FE_OK && hipStreamSynchronize(c->stream) != hipSuccess) s = fail(c, FE_EDEVICE, "upload sync failed");
+    // laid out now rather than in the first assembly, which it would double
+    if (s == FE_OK && m->dm.img_total) {
+        s = mesh_alloc(m, (void **)&m->img_work, image_bytes(m->dm));
+        if (s == FE_ENOMEM) {   // no room: colour by colour
+            m->img_work = nullptr;
+            s = FE_OK;
+        }
+    }
     if (s != FE_OK) {
         (void)hipStreamSynchronize(c->stream);
         mesh_release(m);
@@ -1297,8 +1322,8 @@ fe_status fe_assemble_block(fe_mesh m, uint32_t form, double dt, const double *u
     if (s != FE_OK) return s;
     {
         ProfScope ps(c, 1);
-        HIPCALL(c, launch_assemble_block(m->dm, m->rowplan, (int)form, dt, u, rho, mu, values, rhs, m->status,
-                                         c->stream));
+        HIPCALL(c, launch_assemble_block(m->dm, m->rowplan, (int)form, dt, u, rho, mu, values, rhs,
+                                         host_status(c), c->stream));
     }
     return read_asm_status(m, info);
 }

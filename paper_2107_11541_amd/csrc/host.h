@@ -74,6 +74,7 @@ struct fe_mesh_s {
     feasm::CGWork cg;
     double *vec_work = nullptr;          // element-vector passes: [4][vec_T] block sums
     bool vec_off = false;                // no room for vec_work: the passes run colour by colour
+    double *img_work = nullptr;          // matrix assembly by blocks: row images, then [3][vec_T] right-hand sides
     double *step_work = nullptr;         // explicit step: u0 [3][N], residual + mass [4][N], f [N], g [3][N]
     feasm::DevWall wall;                 // wall faces of the wall model (F = 0: none)
     double *scalar_work = nullptr;       // explicit scalar step: Y0 [N], residual + mass [2][N]
@@ -145,9 +146,14 @@ struct MeshImage {
 // serving runtime, which assembles each mesh once, skips it: its host time
 // exceeds the assembly time it saves there).  vector_passes: build the
 // gather map of the element-vector passes (the serving runtime runs none).
+// images: plan the assembly by blocks with a gather, of hybrid meshes and,
+// with owner_plan, of the other meshes that take no owner plan.
 int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double *coords, int64_t n_elems,
                  const int32_t *conn, int64_t n_dirichlet, const int32_t *dirichlet_nodes, bool renumber,
-                 MeshImage &img, std::string &err, bool owner_plan = true, bool vector_passes = true);
+                 MeshImage &img, std::string &err, bool owner_plan = true, bool vector_passes = true,
+                 bool images = true);
+// Bytes of img_work: the blocks' row images and their right-hand sides.
+inline size_t image_bytes(const DevMesh &d) { return ((size_t)d.img_total + 3 * (size_t)d.vec_T) * sizeof(double); }
 // Allocates (from m->arena or hipMalloc) and queues the copies of img on
 // `stream`.  img must stay alive until the copies have completed.
 fe_status mesh_commit(fe_mesh_s *m, MeshImage &img, hipStream_t stream);
@@ -158,7 +164,7 @@ void mesh_release(fe_mesh_s *m);
 size_t cg_bytes(int64_t n, int max_iter);
 fe_status ensure_cg(fe_mesh_s *m, int max_iter, bool mixed);
 // Queues every assembly pass of one operator on `stream`; the status word
-// stays on the device (m->status).
+// goes to the context's pinned word.
 fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, double *values, double *rhs,
                          hipStream_t stream);
 

@@ -36,6 +36,9 @@ struct DevMesh {
     std::vector<AsmLaunch> vec_launches;   // host: element-vector passes, one launch per type over vec_blk
     int64_t vec_T = 0;                  // touched rows of all blocks (0: no gather map)
     int32_t *vec_blk = nullptr, *node_slot_ptr = nullptr, *node_slot = nullptr;
+    int64_t img_total = 0;              // entries of all blocks' row images (0: no matrix gather)
+    int32_t *blk_img_ptr = nullptr, *node_img = nullptr;
+    bool hybrid = false;                // several element types
 
     double *X = nullptr;                // [3][N]
     int32_t *rowptr = nullptr, *colidx = nullptr, *diagpos = nullptr;
@@ -57,12 +60,12 @@ struct DevMesh {
     // sentinel); roff holds each block's row offsets relative to its first
     // nonzero, rows + 1 entries at roff[first row + b]; lidx and cols the
     // block-local column indices and column sets (see SpmvMap).
-    // Owner plan of the matrix assembly (single-type meshes; own_G = 0
+    // Owner plan of the matrix assembly (HEX08 meshes; own_G = 0
     // otherwise): groups {first task, tasks, first row, rows}, their touched
     // nodes (owned rows first), phases, and per task the element, the local
     // node of each (rotated) element node and the in-row column positions.
     int64_t own_G = 0, own_T = 0;
-    int own_ra = 0, own_ln_stride = 0, own_off_stride = 0, own_priv = 0;
+    int own_ln_stride = 0, own_off_stride = 0;
     int own_max_nodes = 0, own_max_img = 0, own_max_rows = 0;
     int4 *own_groups = nullptr;
     int32_t *own_node_ptr = nullptr, *own_nodes = nullptr, *own_elem = nullptr;
@@ -163,7 +166,9 @@ struct AsmArgs {
     double *rhs;             // first rhs row [N] (momentum: 3 rows of N; element-vector passes: their rows)
     AsmStatus *status;       // status word, followed by the per-block / per-group scratch
     double *vec_work = nullptr;   // element-vector passes: block sums [4][vec_T] (null: colour by colour)
+    double *img_work = nullptr;   // matrix passes by blocks: row images [img_total], sums [3][vec_T] (null: as above)
     AsmStatus *status_out = nullptr;   // where the reduced word goes instead of *status (null: *status)
+    bool want_status = true;  // false: leave the status word as it is (where it takes a launch)
 };
 
 // Launchers (asm_kernels.hip).

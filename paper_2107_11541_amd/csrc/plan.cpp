@@ -104,7 +104,7 @@ void Plan::clear()
     max_row = n_colors = max_T = max_L = max_phase = 0;
     for (auto *v : {&node_perm, &node_iperm, &elem_perm, &conn, &rowptr, &colidx, &diagpos, &blk_elem_ptr,
                     &blk_node_ptr, &blk_nodes, &blk_img, &blk_rdesc, &blk_rowstart, &blk_color, &color_ptr,
-                    &color_blk, &node_slot_ptr, &node_slot})
+                    &color_blk, &node_slot_ptr, &node_slot, &blk_img_ptr, &node_img})
         v->clear();
     for (auto *v : {&etype, &blk_nphase, &elem_off, &blk_nen, &elem_phase}) v->clear();
     X.clear();
@@ -747,6 +747,23 @@ static int build_plan_impl(int S, const uint8_t *types, int64_t N, const double 
                 return FE_EBADMESH;
             }
         }
+    }
+    // 8. places of the touched rows in the blocks' images laid end to end
+    int64_t images = 0;
+    for (int32_t n : P.blk_img) images += n;
+    if (P.want_gather && P.want_images && images <= INT32_MAX) {
+        P.blk_img_ptr.assign(nblk + 1, 0);
+        for (int64_t b = 0; b < nblk; ++b) P.blk_img_ptr[b + 1] = P.blk_img_ptr[b] + P.blk_img[b];
+        std::vector<int32_t> place(P.blk_nodes.size());
+        parallel_for(nblk, [&](int64_t b0, int64_t b1) {
+            for (int64_t b = b0; b < b1; ++b)
+                for (int32_t k = P.blk_node_ptr[b]; k < P.blk_node_ptr[b + 1]; ++k)
+                    place[k] = P.blk_img_ptr[b] + (P.blk_rdesc[k] & 0xffff);
+        });
+        P.node_img.resize(P.node_slot.size());
+        parallel_for((int64_t)P.node_slot.size(), [&](int64_t q0, int64_t q1) {
+            for (int64_t q = q0; q < q1; ++q) P.node_img[q] = place[P.node_slot[q]];
+        });
     }
     return FE_OK;
 }

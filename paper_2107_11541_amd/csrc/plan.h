@@ -85,6 +85,11 @@ struct Plan {
     // blk_nodes, ascending, at node_slot[node_slot_ptr[i] ..]
     bool want_gather = false;
     std::vector<int32_t> node_slot_ptr, node_slot;
+    // the matrix gather (want_images): the blocks' row images one after the
+    // other, block b's at blk_img_ptr[b]; node_img parallel to node_slot, the
+    // row's place in all images.  Left empty when they exceed 2^31 entries.
+    bool want_images = false;
+    std::vector<int32_t> blk_img_ptr, node_img;
     int n_colors = 0, max_T = 0, max_L = 0, max_phase = 0;
 
     int64_t n_blocks() const { return (int64_t)blk_elem_ptr.size() - 1; }
@@ -171,6 +176,13 @@ struct OwnerPlan {
 // Single-type meshes only (P.etype empty).  0 or an fe_status code with a
 // message in err.
 int build_owner_plan(const Plan &P, OwnerPlan &O, std::string &err);
+// Rearranges a HEX08 owner plan for the kernel: each group's tasks dealt to
+// its wavefronts of 64 (all but the last full) so that tasks of one wavefront
+// hold a row at different local places where possible.  tk_phase becomes the
+// task's step within its wavefront (tasks of one step hold any row at most
+// once per local place) and nphase the steps of the group's longest wavefront:
+// the kernel adds wavefront after wavefront, local row after local row.
+void arrange_waves(OwnerPlan &O);
 // The node order of a HEX08 element seen from face f (0..5: -z, +z, -y, +y,
 // -x, +x): kHexFaceRot[f][b] is the element's local node at the rotated
 // element's node b; nodes 0-3 of the rotated element are face f.

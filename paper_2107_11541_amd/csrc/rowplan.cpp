@@ -496,4 +496,60 @@ int build_owner_plan(const Plan &P, OwnerPlan &O, std::string &err)
     return FE_OK;
 }
 
+void arrange_waves(OwnerPlan &O)
+{
+    const int64_t G = (int64_t)O.groups.size();
+    const int ra = O.ra, ls = O.ln_stride, os = O.off_stride;
+    parallel_chunks((G + 255) / 256, [&](int64_t c) {
+        std::vector<uint8_t> cnt;   // [wave][owned row][local place]: tasks that hold it
+        std::vector<int32_t> of, elem;
+        std::vector<uint8_t> step, off;
+        std::vector<OwnLn> ln;
+        for (int64_t g = c * 256; g < std::min<int64_t>(G, (c + 1) * 256); ++g) {
+            const OwnGroup &q = O.groups[g];
+            const int n = q.n_tasks, nr = q.n_rows, nw = (n + 63) / 64;
+            cnt.assign((size_t)nw * nr * ra, 0);
+            int fill[kOwnTasks / 64] = {};
+            of.resize(n);
+            step.resize(n);
+            int steps = 1;
+            for (int t = 0; t < n; ++t) {
+                const OwnLn *l = &O.tk_ln[(size_t)(q.first_task + t) * ls];
+                int best = -1, bc = 256;
+                for (int w = 0; w < nw; ++w) {
+                    if (fill[w] >= (w < nw - 1 ? 64 : n - 64 * (nw - 1))) continue;
+                    int m = 0;
+                    for (int r = 0; r < ra; ++r)
+                        if (l[r] < nr) m = std::max<int>(m, cnt[((size_t)w * nr + l[r]) * ra + r]);
+                    if (m < bc) {
+                        bc = m;
+                        best = w;
+                    }
+                }
+                of[t] = best;
+                step[t] = (uint8_t)bc;
+                ++fill[best];
+                for (int r = 0; r < ra; ++r)
+                    if (l[r] < nr) cnt[((size_t)best * nr + l[r]) * ra + r] = (uint8_t)(bc + 1);
+                steps = std::max(steps, bc + 1);
+            }
+            const size_t t0 = (size_t)q.first_task;
+            elem.assign(O.tk_elem.begin() + t0, O.tk_elem.begin() + t0 + n);
+            ln.assign(O.tk_ln.begin() + t0 * ls, O.tk_ln.begin() + (t0 + n) * ls);
+            off.assign(O.tk_off.begin() + t0 * os, O.tk_off.begin() + (t0 + n) * os);
+            size_t d = t0;
+            for (int w = 0; w < nw; ++w)
+                for (int t = 0; t < n; ++t)
+                    if (of[t] == w) {
+                        O.tk_elem[d] = elem[t];
+                        O.tk_phase[d] = step[t];
+                        memcpy(&O.tk_ln[d * ls], &ln[(size_t)t * ls], ls * sizeof(OwnLn));
+                        memcpy(&O.tk_off[d * os], &off[(size_t)t * os], os);
+                        ++d;
+                    }
+            O.nphase[g] = (uint8_t)steps;
+        }
+    });
+}
+
 }  // namespace feasm

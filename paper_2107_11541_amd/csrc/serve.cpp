@@ -141,6 +141,15 @@ void give_image(fe_server_s *S, std::unique_ptr<MeshImage> &img)
     if (S->img_pool.size() < S->pool_cap) S->img_pool.push_back(std::move(mine));
 }
 
+// Arena bytes of a planned request: mesh, PCG work and the job's arrays.
+size_t request_bytes(const MeshImage &I, int max_iter)
+{
+    const DevMesh &d = I.d;
+    const size_t vb = DevArena::round((size_t)d.nnz * 8), nb = DevArena::round((size_t)d.N * 8);
+    return I.device_bytes() + cg_bytes(d.N, max_iter) + 2 * vb + 3 * nb + nb + 5 * nb + nb +
+           (d.img_total ? DevArena::round(image_bytes(d)) : 0);
+}
+
 // idle: no other request waits to be planned (see planner_main)
 void plan_job(fe_server_s *S, Job *j, bool idle)
 {
@@ -158,9 +167,13 @@ void plan_job(fe_server_s *S, Job *j, bool idle)
         st = FE_EINVAL;
         err = "request needs dt > 0, rtol > 0, max_iter >= 0 and u, rho, mu, x";
     } else {
-        st = mesh_prepare(q.elem_types ? 8 : (int)q.type, q.elem_types, q.n_nodes, q.coords, q.n_elems, q.conn,
-                          q.n_dirichlet,
-                          q.dirichlet_nodes, true, *j->img, err, false, false);
+        // a hybrid mesh assembles by blocks, as fe_assemble does; one that would
+        // then not fit the empty arena, colour by colour
+        for (const bool images : {true, false}) {
+            st = mesh_prepare(q.elem_types ? 8 : (int)q.type, q.elem_types, q.n_nodes, q.coords, q.n_elems, q.conn,
+                              q.n_dirichlet, q.dirichlet_nodes, true, *j->img, err, false, false, images);
+            if (st != FE_OK || !j->img->d.img_total || request_bytes(*j->img, q.max_iter) <= S->arena->capacity()) break;
+        }
     }
     if (st != FE_OK) {
         j->res.status = (fe_status)st;
@@ -179,8 +192,7 @@ void plan_job(fe_server_s *S, Job *j, bool idle)
         f[3 * N + i] = q.rho[perm[i]];
         f[4 * N + i] = q.mu[perm[i]];
     }
-    const size_t vb = DevArena::round((size_t)d.nnz * 8), nb = DevArena::round((size_t)N * 8);
-    j->bytes = j->img->device_bytes() + cg_bytes(N, q.max_iter) + 2 * vb + 3 * nb + nb + 5 * nb + nb;
+    j->bytes = request_bytes(*j->img, q.max_iter);
 }
 
 void planner_main(fe_server_s *S)
@@ -258,6 +270,7 @@ AsmArgs job_asm_args(Job *j, int op)
     a.rho = j->fields_d + 3 * N;
     a.mu = j->fields_d + 4 * N;
     a.status = m->status;
+    a.img_work = m->img_work;
     a.values = op == FE_OP_MOMENTUM ? j->vals_m : j->vals_p;
     a.rhs = op == FE_OP_MOMENTUM ? j->rhs_m : j->rhs_p;
     return a;
@@ -290,6 +303,7 @@ fe_status admit(fe_server_s *S, Job *j)
     }
     fe_status s = mesh_commit(m, *j->img, S->stream);
     if (s == FE_OK) s = ensure_cg(m, q.max_iter, false);
+    if (s == FE_OK && d.img_total) s = mesh_alloc(m, (void **)&m->img_work, image_bytes(d));
     double **bufs[] = {&j->vals_m, &j->rhs_m, &j->vals_p, &j->rhs_p, &j->fields_d, &j->x_d};
     const size_t sizes[] = {(size_t)nnz, (size_t)3 * N, (size_t)nnz, (size_t)N, (size_t)5 * N, (size_t)N};
     for (int b = 0; b < 6 && s == FE_OK; ++b) s = mesh_alloc(m, (void **)bufs[b], sizes[b] * sizeof(double));
@@ -316,20 +330,27 @@ fe_status admit(fe_server_s *S, Job *j)
 // The momentum and Poisson assemblies of the requests admitted in one
 // dispatcher pass: one launch per (colour, type) launch index and element
 // type over all of them, each request's blocks running the code of its own
-// coloured launch (its results do not depend on the batch).
+// coloured launch (its results do not depend on the batch).  Hybrid meshes
+// assemble by blocks, each on its own.
 fe_status assemble_admitted(fe_server_s *S, const std::vector<Job *> &js)
 {
     fe_ctx_s *c = &S->sctx;
     AsmArgs a[kMaxBatch];
     int slot[kMaxBatch];
-    const int n = (int)js.size();
-    if (n < 1 || n > kMaxBatch) return fail(c, FE_EINVAL, "internal: %d admissions in one pass", n);
+    if (js.size() < 1 || js.size() > (size_t)kMaxBatch)
+        return fail(c, FE_EINVAL, "internal: %d admissions in one pass", (int)js.size());
     for (int o = 0; o < 2; ++o) {
-        for (int i = 0; i < n; ++i) {
-            a[i] = job_asm_args(js[i], o == 0 ? FE_OP_MOMENTUM : FE_OP_POISSON);
-            slot[i] = 2 * js[i]->slot + o;
+        int n = 0;
+        for (Job *j : js) {
+            const AsmArgs x = job_asm_args(j, o == 0 ? FE_OP_MOMENTUM : FE_OP_POISSON);
+            if (x.img_work) {
+                HIPCALL(c, launch_assemble(x, false, S->stream));
+                continue;
+            }
+            a[n] = x;
+            slot[n++] = 2 * j->slot + o;
         }
-        HIPCALL(c, launch_assemble_batch(a, slot, n, S->kargs_d, S->stream));
+        if (n) HIPCALL(c, launch_assemble_batch(a, slot, n, S->kargs_d, S->stream));
     }
     return FE_OK;
 }
