@@ -211,7 +211,7 @@ fe_status fe_assemble(fe_mesh mesh, const fe_fields *fields, fe_precision prec, 
  * terms cancel).  Every CSR block row is written once (no
  * read-back); the sums run in a fixed order, so the result is bitwise
  * reproducible.  The first call on a mesh plans the row-owner assembly on the
- * host and keeps the plan on the device (about 14 bytes per element node).
+ * host and keeps the plan on the device (about 25 bytes per element node).
  * Errors: FE_EINVAL, FE_EBADELEM (element in *info), FE_EBADMESH if a node
  * lies in more than 64 elements, FE_ENOMEM, FE_EDEVICE.
  */

@@ -247,6 +247,26 @@ __device__ __forceinline__ void load_geo(const double *nd, int T, const int (&ln
     }
 }
 
+// A Jacobian's determinant (returned) and inverse.
+__device__ __forceinline__ double invert_jacobian(const double (&J)[3][3], double (&Ji)[3][3])
+{
+    const double c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
+    const double c01 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
+    const double c02 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
+    const double det = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
+    const double id = 1.0 / det;
+    Ji[0][0] = c00 * id;
+    Ji[1][0] = c01 * id;
+    Ji[2][0] = c02 * id;
+    Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
+    Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
+    Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
+    Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
+    Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
+    Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
+    return det;
+}
+
 // Jacobian of the map at Gauss point g, its determinant (returned) and inverse.
 template <class EL>
 __device__ __forceinline__ double jacobian_inverse(int g, const Geo<EL> &GE, double (&Ji)[3][3])
@@ -280,21 +300,7 @@ __device__ __forceinline__ double jacobian_inverse(int g, const Geo<EL> &GE, dou
                 J[i][j] = s;
             }
     }
-    const double c00 = J[1][1] * J[2][2] - J[1][2] * J[2][1];
-    const double c01 = J[1][2] * J[2][0] - J[1][0] * J[2][2];
-    const double c02 = J[1][0] * J[2][1] - J[1][1] * J[2][0];
-    const double det = J[0][0] * c00 + J[0][1] * c01 + J[0][2] * c02;
-    const double id = 1.0 / det;
-    Ji[0][0] = c00 * id;
-    Ji[1][0] = c01 * id;
-    Ji[2][0] = c02 * id;
-    Ji[0][1] = (J[0][2] * J[2][1] - J[0][1] * J[2][2]) * id;
-    Ji[1][1] = (J[0][0] * J[2][2] - J[0][2] * J[2][0]) * id;
-    Ji[2][1] = (J[0][1] * J[2][0] - J[0][0] * J[2][1]) * id;
-    Ji[0][2] = (J[0][1] * J[1][2] - J[0][2] * J[1][1]) * id;
-    Ji[1][2] = (J[0][2] * J[1][0] - J[0][0] * J[1][2]) * id;
-    Ji[2][2] = (J[0][0] * J[1][1] - J[0][1] * J[1][0]) * id;
-    return det;
+    return invert_jacobian(J, Ji);
 }
 
 // One Gauss point of an element-vector pass for rows [A0, A0 + RA), FP64,
@@ -1900,20 +1906,38 @@ void launch_vec(const AsmLaunch &L, const KArgs &k, int op, double *work, int64_
 //   delta_ik (M_ab / dt + C_ab + K_ab [+ E_ab]) [+ T_ab[i][k]],
 //   T_ab[i][k] = sum_g dV mu_g (dN_a / dx_k)(dN_b / dx_i)   (FE_FORM_FULL_STRESS),
 //   E_ab = sum_g dV rho_g (div u)_g N_a N_b                  (FE_FORM_EMAC),
-// with M, C, K those of the scalar momentum operator.  Row-owner form: one
-// lane per (element, row) task, one wavefront per group of whole rows, the
-// rows' block values accumulated in LDS in phase order (a row's tasks in
-// element order) and written to HBM once, contiguously.
+// with M, C, K those of the scalar momentum operator.
+//
+// One lane per (element, row) task, one work-group per group of whole rows,
+// each block row written to HBM once, contiguously.  A group
+//   1. stages its nodes' fields in LDS;
+//   2. some Gauss points at a time: one lane per (element, point) writes what
+//      its tasks share to LDS: grad N_b and s_b = rho dV (N_b / dt + u . grad N_b
+//      [+ (div u) N_b]) of every node b, mu dV and rho dV u / dt; then every
+//      task adds the points to its 8 block columns in registers (grad N_a .
+//      grad N_b is the trace of the full-stress block: one sum more a column);
+//   3. adds the columns into the rows' image in LDS, a row's tasks at once:
+//      the plan orders each task's columns so that they never meet;
+//   4. writes the rows.
+// The order of every sum is fixed.  Bound by LDS (32 doubles a task and point, the
+// items of ~85 elements a group of 256 tasks) and FP64 arithmetic, 41 of 135 us,
+// at two waves a SIMD.  FE_FORM_FULL_STRESS | EMAC on 40^3 HEX08 (134 MB of blocks):
+// 135 us against 206 with each task computing its element's points from global
+// memory, 390 registers, and a row's tasks adding one after the other (8 x 75
+// LDS additions with 8 lanes active).  Whole calls, form 3: 64^3 HEX08 840 -> 512
+// us, 30^3 cubes TET04 218 -> 141, 40^3 PEN06 272 -> 187, 30^3 PYR05 370 -> 235,
+// hybrid 32^3 286 -> 236.  Groups of 64 or 128 tasks share an element's points
+// among fewer (194 and 175 us).
 struct BArgs {
     const double *X;
-    const int32_t *conn;
     const uint8_t *etype;
-    int stride;
     const int32_t *rowptr;
-    const int32_t *task_elem;
-    const uint16_t *task_meta;
+    const uint32_t *task_meta, *task_perm;
     const uint8_t *task_cols;
-    const int4 *wdesc;
+    const int4 *wdesc, *wlists;
+    const int32_t *wave_elem, *wave_node;
+    const uint16_t *wave_ln;
+    int class_end[4];   // of several types: see RowPlan
     int64_t N;
     const double *u, *rho, *mu;
     double inv_dt;
@@ -1922,179 +1946,386 @@ struct BArgs {
     long long *w_bad;
 };
 
-// Element e's block row a: S[b] (the scalar part, times the identity) and
-// T[b][3i + k] (the full-stress coupling), and the right-hand side B[i].
-template <class EL, int FORM>
-__device__ __forceinline__ void block_row(const BArgs &k, int64_t e, int a, double (&S)[8], double (&T)[8][9],
-                                          double (&B)[3], double &mindet)
+// Meshes of several types: eight nodes and points, those that a type lacks zero.
+struct AnyElement {
+    static constexpr int NEN = 8, NG = 8;
+};
+
+// Doubles of one (element, point) item: [8]{grad N_b, s_b}, mu dV, rho dV u / dt,
+// padded so that 16 lanes' 16-byte accesses fall on distinct banks.
+constexpr int kItemNodes = 32, kItem = 38;
+// Doubles of a staged node: x, y, z, u_x, u_y, u_z, rho, mu, padded alike.  Node by
+// node, so that an element's reads take one address a node and constant offsets
+// (field by field, the 64 addresses of a HEX08 element went to scratch).
+constexpr int kBlockNode = 10;
+
+// Shape functions: {d N_b / d xi, N_b} of node b at point g, and the weights, of
+// TET04, PYR05, PEN06 and HEX08; zero where the type lacks them.
+struct ItemTable {
+    double v[4][8][8][4], w[4][8];
+};
+template <class EL> constexpr void fill_items(ItemTable &t, int type)
 {
-    constexpr int NEN = EL::NEN, NG = EL::NG;
-    constexpr bool FULL = (FORM & FE_FORM_FULL_STRESS) != 0, EMAC = (FORM & FE_FORM_EMAC) != 0;
-    const int64_t N = k.N;
-    int c[NEN];
-#pragma unroll
-    for (int b = 0; b < NEN; ++b) c[b] = k.conn[e * k.stride + b];
-    double xl[3 * NEN], ul[3][NEN], rl[NEN], ml[NEN];
-#pragma unroll
-    for (int b = 0; b < NEN; ++b) {
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            xl[i * NEN + b] = k.X[i * N + c[b]];
-            ul[i][b] = k.u[i * N + c[b]];
+    for (int g = 0; g < EL::NG; ++g) {
+        t.w[type][g] = EL::w(g);
+        for (int b = 0; b < EL::NEN; ++b) {
+            for (int j = 0; j < 3; ++j) t.v[type][g][b][j] = EL::dN(g, b, j);
+            t.v[type][g][b][3] = EL::N(g, b);
         }
-        rl[b] = k.rho[c[b]];
-        ml[b] = k.mu[c[b]];
     }
-    int ln[NEN];
+}
+constexpr ItemTable make_items()
+{
+    ItemTable t{};
+    fill_items<Tet>(t, 0);
+    fill_items<Pyr>(t, 1);
+    fill_items<Pen>(t, 2);
+    fill_items<Hex>(t, 3);
+    return t;
+}
+__constant__ ItemTable kItems = make_items();
+__device__ constexpr int item_type(int nen) { return nen == 8 ? 3 : nen - 4; }
+__device__ __forceinline__ int item_points(int type) { return type == 0 ? Tet::NG : type == 2 ? Pen::NG : 8; }
+
+// Node b's reference gradient and shape function at point g.  Several types: read
+// anew from LDS for each use (the opaque 0), not kept in registers.
+template <class EL>
+__device__ __forceinline__ void shape(int g, int b, const double2 *tab, double (&d)[3], double &N)
+{
+    if constexpr (std::is_same<EL, AnyElement>::value) {
+        int again = 0;
+        asm volatile("" : "+v"(again));
+        const double2 t0 = tab[again + 2 * b], t1 = tab[again + 2 * b + 1];
+        d[0] = t0.x;
+        d[1] = t0.y;
+        d[2] = t1.x;
+        N = t1.y;
+    } else {
+        N = RefN<EL>(g, b);
 #pragma unroll
-    for (int b = 0; b < NEN; ++b) ln[b] = b;
-    Geo<EL> GE;
-    load_geo<EL>(xl, NEN, ln, GE);
-#pragma unroll 1
-    for (int g = 0; g < NG; ++g) {
-        double Ji[3][3];
-        const double det = jacobian_inverse<EL>(g, GE, Ji);
-        mindet = fmin(mindet, det);
-        double dN[NEN][3];
-#pragma unroll
-        for (int b = 0; b < NEN; ++b)
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                double s = 0.0;
-#pragma unroll
-                for (int j = 0; j < 3; ++j) s += Ji[j][i] * RefdN<EL>(g, b, j);
-                dN[b][i] = s;
-            }
-        // the task's own row a (a runtime index: read from the tables, not
-        // from the register array)
-        double dNa[3];
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            double s = 0.0;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) s += Ji[j][i] * RefdN<EL>(g, a, j);
-            dNa[i] = s;
-        }
-        const double Na = RefN<EL>(g, a);
-        const double dV = EL::w(g) * det;
-        double rg = 0.0, mg = 0.0, ag[3] = {0.0, 0.0, 0.0}, diva = 0.0;
-#pragma unroll
-        for (int b = 0; b < NEN; ++b) {
-            const double Nb = RefN<EL>(g, b);
-            rg += Nb * rl[b];
-            mg += Nb * ml[b];
-#pragma unroll
-            for (int i = 0; i < 3; ++i) {
-                ag[i] += Nb * ul[i][b];
-                if (EMAC) diva += dN[b][i] * ul[i][b];
-            }
-        }
-        const double w1 = dV * rg, wm = dV * mg, wa = w1 * Na;
-#pragma unroll
-        for (int b = 0; b < NEN; ++b) {
-            const double Nb = RefN<EL>(g, b);
-            const double gg = dNa[0] * dN[b][0] + dNa[1] * dN[b][1] + dNa[2] * dN[b][2];
-            const double agb = ag[0] * dN[b][0] + ag[1] * dN[b][1] + ag[2] * dN[b][2];
-            double sv = wa * (Nb * k.inv_dt + agb) + wm * gg;
-            if (EMAC) sv += wa * diva * Nb;
-            S[b] += sv;
-            if (FULL) {
-#pragma unroll
-                for (int i = 0; i < 3; ++i)
-#pragma unroll
-                    for (int kk = 0; kk < 3; ++kk) T[b][3 * i + kk] += wm * dNa[kk] * dN[b][i];
-            }
-        }
-#pragma unroll
-        for (int i = 0; i < 3; ++i) B[i] += wa * ag[i] * k.inv_dt;
+        for (int j = 0; j < 3; ++j) d[j] = RefdN<EL>(g, b, j);
     }
 }
 
-template <int FORM>
-__global__ void __launch_bounds__(64) k_block(BArgs k)
+// The item of point g of an element whose nodes' fields start at nd + ln[b] in
+// LDS; returns det J.  g is the wave's, so one type's shape functions are scalar
+// operands; of several types they are the lane's, tab in LDS, wg the weight.
+// One node's loads at a time (sched_barrier): the block sums hold most of the
+// registers.
+template <class EL, bool EMAC>
+__device__ __forceinline__ double block_item(int g, const double *nd, const int (&ln)[8], const double2 *tab, double wg,
+                                             double inv_dt, double *out)
 {
-    extern __shared__ double lds[];
-    const int wi = xcd_item(blockIdx.x, gridDim.x);   // this wave's row range
-    const int4 wd = k.wdesc[wi];   // first task, tasks, first row, rows
-    const int lane = threadIdx.x;
+    constexpr int NEN = EL::NEN;
+    [[maybe_unused]] double gu[3][3] = {};
+    double J[3][3] = {}, Ji[3][3], rg = 0.0, mg = 0.0, ag[3] = {0.0, 0.0, 0.0}, div = 0.0;
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) {
+        const double *f = nd + ln[b];
+        double d[3], N;
+        shape<EL>(g, b, tab, d, N);
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const double x = f[i], u = f[3 + i];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                J[i][j] += x * d[j];
+                if (EMAC) gu[i][j] += u * d[j];
+            }
+            ag[i] += N * u;
+        }
+        rg += N * f[6];
+        mg += N * f[7];
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    const double det = invert_jacobian(J, Ji);
+    if constexpr (EMAC)
+#pragma unroll
+        for (int i = 0; i < 3; ++i) div += Ji[0][i] * gu[i][0] + Ji[1][i] * gu[i][1] + Ji[2][i] * gu[i][2];
+    const double dV = wg * det, w1 = dV * rg, c0 = w1 * (inv_dt + div);
+    double c[3];   // w1 u in reference directions
+#pragma unroll
+    for (int j = 0; j < 3; ++j) c[j] = w1 * (ag[0] * Ji[j][0] + ag[1] * Ji[j][1] + ag[2] * Ji[j][2]);
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) {
+        double d[3], N;
+        shape<EL>(g, b, tab, d, N);
+        double2 o0, o1;
+        o0.x = Ji[0][0] * d[0] + Ji[1][0] * d[1] + Ji[2][0] * d[2];
+        o0.y = Ji[0][1] * d[0] + Ji[1][1] * d[1] + Ji[2][1] * d[2];
+        o1.x = Ji[0][2] * d[0] + Ji[1][2] * d[1] + Ji[2][2] * d[2];
+        o1.y = c0 * N + c[0] * d[0] + c[1] * d[1] + c[2] * d[2];
+        *(double2 *)(out + 4 * b) = o0;
+        *(double2 *)(out + 4 * b + 2) = o1;
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    out[kItemNodes] = dV * mg;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) out[kItemNodes + 1 + i] = w1 * ag[i] * inv_dt;
+    return det;
+}
+
+// double2 of a kernel's table in LDS: [types][NG][NS]{d N_b / d xi, N_b}, or one
+// type's [NG][NS] N_b.
+constexpr int item_table(int nen, int ng, bool any) { return any ? 4 * 128 : (nen * ng + 1) / 2; }
+
+template <class EL, int FORM, int NT>
+__device__ __forceinline__ void block_group(const BArgs &k, int wi)
+{
+    constexpr bool FULL = (FORM & FE_FORM_FULL_STRESS) != 0, EMAC = (FORM & FE_FORM_EMAC) != 0;
+    constexpr bool ANY = std::is_same<EL, AnyElement>::value;
+    constexpr int NS = EL::NEN, NG = EL::NG;
+    constexpr int NV = FULL ? 9 : 1;   // values of a block kept in the image
+    extern __shared__ double2 lds2[];
+    double *lds = (double *)lds2;
+    const int4 wd = k.wdesc[wi], wl = k.wlists[wi];
+    const int tid = threadIdx.x, ne = wl.y, T = wl.w;
+    const int64_t N = k.N;
+    double *nd = lds;                       // [T] nodes
+    double2 *tab = (double2 *)(nd + kBlockNode * T);
+    double *items = (double *)(tab + item_table(EL::NEN, EL::NG, ANY));   // [points][ne] items
     const int r0 = wd.z, nr = wd.w;
     const int64_t v0 = k.rowptr[r0];
-    const int nimg = 9 * (int)(k.rowptr[r0 + nr] - v0);
-    double *img = lds;            // [nimg] block values of the wave's rows
-    double *rimg = lds + nimg;    // [3][64] their right-hand sides
-    for (int j = lane; j < nimg; j += 64) img[j] = 0.0;
-#pragma unroll
-    for (int i = 0; i < 3; ++i) rimg[i * 64 + lane] = 0.0;
-
-    const bool live = lane < wd.y;
-    const int64_t t = wd.x + (live ? lane : 0);
-    const int64_t e = k.task_elem[t];
-    const int meta = k.task_meta[t];
-    const int a = meta & 15, ph = live ? (meta >> 4) : -1;
-    const int nen = k.etype ? (int)k.etype[e] : k.stride;
+    const int L = (int)(k.rowptr[r0 + nr] - v0);
+    const int64_t t = wd.x + (tid < wd.y ? tid : 0);
+    uint32_t meta = tid < wd.y ? k.task_meta[t] : kRowNoTask;
+    const bool live = meta != kRowNoTask;
+    const uint32_t perm = live ? k.task_perm[t] : 0x88888888u;
+    const bool row_first = live && (meta & kRowFirstTask) != 0;
+    meta = live ? meta & ~kRowFirstTask : 0u;
     const uint64_t cols = *(const uint64_t *)(k.task_cols + 8 * t);
-    const int row = k.conn[e * k.stride + a];
-    const int ro = (int)(k.rowptr[row] - v0), rl = row - r0;
-    double S[8], T[8][9], B[3] = {0.0, 0.0, 0.0};
+    const int le = meta & 255, a = meta >> 8 & 7, rl = meta >> 11 & 255, round = live ? (int)(meta >> 19) : -1;
+    const int ro = (int)(k.rowptr[r0 + rl] - v0);
+    __shared__ int nround;   // rounds of the group's rows
+    if (tid == 0) nround = 0;
+    // this lane's element in the item passes
+    // (a wave's lanes take one point)
+    const int np = row_points(ne, NT), wpp = (ne + 63) / 64, wv = __builtin_amdgcn_readfirstlane(tid / 64);
+    const int gi = ne > 0 ? wv / wpp : NG, ie = ne > 0 ? (wv - gi * wpp) * 64 + tid % 64 : 0;
+    const bool item = gi < np && ie < ne;
+    const int64_t lel = wl.x + (item ? ie : 0);
+    const int e = ne > 0 ? k.wave_elem[lel] : 0;
+    int ln[8];
+    {
+        const uint4 q = ne > 0 ? *(const uint4 *)(k.wave_ln + 8 * lel) : uint4{0, 0, 0, 0};
+        const uint32_t w[4] = {q.x, q.y, q.z, q.w};
 #pragma unroll
-    for (int b = 0; b < 8; ++b) {
-        S[b] = 0.0;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) T[b][q] = 0.0;
+        for (int b = 0; b < 8; ++b) ln[b] = kBlockNode * (int)(w[b / 2] >> (16 * (b % 2)) & 0xffff);
     }
-    double mindet = __builtin_huge_val();
-    if (live) {
-        switch (nen) {
-        case 8: block_row<Hex, FORM>(k, e, a, S, T, B, mindet); break;
-        case 6: block_row<Pen, FORM>(k, e, a, S, T, B, mindet); break;
-        case 5: block_row<Pyr, FORM>(k, e, a, S, T, B, mindet); break;
-        default: block_row<Tet, FORM>(k, e, a, S, T, B, mindet); break;
+    // type (of several) of the item's and of the task's element
+    [[maybe_unused]] int type = 0, ttype = 0;
+    if constexpr (ANY) {
+        type = ne > 0 ? item_type(k.etype[e]) : 0;
+        ttype = ne > 0 ? item_type(k.etype[k.wave_elem[wl.x + le]]) : 0;
+    }
+    if constexpr (ANY)
+        for (int q = tid; q < item_table(NS, NG, ANY); q += NT) tab[q] = ((const double2 *)&kItems.v[0][0][0][0])[q];
+    else
+        for (int q = tid; q < NG * NS; q += NT) ((double *)tab)[q] = kItems.v[item_type(NS)][q / NS][q % NS][3];
+    for (int q = tid; q < T; q += NT) {
+        const int g = k.wave_node[wl.z + q];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            nd[kBlockNode * q + i] = k.X[i * N + g];
+            nd[kBlockNode * q + 3 + i] = k.u[i * N + g];
         }
+        nd[kBlockNode * q + 6] = k.rho[g];
+        nd[kBlockNode * q + 7] = k.mu[g];
     }
     __syncthreads();
-    // phases: a row's tasks one after the other in element order; the tasks
-    // of one phase hold distinct rows, so no two lanes add to one address
-    int nph = ph + 1;
+
+    // FULL: A without s_b, which S sums; else S sums both
+    double A[NS][9], S[NS], B[3] = {0.0, 0.0, 0.0};
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) nph = max(nph, __shfl_xor(nph, o));
-    for (int p = 0; p < nph; ++p) {
-        if (ph == p) {
+    for (int s = 0; s < NS; ++s) {
+        S[s] = 0.0;
 #pragma unroll
-            for (int b = 0; b < 8; ++b) {
-                if (b < nen) {
-                    double *dst = img + 9 * (ro + (int)((cols >> (8 * b)) & 0xff));
+        for (int q = 0; q < 9; ++q) A[s][q] = 0.0;
+    }
+    int at[NS];   // slot s's node in an item
+#pragma unroll
+    for (int s = 0; s < NS; ++s) at[s] = 4 * (int)(perm >> (4 * s) & 7);
+    double mindet = __builtin_huge_val();
+#pragma unroll 1
+    for (int g0 = 0; g0 < NG; g0 += np) {
+        const int g = g0 + gi;
+        if (item && g < NG) {
+            double *out = items + kItem * (gi * ne + ie);
+            if constexpr (ANY) {
+                // a point that the type lacks adds zero
+                if (g >= item_points(type))
+                    for (int q = 0; q < kItemNodes + 4; ++q) out[q] = 0.0;
+                else
+                    mindet = fmin(mindet, block_item<EL, EMAC>(g, nd, ln, tab + 128 * type + 16 * g,
+                                                                      kItems.w[type][g], k.inv_dt, out));
+            } else {
+                mindet = fmin(mindet, block_item<EL, EMAC>(g, nd, ln, tab, EL::w(g), k.inv_dt, out));
+            }
+        }
+        __syncthreads();
+#pragma unroll 1
+        for (int p = 0; p < np && g0 + p < NG; ++p) {
+            const double *it = items + kItem * (p * ne + le);
+            const double wm = it[kItemNodes],
+                         Na = ANY ? tab[128 * ttype + 2 * (NS * (g0 + p) + a) + 1].y
+                                  : ((const double *)tab)[NS * (g0 + p) + a];
+            double da[3];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                da[i] = wm * it[4 * a + i];
+                B[i] += Na * it[kItemNodes + 1 + i];
+            }
+#pragma unroll
+            for (int s = 0; s < NS; ++s) {
+                const double2 x = *(const double2 *)(it + at[s]), y = *(const double2 *)(it + at[s] + 2);
+                const double d[3] = {x.x, x.y, y.x};
+                S[s] += Na * y.y;
+                if constexpr (FULL) {
 #pragma unroll
                     for (int i = 0; i < 3; ++i)
 #pragma unroll
-                        for (int kk = 0; kk < 3; ++kk)
-                            lds_add(dst + 3 * i + kk, (i == kk ? S[b] : 0.0) + T[b][3 * i + kk]);
+                        for (int kk = 0; kk < 3; ++kk) A[s][3 * i + kk] += da[kk] * d[i];
+                } else {
+                    S[s] += da[0] * d[0] + da[1] * d[1] + da[2] * d[2];
                 }
+                if (s % 2) __builtin_amdgcn_sched_barrier(0);   // two slots' loads in flight, as above
             }
+        }
+        __syncthreads();
+    }
+
+    // the rows' image, over the fields and items
+    double *img = lds;            // [NV L] block values of the group's rows
+    double *rt = lds + NV * L;    // [3][NT] the tasks' right-hand sides
+    int *rows = (int *)(rt + 3 * NT), *first = rows + NT;   // [NT] the tasks' rows; the rows' first tasks
+    for (int j = tid; j < NV * L; j += NT) img[j] = 0.0;
 #pragma unroll
-            for (int i = 0; i < 3; ++i) lds_add(&rimg[i * 64 + rl], B[i]);
+    for (int i = 0; i < 3; ++i) rt[i * NT + tid] = B[i];
+    rows[tid] = live ? rl : -1;
+    first[tid] = NT;
+    if constexpr (FULL) {
+#pragma unroll
+        for (int s = 0; s < NS; ++s) {
+            S[s] += A[s][0] + A[s][4] + A[s][8];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) A[s][4 * i] += S[s];
         }
     }
+    if (round >= 0) atomicMax(&nround, round + 1);
     __syncthreads();
-    // each value and right-hand side entry written once, contiguously
-    double *vout = k.values + 9 * v0;
-    for (int j = lane; j < nimg; j += 64) vout[j] = img[j];
-    if (lane < nr) {
+    if (row_first) first[rl] = tid;
+    for (int p = 0; p < nround; ++p) {
+        if (round == p) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) k.rhs[i * k.N + r0 + lane] = rimg[i * 64 + lane];
+            for (int s = 0; s < NS; ++s) {
+                if ((perm >> (4 * s) & 8) == 0) {
+                    double *dst = img + NV * (ro + (int)((cols >> (8 * s)) & 0xff));
+#pragma unroll
+                    for (int q = 0; q < NV; ++q) lds_add(dst + q, FULL ? A[s][q] : S[s]);
+                }
+            }
+        }
+        __syncthreads();   // a row's rounds may lie in two wavefronts
     }
-    // status: the wave's smallest det J and first element with det J <= 0
-    double md = live ? mindet : __builtin_huge_val();
-    long long bad = (live && !(mindet > 0.0)) ? (long long)e : (long long)0x7fffffffffffffffLL;
+    double *vout = k.values + 9 * v0;
+    for (int j = tid; j < 9 * L; j += NT) {
+        if constexpr (FULL) vout[j] = img[j];
+        else vout[j] = (j % 9) % 4 == 0 ? img[j / 9] : 0.0;
+    }
+    if (tid < nr) {
+        double b[3] = {0.0, 0.0, 0.0};
+        for (int j = first[tid]; j < NT && (rows[j] == tid || rows[j] < 0); ++j)
+            if (rows[j] == tid) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i) b[i] += rt[i * NT + j];
+            }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) k.rhs[i * N + r0 + tid] = b[i];
+    }
+    // status: the group's smallest det J and first element with det J <= 0
+    constexpr long long kNone = 0x7fffffffffffffffLL;
+    __shared__ double sd[NT / 64];
+    __shared__ long long sb[NT / 64];
+    double md = mindet;
+    long long bad = !(mindet > 0.0) ? (long long)e : kNone;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         md = fmin(md, __shfl_xor(md, o));
         const long long ob = __shfl_xor(bad, o);
         bad = ob < bad ? ob : bad;
     }
-    if (lane == 0) {
-        k.w_mindet[wi] = md;
-        k.w_bad[wi] = bad == 0x7fffffffffffffffLL ? -1 : bad;
+    if (tid % 64 == 0) {
+        sd[tid / 64] = md;
+        sb[tid / 64] = bad;
     }
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) {
+            md = fmin(md, sd[w]);
+            bad = sb[w] < bad ? sb[w] : bad;
+        }
+        k.w_mindet[wi] = md;
+        k.w_bad[wi] = bad == kNone ? -1 : bad;
+    }
+}
+
+template <class EL, int FORM, int NT>
+__global__ void __launch_bounds__(NT, 2) k_block(BArgs k)
+{
+    block_group<EL, FORM, NT>(k, xcd_item(blockIdx.x, gridDim.x));
+}
+
+// Several types: the groups of several types, the longest, first, then those of
+// one type, type after type; one launch, since with one each the chip waits for
+// the last groups of every type (hybrid 10^3: 91 us against 51).
+template <int FORM, int NT>
+__global__ void __launch_bounds__(NT, 2) k_block_types(BArgs k)
+{
+    // each type's groups over all XCDs
+    const int b = blockIdx.x;
+    int c = 0, first = 0;
+    while (c < 4 && b >= k.class_end[c]) first = k.class_end[c++];
+    const int wi = first + xcd_item(b - first, (c < 4 ? k.class_end[c] : (int)gridDim.x) - first);
+    switch (c) {
+    case 0: block_group<AnyElement, FORM, NT>(k, wi); break;
+    case 1: block_group<Hex, FORM, NT>(k, wi); break;
+    case 2: block_group<Pyr, FORM, NT>(k, wi); break;
+    case 3: block_group<Pen, FORM, NT>(k, wi); break;
+    default: block_group<Tet, FORM, NT>(k, wi); break;
+    }
+}
+
+template <class EL, int NT>
+void launch_block_lanes(const BArgs &k, const DevRowPlan &r, int form, hipStream_t s)
+{
+    constexpr bool ANY = std::is_same<EL, AnyElement>::value;
+    const size_t nv = (form & FE_FORM_FULL_STRESS) ? 9 : 1;
+    const size_t work = (size_t)(kBlockNode * r.max_nodes + 2 * item_table(EL::NEN, EL::NG, ANY) + kItem * r.max_items);
+    const size_t image = (size_t)(nv * (r.max_img / 9) + 4 * NT);
+    const size_t lds = std::max(work, image) * sizeof(double);
+    const dim3 grid((unsigned)r.n_waves), blk(NT);
+    if constexpr (ANY) {
+        switch (form) {
+        case 0: hipLaunchKernelGGL((k_block_types<0, NT>), grid, blk, lds, s, k); break;
+        case 1: hipLaunchKernelGGL((k_block_types<1, NT>), grid, blk, lds, s, k); break;
+        case 2: hipLaunchKernelGGL((k_block_types<2, NT>), grid, blk, lds, s, k); break;
+        default: hipLaunchKernelGGL((k_block_types<3, NT>), grid, blk, lds, s, k); break;
+        }
+    } else {
+        switch (form) {
+        case 0: hipLaunchKernelGGL((k_block<EL, 0, NT>), grid, blk, lds, s, k); break;
+        case 1: hipLaunchKernelGGL((k_block<EL, 1, NT>), grid, blk, lds, s, k); break;
+        case 2: hipLaunchKernelGGL((k_block<EL, 2, NT>), grid, blk, lds, s, k); break;
+        default: hipLaunchKernelGGL((k_block<EL, 3, NT>), grid, blk, lds, s, k); break;
+        }
+    }
+}
+template <class EL>
+void launch_block(const BArgs &k, const DevRowPlan &r, int form, hipStream_t s)
+{
+    if (r.lanes == kRowTasks) launch_block_lanes<EL, kRowTasks>(k, r, form, s);
+    else launch_block_lanes<EL, kRowTasksSmall>(k, r, form, s);
 }
 
 // ---- boundary assembly: equilibrium wall model ---------------------------
@@ -2477,14 +2708,16 @@ hipError_t launch_assemble_block(const DevMesh &m, const DevRowPlan &r, int form
     if (r.n_waves <= 0) return hipErrorInvalidValue;
     BArgs k{};
     k.X = m.X;
-    k.conn = r.conn;
     k.etype = r.etype;
-    k.stride = r.stride;
     k.rowptr = m.rowptr;
-    k.task_elem = r.task_elem;
     k.task_meta = r.task_meta;
+    k.task_perm = r.task_perm;
     k.task_cols = r.task_cols;
     k.wdesc = r.wdesc;
+    k.wlists = r.wlists;
+    k.wave_elem = r.wave_elem;
+    k.wave_node = r.wave_node;
+    k.wave_ln = r.wave_ln;
     k.N = m.N;
     k.u = u;
     k.rho = rho;
@@ -2494,15 +2727,16 @@ hipError_t launch_assemble_block(const DevMesh &m, const DevRowPlan &r, int form
     k.rhs = rhs;
     k.w_mindet = r.w_mindet;
     k.w_bad = r.w_bad;
-    const size_t lds = (size_t)(r.max_img + 3 * 64) * sizeof(double);
-    const dim3 grid((unsigned)r.n_waves), blk(64);
-    switch (form) {
-    case 0: hipLaunchKernelGGL(k_block<0>, grid, blk, lds, s, k); break;
-    case 1: hipLaunchKernelGGL(k_block<1>, grid, blk, lds, s, k); break;
-    case 2: hipLaunchKernelGGL(k_block<2>, grid, blk, lds, s, k); break;
-    default: hipLaunchKernelGGL(k_block<3>, grid, blk, lds, s, k); break;
+    if (r.lanes != kRowTasks && r.lanes != kRowTasksSmall) return hipErrorInvalidValue;
+    for (int c = 0; c < 4; ++c) k.class_end[c] = r.class_end[c];
+    switch (r.nen) {
+    case 8: launch_block<Hex>(k, r, form, s); break;
+    case 6: launch_block<Pen>(k, r, form, s); break;
+    case 5: launch_block<Pyr>(k, r, form, s); break;
+    case 4: launch_block<Tet>(k, r, form, s); break;
+    default: launch_block<AnyElement>(k, r, form, s); break;
     }
-    hipError_t e = hipGetLastError();
+    const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_asm_status, dim3(1), dim3(kStatusThreads), 0, s,
                        StatusArgs{r.w_mindet, r.w_bad, r.n_waves, status});

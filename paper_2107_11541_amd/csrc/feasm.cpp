@@ -1280,7 +1280,11 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     P.n_tasks = R.n_tasks;
     P.n_waves = (int64_t)R.wdesc.size();
     P.max_img = R.max_img;
-    P.stride = m->stride_m;
+    P.max_items = R.max_items;
+    P.max_nodes = R.max_nodes;
+    P.lanes = R.lanes;
+    P.nen = R.nen;
+    std::copy(R.class_end, R.class_end + 4, P.class_end);
     fe_status s = FE_OK;
     auto up = [&](void **dst, const void *src, size_t bytes) {
         if (s != FE_OK) return;
@@ -1290,16 +1294,20 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
             if (e != hipSuccess) s = fail(c, FE_EDEVICE, "block plan upload: %s", hipGetErrorString(e));
         }
     };
-    up((void **)&P.conn, m->conn_m.data(), m->conn_m.size() * sizeof(int32_t));
-    if (et) up((void **)&P.etype, et, m->etype_m.size());
-    up((void **)&P.task_elem, R.task_elem.data(), R.task_elem.size() * sizeof(int32_t));
-    up((void **)&P.task_meta, R.task_meta.data(), R.task_meta.size() * sizeof(uint16_t));
+    if (P.nen == 0) up((void **)&P.etype, et, m->etype_m.size());
+    up((void **)&P.task_meta, R.task_meta.data(), R.task_meta.size() * sizeof(uint32_t));
+    up((void **)&P.task_perm, R.task_perm.data(), R.task_perm.size() * sizeof(uint32_t));
     up((void **)&P.task_cols, R.task_cols.data(), R.task_cols.size());
     up((void **)&P.wdesc, R.wdesc.data(), R.wdesc.size() * sizeof(RowWave));
+    up((void **)&P.wlists, R.wlists.data(), R.wlists.size() * sizeof(RowLists));
+    up((void **)&P.wave_elem, R.wave_elem.data(), R.wave_elem.size() * sizeof(int32_t));
+    up((void **)&P.wave_node, R.wave_node.data(), R.wave_node.size() * sizeof(int32_t));
+    up((void **)&P.wave_ln, R.wave_ln.data(), R.wave_ln.size() * sizeof(uint16_t));
     up((void **)&P.w_mindet, nullptr, (size_t)P.n_waves * sizeof(double));
     up((void **)&P.w_bad, nullptr, (size_t)P.n_waves * sizeof(long long));
     if (s != FE_OK) {
-        void *ps[] = {P.conn, P.etype, P.task_elem, P.task_meta, P.task_cols, P.wdesc, P.w_mindet, P.w_bad};
+        void *ps[] = {P.etype, P.task_meta, P.task_perm, P.task_cols, P.wdesc, P.wlists, P.wave_elem, P.wave_node,
+                      P.wave_ln, P.w_mindet, P.w_bad};
         for (void *q : ps) mesh_free_ptr(m, q);
         return s;
     }

@@ -186,16 +186,18 @@ hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const
 // Device copy of the row-owner plan of the 3x3-block momentum operator
 // (plan.h RowPlan), built on the first block assembly of a mesh.
 struct DevRowPlan {
-    int64_t n_tasks = 0, n_waves = 0, max_img = 0;
-    int stride = 0;
-    int32_t *conn = nullptr;       // [E][stride] mesh numbering
-    uint8_t *etype = nullptr;      // [E] node counts, or null (every element has stride nodes)
-    int32_t *task_elem = nullptr;
-    uint16_t *task_meta = nullptr;
-    uint8_t *task_cols = nullptr;  // [T][8]
-    int4 *wdesc = nullptr;         // {first task, tasks, first row, rows}
-    double *w_mindet = nullptr;    // [waves]
-    long long *w_bad = nullptr;    // [waves]
+    int64_t n_tasks = 0, n_waves = 0, max_img = 0, max_items = 0, max_nodes = 0;
+    int lanes = 0, nen = 0;          // of a group; nodes per element (0: several types)
+    int32_t class_end[4] = {};       // see RowPlan
+    uint8_t *etype = nullptr;        // [E] node counts, or null (one type)
+    uint32_t *task_meta = nullptr, *task_perm = nullptr;
+    uint8_t *task_cols = nullptr;    // [T][8]
+    int4 *wdesc = nullptr;           // {first task, tasks, first row, rows}
+    int4 *wlists = nullptr;          // {first element, elements, first node, nodes}
+    int32_t *wave_elem = nullptr, *wave_node = nullptr;
+    uint16_t *wave_ln = nullptr;     // [listed elements][8]
+    double *w_mindet = nullptr;      // [groups]
+    long long *w_bad = nullptr;      // [groups]
 };
 // values[nnz][3][3], rhs[3][N]: the momentum operator with the form bits'
 // terms (FE_FORM_FULL_STRESS, FE_FORM_EMAC) as 3x3 blocks; status word as

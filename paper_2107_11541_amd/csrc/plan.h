@@ -21,6 +21,9 @@
 
 #include <cstdint>
 #include <functional>
+#include <memory>
+#include <new>
+#include <utility>
 #include <string>
 #include <vector>
 
@@ -121,22 +124,60 @@ void parallel_chunks_w(int64_t n, const std::function<void(int64_t, int)> &f);
 
 // Row-owner plan of the 3x3-block momentum operator (rowplan.cpp): tasks =
 // (element, row) pairs ordered by row, then element; whole rows packed into
-// waves of at most kRowTasksMax tasks and kRowImageDoubles block values.
-constexpr int kRowTasksMax = 64;
-constexpr int kRowImageDoubles = 3072;
+// groups of at most `lanes` lanes and kRowImage(lanes) block values.  A group's
+// distinct elements and nodes are listed once.  A task adds its element's
+// nodes in the order of its slots: in one (round, slot) the tasks of a row hold
+// distinct columns, and lie in one wavefront (lanes between are idle).
+constexpr int kRowElemsMax = 64;   // elements at a node
+constexpr int kRowTasks = 256, kRowTasksSmall = 64;   // lanes
+// Meshes of fewer tasks, which 256-lane groups would leave CUs without one, take
+// the small groups: HEX08 10^3 (8 k tasks) 42 us against 48, TET04 10^3 34 against
+// 43; just below and above the line HEX08 20^3 (64 k) 49, 21^3 (74 k) 56 against 69
+// with one wave per 64 tasks as before.
+constexpr int64_t kRowSmallMesh = 1 << 16;
+constexpr int row_image(int lanes) { return lanes == kRowTasks ? 8192 : 3072; }
 struct RowWave {
     int32_t first_task, n_tasks, first_row, n_rows;
 };
+struct RowLists {
+    int32_t first_elem, n_elems, first_node, n_nodes;
+};
+constexpr uint32_t kRowNoTask = 0x7fffffffu, kRowFirstTask = 0x80000000u;   // task_meta: idle lane; a row's first
+// Gauss points whose element data a group of ne elements holds at a time.  A
+// wave's lanes take one point; at most 200 (element, point) pairs, while that is
+// a point at least, so that two groups of 256 lanes share a CU's LDS.
+constexpr int row_points(int ne, int lanes)
+{
+    if (ne < 1) return 1;
+    const int by_waves = lanes / 64 / ((ne + 63) / 64), by_lds = 200 / ne;
+    return by_lds < 1 || by_waves < 1 ? 1 : by_lds < by_waves ? by_lds : by_waves;
+}
+// Left unset by resize, so that the threads that fill a large array also fault its pages in.
+template <class T> struct UnsetAllocator : std::allocator<T> {
+    template <class U> struct rebind {
+        using other = UnsetAllocator<U>;
+    };
+    template <class U> void construct(U *) {}
+    template <class U, class... A> void construct(U *p, A &&...a) { ::new ((void *)p) U(std::forward<A>(a)...); }
+};
+template <class T> using UnsetVector = std::vector<T, UnsetAllocator<T>>;
+
 struct RowPlan {
-    int64_t n_tasks = 0, max_img = 0;
-    std::vector<int32_t> task_elem;    // [T] element (mesh order)
-    std::vector<uint16_t> task_meta;   // [T] local row a (bits 0-3) | phase in the row (bits 4-15)
-    std::vector<uint8_t> task_cols;    // [T][8] position of the element's node b in the row
-    std::vector<RowWave> wdesc;        // [waves]
+    int64_t n_tasks = 0, max_img = 0, max_items = 0, max_nodes = 0;
+    int lanes = 0;                     // of a group
+    int nen = 0;                       // nodes per element, 0 for several types: then the groups of several,
+    int32_t class_end[4] = {};         // HEX08, PYR05 and PEN06 alone, each to its end, before TET04's
+    UnsetVector<uint32_t> task_meta;   // [T] group's element (bits 0-7) | local row a (8-10) | group's row (11-18) | round (19-30)
+    UnsetVector<uint32_t> task_perm;   // [T] slot s adds node (perm >> 4 s) & 15, 8 = none
+    UnsetVector<uint8_t> task_cols;    // [T][8] slot s: its node's position in the row
+    std::vector<RowWave> wdesc;        // [groups]
+    std::vector<RowLists> wlists;      // [groups] places in the next three
+    UnsetVector<int32_t> wave_elem, wave_node;
+    UnsetVector<uint16_t> wave_ln;     // [listed elements][8] the group's node of each element node
 };
 // conn [E][stride] and rowptr/colidx in mesh numbering; etype [E] node
 // counts or NULL (every element has stride nodes).  0 or an fe_status code
-// with a message in err (FE_EBADMESH: a node in more than kRowTasksMax
+// with a message in err (FE_EBADMESH: a node in more than kRowElemsMax
 // elements).
 int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const int32_t *conn,
                    const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err);

@@ -6,11 +6,14 @@
 //   * a task is one (element, row) pair: element e's contribution to the
 //     block row of one of its nodes;
 //   * tasks are ordered by row (mesh numbering), and within a row by element;
-//     the phase of a task is its position in its row's list;
-//   * consecutive rows are packed into wavefronts: whole rows only, at most
-//     64 tasks and kRowImageDoubles of block values per wave, so each wave
-//     owns its rows outright (no other wave adds to them) and holds their
-//     image in LDS.
+//   * consecutive rows are packed into groups: whole rows only, at most
+//     256 lanes (small meshes: 64) and row_image block values, so each group owns
+//     its rows outright (no other adds to them) and holds their image in LDS;
+//     its distinct elements (~90 to 256 tasks of HEX08; 35 to 64) and nodes
+//     are listed, so that their data is computed and staged once;
+//   * a row's tasks add in rounds of up to 8, all at once: the order in which
+//     each adds its element's nodes is an edge colouring of the bipartite
+//     graph (tasks, columns), so no two add to one column in one step.
 #include <algorithm>
 #include <cstring>
 #include <string>
@@ -24,23 +27,102 @@ namespace feasm {
 
 namespace {
 
-template <class F>
-void chunks(int64_t n, F f)
-{
-    const int nt = n < 4096 ? 1 : host_threads();
-    if (nt <= 1) {
-        f((int64_t)0, n);
-        return;
+// The slots and rounds of one row's tasks.  Tasks are taken in order, up to D
+// to a round while no column occurs more than D times in it; D colours (slots)
+// then suffice (Koenig's theorem), found edge by edge, exchanging two colours
+// along a path where an edge's ends share no free one.
+class RowSlots {
+  public:
+    // D: the most nodes of the row's elements; cols_of [nt][8]: the columns (positions in the row) of each task's nen nodes
+    void row(int D, int nt, const uint8_t *cols_of, const uint8_t *nen, uint32_t *perm, uint8_t *cols, uint8_t *round)
+    {
+        D_ = D;
+        int t0 = 0, r = 0;
+        while (t0 < nt) {
+            int m = 0;
+            for (; t0 + m < nt && m < D_; ++m) {
+                const uint8_t *c = cols_of + 8 * (t0 + m);
+                int b = 0;
+                for (; b < nen[t0 + m]; ++b)
+                    if (++mult_[c[b]] > D_) break;
+                if (b < nen[t0 + m]) {
+                    for (; b >= 0; --b) --mult_[c[b]];
+                    break;
+                }
+            }
+            colour(m, cols_of + 8 * t0, nen + t0);
+            for (int i = 0; i < m; ++i) {
+                const uint8_t *c = cols_of + 8 * (t0 + i);
+                perm[t0 + i] = 0;
+                for (int q = 0; q < 8; ++q) {
+                    const int b = q < D_ ? at_task_[i][q] : -1;
+                    perm[t0 + i] |= (uint32_t)(b < 0 ? 8 : b) << (4 * q);
+                    cols[8 * (t0 + i) + q] = b < 0 ? 0 : c[b];
+                }
+                round[t0 + i] = (uint8_t)r;
+                for (int b = 0; b < nen[t0 + i]; ++b) mult_[c[b]] = used_[c[b]] = 0;
+            }
+            t0 += m;
+            ++r;
+        }
     }
-    std::vector<std::thread> th;
-    const int64_t chunk = (n + nt - 1) / nt;
-    for (int t = 0; t < nt; ++t) {
-        const int64_t lo = t * chunk, hi = std::min(n, lo + chunk);
-        if (lo >= hi) break;
-        th.emplace_back([=, &f] { f(lo, hi); });
+
+  private:
+    void colour(int m, const uint8_t *cols_of, const uint8_t *nen)
+    {
+        const unsigned all = (1u << D_) - 1;
+        for (int i = 0; i < m; ++i) {
+            unsigned free_t = all;
+            for (int q = 0; q < 8; ++q) at_task_[i][q] = -1;
+            for (int b = 0; b < nen[i]; ++b) {
+                const int x = cols_of[8 * i + b];
+                const unsigned both = free_t & ~used_[x];
+                int q;
+                if (both) {
+                    q = __builtin_ctz(both);
+                } else {
+                    q = __builtin_ctz(free_t);
+                    exchange(x, q, __builtin_ctz(all & ~used_[x]), cols_of);
+                }
+                free_t &= ~(1u << q);
+                used_[x] |= (uint8_t)(1u << q);
+                at_task_[i][q] = (int8_t)b;
+                at_col_[x][q] = (int8_t)i;
+            }
+        }
     }
-    for (auto &x : th) x.join();
-}
+    // Exchanges colours al and be along the path from column x along al (be is
+    // free at x; the path does not reach the task that al is free at).
+    void exchange(int x, int al, int be, const uint8_t *cols_of)
+    {
+        struct Edge {
+            int task, node, col, q;
+        } path[16];
+        int n = 0;
+        for (int y = x; used_[y] >> al & 1;) {
+            const int j = at_col_[y][al];
+            path[n++] = {j, at_task_[j][al], y, al};
+            const int nb = at_task_[j][be];
+            if (nb < 0) break;
+            y = cols_of[8 * j + nb];
+            path[n++] = {j, nb, y, be};
+        }
+        for (int k = 0; k < n; ++k) {
+            at_task_[path[k].task][path[k].q] = -1;
+            used_[path[k].col] &= (uint8_t)~(1u << path[k].q);
+        }
+        for (int k = 0; k < n; ++k) {
+            const int q = path[k].q == al ? be : al;
+            at_task_[path[k].task][q] = (int8_t)path[k].node;
+            at_col_[path[k].col][q] = (int8_t)path[k].task;
+            used_[path[k].col] |= (uint8_t)(1u << q);
+        }
+    }
+    int D_ = 8;
+    int8_t at_task_[8][8], at_col_[256][8];   // a task's node, a column's task in each slot
+    uint8_t used_[256] = {};                  // a column's slots (which at_col_ holds)
+    uint8_t mult_[256] = {};
+};
 
 }  // namespace
 
@@ -54,65 +136,197 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
     for (int64_t e = 0; e < E; ++e)
         for (int a = 0; a < nen_of(e); ++a) ++inc_ptr[conn[e * stride + a] + 1];
     for (int64_t i = 0; i < N; ++i) {
-        if (inc_ptr[i + 1] > kRowTasksMax) {
+        if (inc_ptr[i + 1] > kRowElemsMax) {
             err = "node " + std::to_string(i) + " (mesh numbering) lies in " + std::to_string(inc_ptr[i + 1]) +
                   " elements; the block operator's row-owner assembly takes at most " +
-                  std::to_string(kRowTasksMax);
+                  std::to_string(kRowElemsMax);
             return FE_EBADMESH;
         }
         inc_ptr[i + 1] += inc_ptr[i];
     }
     const int64_t T = inc_ptr[N];
-    std::vector<int32_t> fill(inc_ptr.begin(), inc_ptr.end() - 1);
-    R.task_elem.resize(T);
-    R.task_meta.resize(T);
-    for (int64_t e = 0; e < E; ++e)
-        for (int a = 0; a < nen_of(e); ++a) {
-            const int32_t i = conn[e * stride + a];
-            const int32_t t = fill[i]++;
-            R.task_elem[t] = (int32_t)e;
-            R.task_meta[t] = (uint16_t)(a | ((t - inc_ptr[i]) << 4));   // local row | phase
+    R.lanes = T < kRowSmallMesh ? kRowTasksSmall : kRowTasks;
+    UnsetVector<int32_t> task_elem(T);
+    UnsetVector<uint8_t> task_row(T);   // local row a
+    {
+        std::vector<int32_t> fill(inc_ptr.begin(), inc_ptr.end() - 1);
+        for (int64_t e = 0; e < E; ++e)
+            for (int a = 0; a < nen_of(e); ++a) {
+                const int32_t t = fill[conn[e * stride + a]]++;
+                task_elem[t] = (int32_t)e;
+                task_row[t] = (uint8_t)a;
+            }
+    }
+    // the rows' slots, in tasks order
+    UnsetVector<uint32_t> perm(T);
+    UnsetVector<uint8_t> cols((size_t)T * 8), round(T);
+    constexpr int64_t kRows = 4096;   // per chunk
+    const int64_t CR = (N + kRows - 1) / kRows;
+    std::vector<uint8_t> missing(CR, 0);
+    std::vector<std::vector<int32_t>> place(parallel_workers(CR));   // per worker, [N]: a column's position
+    parallel_chunks_w(CR, [&](int64_t c, int wk) {
+        RowSlots slots;
+        uint8_t of[kRowElemsMax * 8], nen[kRowElemsMax];
+        std::vector<int32_t> &at = place[wk];
+        at.resize(N);
+        for (int64_t row = c * kRows; row < std::min(N, (c + 1) * kRows); ++row) {
+            const int32_t *c0 = colidx + rowptr[row];
+            const int32_t len = std::min(rowptr[row + 1] - rowptr[row], 256);
+            for (int32_t p = 0; p < len; ++p) at[c0[p]] = p;
+            const int32_t t0 = inc_ptr[row];
+            const int nt = inc_ptr[row + 1] - t0;
+            int D = 1;
+            for (int t = 0; t < nt; ++t) {
+                const int64_t e = task_elem[t0 + t];
+                nen[t] = (uint8_t)nen_of(e);
+                D = std::max<int>(D, nen[t]);
+                for (int b = 0; b < nen[t]; ++b) {
+                    const int32_t j = conn[e * stride + b], p = at[j];
+                    if (p < 0 || p >= len || c0[p] != j) missing[c] = 1;
+                    of[8 * t + b] = (uint8_t)p;
+                }
+            }
+            if (nt > 0 && !missing[c]) slots.row(D, nt, of, nen, &perm[t0], &cols[(size_t)t0 * 8], &round[t0]);
         }
-    // columns of each task's element in its row
-    R.task_cols.assign((size_t)T * 8, 0);
-    bool missing = false;
-    chunks(N, [&](int64_t lo, int64_t hi) {
-        for (int64_t i = lo; i < hi; ++i) {
-            const int32_t *c0 = colidx + rowptr[i], *c1 = colidx + rowptr[i + 1];
-            for (int32_t t = inc_ptr[i]; t < inc_ptr[i + 1]; ++t) {
-                const int64_t e = R.task_elem[t];
-                for (int b = 0; b < nen_of(e); ++b) {
-                    const int32_t j = conn[e * stride + b];
-                    const int32_t *p = std::lower_bound(c0, c1, j);
-                    if (p == c1 || *p != j) {
-                        missing = true;
-                        continue;
-                    }
-                    R.task_cols[(size_t)t * 8 + b] = (uint8_t)(p - c0);
+    });
+    for (int64_t c = 0; c < CR; ++c)
+        if (missing[c]) {
+            err = "the CSR pattern lacks an element's node pair";
+            return FE_EBADMESH;
+        }
+    // Lane of each of a row's tasks in its group, from lane p on (at [0] of its
+    // tasks' lanes if given); the next free lane.  A round's tasks lie in one
+    // wavefront, so that they add in step.
+    const auto lanes_of = [&](int64_t row, int p, int *lane) {
+        for (int32_t t = inc_ptr[row]; t < inc_ptr[row + 1];) {
+            int m = 1;
+            while (t + m < inc_ptr[row + 1] && round[t + m] == round[t]) ++m;
+            if (p % 64 + m > 64) p = (p + 63) / 64 * 64;
+            for (int q = 0; q < m; ++q, ++p)
+                if (lane) *lane++ = p;
+            t += m;
+        }
+        return p;
+    };
+    // whole rows into groups
+    int64_t r = 0;
+    int32_t tasks = 0;
+    while (r < N) {
+        const int64_t r0 = r;
+        int p = 0;
+        while (r < N) {
+            const int next = lanes_of(r, p, nullptr);
+            const int64_t img = 9 * (int64_t)(rowptr[r + 1] - rowptr[r0]);
+            if (r > r0 && (next > R.lanes || img > row_image(R.lanes) || r - r0 >= R.lanes)) break;
+            p = next;
+            ++r;
+        }
+        R.wdesc.push_back({tasks, p, (int32_t)r0, (int32_t)(r - r0)});
+        tasks += p;
+        R.max_img = std::max<int64_t>(R.max_img, 9 * (int64_t)(rowptr[r] - rowptr[r0]));
+    }
+    R.n_tasks = tasks;
+    R.nen = !etype ? stride : std::all_of(etype, etype + E, [&](uint8_t n) { return n == etype[0]; }) ? etype[0] : 0;
+    if (R.nen == 0) {
+        std::vector<uint8_t> cls(R.wdesc.size());
+        for (size_t w = 0; w < R.wdesc.size(); ++w) {
+            const RowWave &q = R.wdesc[w];
+            const int32_t t0 = inc_ptr[q.first_row], t1 = inc_ptr[q.first_row + q.n_rows];
+            cls[w] = t0 < t1 ? etype[task_elem[t0]] : 0;
+            for (int32_t t = t0; t < t1; ++t)
+                if (etype[task_elem[t]] != cls[w]) cls[w] = 0;
+        }
+        std::vector<RowWave> by_row = std::move(R.wdesc);
+        R.wdesc.clear();
+        const int order[5] = {0, 8, 5, 6, 4};
+        for (int c = 0; c < 5; ++c) {
+            for (size_t w = 0; w < by_row.size(); ++w)
+                if (cls[w] == order[c]) R.wdesc.push_back(by_row[w]);
+            if (c < 4) R.class_end[c] = (int32_t)R.wdesc.size();
+        }
+    }
+    // each group's elements and nodes, in the order of their first use by its
+    // tasks: counted, then listed
+    const int64_t W = (int64_t)R.wdesc.size();
+    R.task_meta.resize(tasks);
+    R.task_perm.resize(tasks);
+    R.task_cols.resize((size_t)tasks * 8);
+    R.wlists.resize(W);
+    constexpr int64_t kGroups = 64;   // per chunk
+    const int64_t C = (W + kGroups - 1) / kGroups;
+    // per worker: an element's and a node's place in its group's list, which
+    // counts if the list holds it there; the lists
+    struct Lists {
+        std::vector<int32_t> elem_at, node_at, elems, nodes;
+        std::vector<uint16_t> ln;
+    };
+    std::vector<Lists> work(parallel_workers(C));
+    const auto listed = [](std::vector<int32_t> &list, std::vector<int32_t> &at, int32_t x) {
+        const size_t p = (size_t)(uint32_t)at[x];
+        if (p < list.size() && list[p] == x) return (int32_t)p;
+        list.push_back(x);
+        return at[x] = (int32_t)list.size() - 1;
+    };
+    const auto make = [&](const RowWave &q, Lists &l) {
+        l.elem_at.resize(E);
+        l.node_at.resize(N);
+        l.elems.clear();
+        l.nodes.clear();
+        l.ln.clear();
+        for (int32_t t = inc_ptr[q.first_row]; t < inc_ptr[q.first_row + q.n_rows]; ++t)
+            (void)listed(l.elems, l.elem_at, task_elem[t]);
+        for (const int32_t e : l.elems) {
+            const int32_t *ce = conn + (int64_t)e * stride;
+            const int n = nen_of(e);
+            for (int b = 0; b < 8; ++b) l.ln.push_back(b < n ? (uint16_t)listed(l.nodes, l.node_at, ce[b]) : (uint16_t)0);
+        }
+    };
+    parallel_chunks_w(C, [&](int64_t c, int wk) {
+        for (int64_t w = c * kGroups; w < std::min(W, (c + 1) * kGroups); ++w) {
+            make(R.wdesc[w], work[wk]);
+            R.wlists[w] = {0, (int32_t)work[wk].elems.size(), 0, (int32_t)work[wk].nodes.size()};
+        }
+    });
+    int32_t ne = 0, nn = 0;
+    for (RowLists &l : R.wlists) {
+        l.first_elem = ne;
+        l.first_node = nn;
+        ne += l.n_elems;
+        nn += l.n_nodes;
+        R.max_items = std::max<int64_t>(R.max_items, (int64_t)l.n_elems * row_points(l.n_elems, R.lanes));
+        R.max_nodes = std::max<int64_t>(R.max_nodes, l.n_nodes);
+    }
+    R.wave_elem.resize(ne);
+    R.wave_node.resize(nn);
+    R.wave_ln.resize((size_t)ne * 8);
+    parallel_chunks_w(C, [&](int64_t c, int wk) {
+        Lists &l = work[wk];
+        int lane[kRowElemsMax];
+        for (int64_t w = c * kGroups; w < std::min(W, (c + 1) * kGroups); ++w) {
+            const RowWave &q = R.wdesc[w];
+            make(q, l);
+            std::copy(l.elems.begin(), l.elems.end(), R.wave_elem.begin() + R.wlists[w].first_elem);
+            std::copy(l.nodes.begin(), l.nodes.end(), R.wave_node.begin() + R.wlists[w].first_node);
+            std::copy(l.ln.begin(), l.ln.end(), R.wave_ln.begin() + (size_t)R.wlists[w].first_elem * 8);
+            const size_t t0 = (size_t)q.first_task;
+            std::fill_n(R.task_meta.begin() + t0, q.n_tasks, kRowNoTask);
+            std::fill_n(R.task_perm.begin() + t0, q.n_tasks, 0x88888888u);
+            std::fill_n(R.task_cols.begin() + t0 * 8, (size_t)q.n_tasks * 8, (uint8_t)0);
+            int p = 0;
+            for (int i = 0; i < q.n_rows; ++i) {
+                const int64_t row = q.first_row + i;
+                p = lanes_of(row, p, lane);
+                for (int32_t t = inc_ptr[row]; t < inc_ptr[row + 1]; ++t) {
+                    const int k = t - inc_ptr[row];
+                    const size_t d = t0 + lane[k];
+                    R.task_meta[d] = (uint32_t)l.elem_at[task_elem[t]] | (uint32_t)task_row[t] << 8 | (uint32_t)i << 11 |
+                                     (uint32_t)round[t] << 19 | (k == 0 ? kRowFirstTask : 0u);
+                    R.task_perm[d] = perm[t];
+                    memcpy(&R.task_cols[d * 8], &cols[(size_t)t * 8], 8);
                 }
             }
         }
     });
-    if (missing) {
-        err = "the CSR pattern lacks an element's node pair";
-        return FE_EBADMESH;
-    }
-    // whole rows into waves
-    int64_t r = 0;
-    while (r < N) {
-        const int64_t r0 = r;
-        int tasks = 0;
-        while (r < N) {
-            const int nt = inc_ptr[r + 1] - inc_ptr[r];
-            const int64_t img = 9 * (int64_t)(rowptr[r + 1] - rowptr[r0]);
-            if (r > r0 && (tasks + nt > kRowTasksMax || img > kRowImageDoubles || r - r0 >= kRowTasksMax)) break;
-            tasks += nt;
-            ++r;
-        }
-        R.wdesc.push_back({inc_ptr[r0], tasks, (int32_t)r0, (int32_t)(r - r0)});
-        R.max_img = std::max<int64_t>(R.max_img, 9 * (int64_t)(rowptr[r] - rowptr[r0]));
-    }
-    R.n_tasks = T;
     return FE_OK;
 }
 
