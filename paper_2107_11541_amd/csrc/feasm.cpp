@@ -847,21 +847,21 @@ static fe_status ensure_resident(fe_mesh_s *m)
     const size_t hw = ((size_t)N.G * kResidentHalo + N.G) * sizeof(int32_t);
     const size_t sw = kResidentSlots * sizeof(unsigned long long);
     void *p = nullptr;
-    fe_status s = mesh_alloc(m, &p, ow + sw + hw + sizeof(ResidentOut));
+    fe_status s = mesh_alloc(m, &p, ow + sw + hw + 2 * sizeof(uint32_t));
     if (s == FE_ENOMEM) {
         Y = N;
         return FE_OK;
     }
     if (s != FE_OK) return s;
     N.slots = (unsigned long long *)p;
-    N.out = (ResidentOut *)(N.slots + kResidentSlots);
-    N.plan.off = (uint32_t *)(N.out + 1);
+    int32_t *const flag = (int32_t *)(N.slots + kResidentSlots);   // a halo does not fit
+    N.plan.off = (uint32_t *)(flag + 2);
     N.plan.hcol = (int32_t *)((char *)N.plan.off + ow);
     N.plan.nh = N.plan.hcol + (size_t)N.G * kResidentHalo;
     int32_t bad = 0;
-    HIPCALL(c, hipMemsetAsync(N.out, 0, sizeof(ResidentOut), c->stream));
-    HIPCALL(c, launch_resident_plan(d, N.plan, N.G, N.R, &N.out->abandoned, c->stream));
-    HIPCALL(c, hipMemcpyAsync(c->host, &N.out->abandoned, sizeof bad, hipMemcpyDeviceToHost, c->stream));
+    HIPCALL(c, hipMemsetAsync(flag, 0, sizeof bad, c->stream));
+    HIPCALL(c, launch_resident_plan(d, N.plan, N.G, N.R, flag, c->stream));
+    HIPCALL(c, hipMemcpyAsync(c->host, flag, sizeof bad, hipMemcpyDeviceToHost, c->stream));
     if ((s = sync(c)) != FE_OK) return s;
     memcpy(&bad, c->host, sizeof bad);
     if (bad) {
@@ -886,7 +886,8 @@ static bool resident_fits(const fe_mesh_s *m)
 // Runs the one-launch form (resident.hip) of a PCG solve of `values` in
 // precision T (resident_fits).  ran: it did, o holds its outcome; else the
 // general form has to run, on the x that was passed in (o.abandoned == 0:
-// the pair check behind `bad` failed).  Synchronises the stream.
+// the pair check behind `bad` failed).  launch_resident_init is queued already.
+// Synchronises the stream.
 template <class T>
 static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, const T *b, T *x, double rtol,
                               int max_iter, bool x_zero, const int32_t *bad, ResidentOut &o, bool &ran)
@@ -896,15 +897,15 @@ static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, con
     const fe_mesh_s::ResidentState &Y = m->resident;
     constexpr bool f64 = sizeof(T) == 8;
     T *z = f64 ? (T *)w.z : (T *)w.z32, *x0 = f64 ? (T *)w.q : (T *)w.q32;
-    ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, Y.out, bad, rtol, kResidentLimit,
-                   (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
+    // the outcome goes to pinned memory
+    ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, (ResidentOut *)c->host, bad, rtol,
+                   kResidentLimit, (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
     {
         std::lock_guard<std::mutex> lk(g_resident_mu[c->device]);
         {
             ProfScope ps(c, 0);
             HIPCALL(c, launch_resident<T>(A, d.max_row, Y.G, c->stream));
         }
-        HIPCALL(c, hipMemcpyAsync(c->host, Y.out, sizeof o, hipMemcpyDeviceToHost, c->stream));
         const fe_status s = sync(c);
         if (s != FE_OK) return s;
     }
@@ -929,7 +930,8 @@ static fe_status select_sym(fe_mesh_s *m, CGWork &w, const double *values)
     fe_status s = ensure_sym(m);
     if (s != FE_OK || m->sym.state != 1) return s;
     fe_mesh_s::SymState &Y = m->sym;
-    HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, const_cast<double *>(Y.map.vals), Y.bad, c->stream));
+    HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, const_cast<double *>(Y.map.vals), Y.bad, true,
+                               c->stream));
     int32_t *hf = (int32_t *)c->host;
     HIPCALL(c, hipMemcpyAsync(hf, Y.bad, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream));
     if ((s = sync(c)) != FE_OK) return s;
@@ -956,7 +958,8 @@ fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *
         if (m->sym.state == 1 && (s = ensure_resident(m)) != FE_OK) return s;
         if (m->sym.state == 1 && resident_fits<double>(m)) {
             fe_mesh_s::SymState &Y = m->sym;
-            HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, nullptr, Y.bad, c->stream));
+            HIPCALL(c, launch_resident_init(m->resident.slots, (ResidentOut *)c->host, Y.bad, c->stream));
+            HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, nullptr, Y.bad, false, c->stream));
             ResidentOut o;
             bool ran;
             s = resident_pcg<double>(m, w, values, rhs, x, rtol, max_iter, false, Y.bad, o, ran);
@@ -1001,8 +1004,7 @@ fe_status pcg_finish(fe_mesh_s *m, CGWork &w, const double *values, const double
 {
     fe_ctx_s *c = m->ctx;
     if (!finished) {
-        HIPCALL(c, residual_f64(m->dm, values, rhs, x, w.d64, w.part, c->scratch + 2048, c->stream));
-        HIPCALL(c, hipMemcpyAsync(c->host, c->scratch + 2048, 2 * sizeof(double), hipMemcpyDeviceToHost, c->stream));
+        HIPCALL(c, residual_f64(m->dm, values, rhs, x, w.d64, w.part, c->host, c->stream));
         fe_status s = sync(c);
         if (s != FE_OK) return s;
         inf.true_rel_residual = c->host[1] > 0 ? std::sqrt(c->host[0] / c->host[1]) : std::sqrt(c->host[0]);
@@ -1080,7 +1082,7 @@ fe_status fe_ctx_create(int device, void *hip_stream, fe_ctx *out)
     c->device = device;
     c->cus = cus;
     c->stream = (hipStream_t)hip_stream;
-    if (hipMalloc((void **)&c->scratch, (2048 + 64) * sizeof(double)) != hipSuccess ||
+    if (hipMalloc((void **)&c->scratch, 2048 * sizeof(double)) != hipSuccess ||
         hipHostMalloc((void **)&c->host, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         if (c->scratch) (void)hipFree(c->scratch);
         delete c;
@@ -1362,8 +1364,7 @@ fe_status fe_dot(fe_ctx c, int64_t n, const double *x, const double *y, double *
         *out = 0.0;
         return FE_OK;
     }
-    HIPCALL(c, launch_dot(n, x, y, c->scratch, c->scratch + 2048, c->stream));
-    HIPCALL(c, hipMemcpyAsync(c->host, c->scratch + 2048, sizeof(double), hipMemcpyDeviceToHost, c->stream));
+    HIPCALL(c, launch_dot(n, x, y, c->scratch, c->host, c->stream));
     fe_status s = sync(c);
     if (s != FE_OK) return s;
     *out = c->host[0];
@@ -1406,9 +1407,7 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
         double rel = 0.0;
         result = FE_ENOCONV;
         for (outer = 0; outer < 64; ++outer) {
-            HIPCALL(c, residual_f64(d, values, rhs, x, w.d64, w.part, c->scratch + 2048, c->stream));
-            HIPCALL(c, hipMemcpyAsync(c->host, c->scratch + 2048, 2 * sizeof(double), hipMemcpyDeviceToHost,
-                                      c->stream));
+            HIPCALL(c, residual_f64(d, values, rhs, x, w.d64, w.part, c->host, c->stream));
             if ((s = sync(c)) != FE_OK) return s;
             const double rr = c->host[0], bb = c->host[1];
             rel = bb > 0 ? std::sqrt(rr / bb) : std::sqrt(rr);
@@ -1429,6 +1428,7 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
             ResidentOut o;
             bool ran = false;
             if (resident_fits<float>(m)) {
+                HIPCALL(c, launch_resident_init(m->resident.slots, (ResidentOut *)c->host, nullptr, c->stream));
                 s = resident_pcg<float>(m, w, values, w.r32, w.x32, tol_in, max_iter - used, true, nullptr, o, ran);
                 if (s != FE_OK) return s;
             }

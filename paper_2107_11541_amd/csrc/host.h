@@ -56,7 +56,7 @@ struct fe_ctx_s {
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;   // private stream that PCG graphs are recorded on (never run on)
     std::string err;
-    double *scratch = nullptr;    // 2048 partials + 64 results
+    double *scratch = nullptr;    // 2048 partials
     double *host = nullptr;       // pinned read-back area (64 doubles)
     bool profiling = false;
     std::vector<fe_mesh_s *> meshes;   // live meshes, freed by fe_ctx_destroy
@@ -106,7 +106,6 @@ struct fe_mesh_s {
         int state = 0, G = 0, R = 0;
         feasm::ResidentPlan plan;
         unsigned long long *slots = nullptr;   // the groups' meeting slots
-        feasm::ResidentOut *out = nullptr;
     } resident;
 };
 

@@ -123,9 +123,9 @@ struct SymSpmv {
 // map (mstart: its per-row mirror-run starts) and sets *bad to 1 when a
 // mirror entry a_ij differs from the stored a_ji by more than 2^-40
 // max(|a_ij|, |a_ji|, sqrt|a_ii a_jj|) (or either is not finite).  *bad is
-// set to 0 first.  packed null: the check alone.
+// set to 0 first with reset, else it has to be.  packed null: the check alone.
 hipError_t launch_sym_pack(const DevMesh &m, const SymSpmv &map, const uint8_t *mstart, const double *vals,
-                           double *packed, int32_t *bad, hipStream_t s);
+                           double *packed, int32_t *bad, bool reset, hipStream_t s);
 
 // Wall faces of a mesh (boundary assembly of the wall model): face node
 // counts and connectivity (mesh numbering, unused slots repeat slot 0), the
@@ -229,7 +229,7 @@ struct ResidentArgs {
     const void *b;               // T [N]
     void *x, *z, *x0;            // T [N]: solution (in: first guess unless x_zero), exchange, copy of the guess
     unsigned long long *slots;   // kResidentSlots
-    ResidentOut *out;
+    ResidentOut *out;            // device or pinned
     const int32_t *bad;          // nothing runs when *bad != 0 (null: no such word)
     double rtol;
     unsigned long long limit;    // longest wait, in 10 ns
@@ -245,6 +245,8 @@ bool resident_shape(int elem_bytes, int64_t N, int max_row, int cus, int &G, int
 size_t resident_off_words(int G, int R, int max_row);
 // Fills the plan; *bad = 1 when a group's halo does not fit.
 hipError_t launch_resident_plan(const DevMesh &m, const ResidentPlan &P, int G, int R, int32_t *bad, hipStream_t s);
+// Before each solve: empties the slots and *out, sets *bad (or null) to 0.
+hipError_t launch_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad, hipStream_t s);
 template <class T>
 hipError_t launch_resident(const ResidentArgs &A, int max_row, int G, hipStream_t s);
 
@@ -279,6 +281,7 @@ int stream_blocks(int64_t n);
 // as are co-resident (context creation).
 hipError_t init_spmv_grid(int device);
 hipError_t launch_spmv(const DevMesh &m, const double *vals, const double *x, double *y, hipStream_t s);
+// out: device or pinned.
 hipError_t launch_dot(int64_t n, const double *x, const double *y, double *part, double *out, hipStream_t s);
 hipError_t launch_axpy(int64_t n, double a, const double *x, double *y, hipStream_t s);
 hipError_t launch_dirichlet(const DevMesh &m, double *vals, double *rhs, const double *g, hipStream_t s);

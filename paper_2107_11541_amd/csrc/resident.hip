@@ -509,10 +509,13 @@ __global__ void __launch_bounds__(kRB, 1) k_resident(ResidentArgs A)
     }
 }
 
-__global__ void __launch_bounds__(256) k_resident_init(unsigned long long *slots, ResidentOut *out)
+__global__ void __launch_bounds__(256) k_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad)
 {
     for (int q = threadIdx.x; q < (int)(3 * kMeetBuffer); q += 256) slots[q] = kEmpty;
-    if (threadIdx.x == 0) *out = ResidentOut{};
+    if (threadIdx.x == 0) {
+        *out = ResidentOut{};
+        if (bad) *bad = 0;
+    }
 }
 
 template <class T, int W, int S, int L = 0>
@@ -574,10 +577,15 @@ hipError_t launch_resident_plan(const DevMesh &m, const ResidentPlan &P, int G, 
     return hipGetLastError();
 }
 
+hipError_t launch_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_resident_init, dim3(1), dim3(256), 0, s, slots, out, bad);
+    return hipGetLastError();
+}
+
 template <class T>
 hipError_t launch_resident(const ResidentArgs &A, int max_row, int G, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_resident_init, dim3(1), dim3(256), 0, s, A.slots, A.out);
     const int S = (A.R + kRB - 1) / kRB;
     if (G < 1 || G > kResidentMaxGroups || (int64_t)G * A.R < A.N || (int64_t)(G - 1) * A.R >= A.N ||
         S > resident_rows(sizeof(T), resident_width(max_row)))
