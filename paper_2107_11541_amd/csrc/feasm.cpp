@@ -553,14 +553,18 @@ fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, do
     a.status_out = host_status(c);
     a.img_work = m->img_work;
     const int passes = f->op == FE_OP_SCALAR ? f->n_scalars : 1;
-    for (int k = 0; k < passes; ++k) {
+    const bool several = f->op == FE_OP_SCALAR && prec == FE_MIXED && d.own_G > 0;
+    for (int k = 0; k < passes; k += a.scalars) {
+        const int left = passes - k;
+        a.scalars = !several ? 1 : left == 4 ? 2 : std::min(left, kOwnScalars);
         a.values = values + (int64_t)k * d.nnz;
         a.rhs = rhs + (int64_t)k * d.N;
         if (f->op == FE_OP_SCALAR) {
             a.Y = f->Y + (int64_t)k * d.N;
             a.Dk = f->D[k];
+            for (int c = 1; c < a.scalars; ++c) a.D_next[c - 1] = f->D[k + c];
         }
-        a.want_status = k == passes - 1;   // every pass has the same elements, so the same word
+        a.want_status = left == a.scalars;   // every pass has the same elements, so the same word
         HIPCALL(c, launch_assemble(a, prec == FE_MIXED, stream));
     }
     return FE_OK;

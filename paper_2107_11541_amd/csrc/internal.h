@@ -155,6 +155,9 @@ struct AsmStatus {
 // Systems (serving slots) one batched launch may cover.
 constexpr int kMaxBatch = 32;
 
+// Scalars that one pass of the owner assembly may take (mixed precision).
+constexpr int kOwnScalars = 3;
+
 struct AsmArgs {
     const DevMesh *m;
     int op;                  // fe_operator, or kOpResidual / kOpGradient / kOpDivergence
@@ -168,6 +171,8 @@ struct AsmArgs {
     double *vec_work = nullptr;   // element-vector passes: block sums [4][vec_T] (null: colour by colour)
     double *img_work = nullptr;   // matrix passes by blocks: row images [img_total], sums [3][vec_T] (null: as above)
     AsmStatus *status_out = nullptr;   // where the reduced word goes instead of *status (null: *status)
+    int scalars = 1;         // owner groups, mixed FE_OP_SCALAR: scalars of this pass, Y, values, rhs one after the other
+    double D_next[kOwnScalars - 1] = {};   // diffusivities of those after the first (Dk)
     bool want_status = true;  // false: leave the status word as it is (where it takes a launch)
 };
 

@@ -58,3 +58,25 @@ def test_matrix_blocks_at_their_edges(fe_ctx, kind, n, renumber):
                 assert torch.equal(v, again[0]) and torch.equal(b, again[1])
     for mesh in meshes:
         mesh.close()
+
+
+@pytest.mark.parametrize("count", [2, 3, 4, 5])
+@pytest.mark.parametrize("n,renumber", [(1, True), (5, False), (9, True)])
+def test_scalars_of_one_pass_equal_each_alone(fe_ctx, n, renumber, count):
+    """Mixed HEX08 scalars share passes of up to three: bitwise what each gives alone."""
+    import torch
+    import paper_2107_11541_amd as fe
+    c = meshgen.make_case(n, 8, 0.12, case_id=800 + n, shuffle=True, n_scalars=5)
+    mesh = make_mesh(fe_ctx, c, renumber=renumber)
+    f = mesh_fields(mesh, c)
+
+    def run(a, b):
+        v, r, info = fe.assemble(mesh, fe.SCALAR, c.dt, f["u"], f["rho"], Y=f["Y"][a:b].contiguous(), D=c.D[a:b],
+                                 precision=fe.MIXED)
+        return v, r, info["min_detJ"]
+
+    V, B, det = run(0, count)
+    for k in range(count):
+        v, b, d = run(k, k + 1)
+        assert torch.equal(V[k], v[0]) and torch.equal(B[k], b[0]) and d == det
+    mesh.close()
