@@ -73,7 +73,6 @@ struct fe_mesh_s {
     feasm::AsmStatus *status = nullptr;  // + per-block scratch
     feasm::CGWork cg;
     double *vec_work = nullptr;          // element-vector passes: [4][vec_T] block sums
-    bool vec_off = false;                // no room for vec_work: the passes run colour by colour
     double *img_work = nullptr;          // matrix assembly by blocks: row images, then [3][vec_T] right-hand sides
     double *step_work = nullptr;         // explicit step: u0 [3][N], residual + mass [4][N], f [N], g [3][N]
     feasm::DevWall wall;                 // wall faces of the wall model (F = 0: none)
