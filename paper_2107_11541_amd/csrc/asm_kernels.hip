@@ -105,6 +105,8 @@ struct Tet {
 struct Pen {
     static constexpr int NEN = 6, NG = 6;
     static constexpr bool kRolled = true, kSparse = false;
+    // dN(g, a, j) is zero at every point
+    __host__ __device__ static constexpr bool zero(int a, int j) { return j < 2 && a % 3 != 0 && a % 3 != j + 1; }
     static constexpr double kG = 0.57735026918962576451;
     __host__ __device__ static constexpr double px(int g) { return g % 3 == 1 ? 2.0 / 3.0 : 1.0 / 6.0; }
     __host__ __device__ static constexpr double py(int g) { return g % 3 == 2 ? 2.0 / 3.0 : 1.0 / 6.0; }
@@ -207,6 +209,20 @@ template <> __device__ inline double RefdN<Pen>(int g, int a, int j) { return kP
 template <> __device__ inline double RefN<Pyr>(int g, int a) { return kPyrTab.N[g][a]; }
 template <> __device__ inline double RefdN<Pyr>(int g, int a, int j) { return kPyrTab.dN[g][a][j]; }
 
+// Whether d = dN(g, a, j) counts (a compile-time answer: its table may be read
+// at run time).
+template <class EL> __device__ constexpr bool has_dN(int a, int j, double d)
+{
+    if constexpr (EL::NEN == 6) return !EL::zero(a, j);
+    else return !EL::kSparse || d != 0.0;
+}
+
+// FP64 Poisson matrices of the types with an element on one lane: the entries
+// on and above the diagonal are summed, the others are theirs (PEN06: 63 of 108
+// products a point; with the zeros above 57^3 takes 113 us instead of 126).
+template <class EL, int OP, class Q, int RA>
+constexpr bool kSymmetric = OP == OP_POI && RA == EL::NEN && sizeof(Q) == 8;
+
 // One Gauss point for rows [a0, a0 + RA) of the elemental matrix.
 // Geometry in FP64 (from the LDS-staged nodal data), products in Q.
 //   MOM/SCA: A_ab += N_a s_b + wk grad N_a . grad N_b,
@@ -295,7 +311,7 @@ __device__ __forceinline__ double jacobian_inverse(int g, const Geo<EL> &GE, dou
 #pragma unroll
                 for (int a = 0; a < NEN; ++a) {
                     const double d = RefdN<EL>(g, a, j);
-                    if (!EL::kSparse || d != 0.0) s += geo[a][i] * d;
+                    if (has_dN<EL>(a, j, d)) s += geo[a][i] * d;
                 }
                 J[i][j] = s;
             }
@@ -422,7 +438,7 @@ __device__ __forceinline__ void gauss_point(int g, const Geo<EL> &GE, const doub
 #pragma unroll
             for (int j = 0; j < 3; ++j) {
                 const double d = RefdN<EL>(g, a, j);
-                if (!EL::kSparse || d != 0.0) s += Ji[j][i] * d;
+                if (has_dN<EL>(a, j, d)) s += Ji[j][i] * d;
             }
             dN[a][i] = Q(s);
         }
@@ -450,7 +466,8 @@ __device__ __forceinline__ void gauss_point(int g, const Geo<EL> &GE, const doub
                 const int a = A0 + r;
                 const Q G0 = qdV * dN[a][0], G1 = qdV * dN[a][1], G2 = qdV * dN[a][2];
 #pragma unroll
-                for (int b = 0; b < NEN; ++b) A[r][b] += G0 * dN[b][0] + G1 * dN[b][1] + G2 * dN[b][2];
+                for (int b = kSymmetric<EL, OP, Q, RA> ? r : 0; b < NEN; ++b)
+                    A[r][b] += G0 * dN[b][0] + G1 * dN[b][1] + G2 * dN[b][2];
                 B[0][r] += qi * (G0 * f0 + G1 * f1 + G2 * f2);
             }
         } else {
@@ -507,6 +524,12 @@ __device__ __forceinline__ void gauss_loop(const Geo<EL> &GE, const double *nd, 
 #pragma unroll
         for (int g = 0; g < NG; ++g)
             gauss_point<EL, OP, Q, RA, A0, FT>(g, GE, nd, nf, T, ln, A, B, mindet, inv_dt, Dk, form);
+    }
+    if constexpr (kSymmetric<EL, OP, Q, RA>) {
+#pragma unroll
+        for (int r = 1; r < RA; ++r)
+#pragma unroll
+            for (int b = 0; b < r; ++b) A[r][b] = A[b][r];
     }
 }
 
@@ -1412,7 +1435,7 @@ __device__ __forceinline__ void reduce_status(const StatusArgs &st)
 // 4 us, of 11) as in the gather, with 8-12 blocks to a CU; PEN06 half by FP64
 // arithmetic.  Whole calls, owner groups (each element computed by every group
 // that owns one of its rows: 1.6x) -> blocks: TET04 45^3 cubes momentum 110 -> 79
-// us, 90^3 695 -> 498; PEN06 57^3 momentum 183 -> 134, Poisson 150 -> 121; PYR05
+// us, 90^3 695 -> 498; PEN06 57^3 momentum 183 -> 134, Poisson 150 -> 104; PYR05
 // 40^3 184 -> 120.  Coloured blocks (40 launches) -> blocks: hybrid 64^3 momentum
 // 816 -> 218, 20^3 680 -> 76.  A HEX08 mesh stays with owner
 // groups: k_part takes 0.42 ns per HEX08 element (65 k of the hybrid mesh) before
