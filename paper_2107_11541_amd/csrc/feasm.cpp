@@ -1262,6 +1262,7 @@ fe_status fe_assemble(fe_mesh m, const fe_fields *f, fe_precision prec, double *
 }
 
 // Builds and uploads the row-owner plan of the block operator (first use).
+constexpr size_t kPackedPlan = (size_t)4 << 20;
 static fe_status ensure_rowplan(fe_mesh_s *m)
 {
     fe_ctx_s *c = m->ctx;
@@ -1307,14 +1308,19 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     char *base = nullptr;
     fe_status s = mesh_alloc(m, (void **)&base, total);
     if (s != FE_OK) return s;
+    // small plans in one copy (each takes ~20 us)
+    std::vector<char> packed(total <= kPackedPlan ? total : 0);
     size_t at = 0;
     hipError_t e = hipSuccess;
     for (const Part &q : parts) {
         *q.dst = base + at;
+        if (q.src && q.bytes && e == hipSuccess) {
+            if (packed.empty()) e = hipMemcpyAsync(*q.dst, q.src, q.bytes, hipMemcpyHostToDevice, c->stream);
+            else memcpy(packed.data() + at, q.src, q.bytes);
+        }
         at += DevArena::round(q.bytes);
-        if (q.src && q.bytes && e == hipSuccess)
-            e = hipMemcpyAsync(*q.dst, q.src, q.bytes, hipMemcpyHostToDevice, c->stream);
     }
+    if (!packed.empty()) e = hipMemcpyAsync(base, packed.data(), total, hipMemcpyHostToDevice, c->stream);
     const hipError_t e2 = hipStreamSynchronize(c->stream);   // the host arrays end here
     if (e == hipSuccess) e = e2;
     if (e != hipSuccess) {

@@ -160,7 +160,7 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
     // the rows' slots, in tasks order
     UnsetVector<uint32_t> perm(T);
     UnsetVector<uint8_t> cols((size_t)T * 8), round(T);
-    constexpr int64_t kRows = 4096;   // per chunk
+    constexpr int64_t kRows = 512;   // per chunk
     const int64_t CR = (N + kRows - 1) / kRows;
     std::vector<uint8_t> missing(CR, 0);
     std::vector<std::vector<int32_t>> place(parallel_workers(CR));   // per worker, [N]: a column's position
@@ -252,7 +252,7 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
     R.task_perm.resize(tasks);
     R.task_cols.resize((size_t)tasks * 8);
     R.wlists.resize(W);
-    constexpr int64_t kGroups = 64;   // per chunk
+    constexpr int64_t kGroups = 32;   // per chunk
     const int64_t C = (W + kGroups - 1) / kGroups;
     // per worker: an element's and a node's place in its group's list, which
     // counts if the list holds it there; the lists
