@@ -61,8 +61,9 @@ typedef enum { FE_OP_MOMENTUM = 0, FE_OP_SCALAR = 1, FE_OP_POISSON = 2 } fe_oper
                                  * element blocks (the serving runtime's form) instead of the owner groups
                                  * (HEX08) or the blocks with a gather (the other types; always that of
                                  * hybrid meshes); they agree to rounding order */
-#define FE_UPLOAD_GENERAL_SPMV 4u   /* fe_cg_solve runs the general SpMV on this mesh and never builds
-                                     * the symmetric one's map: for a mesh solved once or a few times,
+#define FE_UPLOAD_GENERAL_SPMV 4u   /* fe_cg_solve runs the general SpMV on this mesh, in either precision,
+                                     * and builds neither the symmetric one's map nor the plan of the
+                                     * one-launch solves: for a mesh solved once or a few times,
                                      * where building the map on the host (~3 ns per nonzero on 8
                                      * threads) costs more than the solves save (see fe_cg_solve) */
 
