@@ -489,6 +489,14 @@ void fe_serve_destroy(fe_server server);
 fe_status fe_ctx_profile(fe_ctx ctx, int enable);
 fe_status fe_ctx_profile_read(fe_ctx ctx, int slot, int64_t *launches, double *total_ms);
 
+/* ---- test hooks -----------------------------------------------------------------
+ * How long the groups of this mesh's one-launch solves (fe_cg_solve) wait for
+ * each other before they give the solve up, in microseconds: at any meeting,
+ * and at the last one of an FP64 solve (both 50,000 otherwise; 0 to 1e6).
+ * stopped: the next solves find themselves given up when they start.  A solve
+ * given up runs again in the general form. */
+fe_status fe_test_one_launch(fe_mesh mesh, double wait_us, double last_wait_us, int32_t stopped);
+
 /* ---- host-only preprocessing (no device needed; used to test the planner) --- */
 
 typedef struct fe_plan_s *fe_plan;

@@ -819,10 +819,6 @@ static fe_status ensure_sym(fe_mesh_s *m)
 // run one after the other per device (a solve is synchronous to its caller).
 constexpr int kResidentDevices = 64;
 static std::mutex g_resident_mu[kResidentDevices];
-// Longest wait of such a solve's groups for each other, in 10 ns: 50 ms, far
-// beyond any iteration (~10 us), short for a caller that then runs the solve
-// in the general form.
-constexpr unsigned long long kResidentLimit = 5000000;
 
 // The plan of the mesh's one-launch solves, built on first use.  A pattern
 // that does not fit, or a device without room for the plan, leaves state -1.
@@ -849,8 +845,9 @@ static fe_status ensure_resident(fe_mesh_s *m)
     }
     if (s != FE_OK) return s;
     N.slots = (unsigned long long *)p;
-    int32_t *const flag = (int32_t *)(N.slots + kResidentSlots);   // a halo does not fit
-    N.plan.off = (uint32_t *)(flag + 2);
+    N.stop = (uint32_t *)(N.slots + kResidentSlots);
+    int32_t *const flag = (int32_t *)N.stop + 1;   // a halo does not fit
+    N.plan.off = N.stop + 2;
     N.plan.hcol = (int32_t *)((char *)N.plan.off + ow);
     N.plan.nh = N.plan.hcol + (size_t)N.G * kResidentHalo;
     int32_t bad = 0;
@@ -878,10 +875,17 @@ static bool resident_fits(const fe_mesh_s *m)
     return m->resident.state == 1 && resident_shape(sizeof(T), m->dm.N, m->dm.max_row, m->ctx->cus, G, R);
 }
 
+// Empties the words of the next one-launch solve (and *bad, or null).
+static hipError_t resident_init(fe_mesh_s *m, int32_t *bad)
+{
+    return launch_resident_init(m->resident.slots, m->resident.stop, m->waits.stopped, (ResidentOut *)m->ctx->host, bad,
+                                m->ctx->stream);
+}
+
 // Runs the one-launch form (resident.hip) of a PCG solve of `values` in
 // precision T (resident_fits).  ran: it did, o holds its outcome; else the
 // general form has to run, on the x that was passed in (o.abandoned == 0:
-// the pair check behind `bad` failed).  launch_resident_init is queued already.
+// the pair check behind `bad` failed).  resident_init is queued already.
 // Synchronises the stream.
 template <class T>
 static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, const T *b, T *x, double rtol,
@@ -893,8 +897,8 @@ static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, con
     constexpr bool f64 = sizeof(T) == 8;
     T *z = f64 ? (T *)w.z : (T *)w.z32, *x0 = f64 ? (T *)w.q : (T *)w.q32;
     // the outcome goes to pinned memory
-    ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, (ResidentOut *)c->host, bad, rtol,
-                   kResidentLimit, (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
+    ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, Y.stop, (ResidentOut *)c->host, bad, rtol,
+                   m->waits.limit, m->waits.last_limit, (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
     {
         std::lock_guard<std::mutex> lk(g_resident_mu[c->device]);
         {
@@ -953,7 +957,7 @@ fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *
         if (m->sym.state == 1 && (s = ensure_resident(m)) != FE_OK) return s;
         if (m->sym.state == 1 && resident_fits<double>(m)) {
             fe_mesh_s::SymState &Y = m->sym;
-            HIPCALL(c, launch_resident_init(m->resident.slots, (ResidentOut *)c->host, Y.bad, c->stream));
+            HIPCALL(c, resident_init(m, Y.bad));
             HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, nullptr, Y.bad, false, c->stream));
             ResidentOut o;
             bool ran;
@@ -1445,7 +1449,7 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
             ResidentOut o;
             bool ran = false;
             if (resident_fits<float>(m)) {
-                HIPCALL(c, launch_resident_init(m->resident.slots, (ResidentOut *)c->host, nullptr, c->stream));
+                HIPCALL(c, resident_init(m, nullptr));
                 s = resident_pcg<float>(m, w, values, w.r32, w.x32, tol_in, max_iter - used, true, nullptr, o, ran);
                 if (s != FE_OK) return s;
             }
@@ -1735,6 +1739,19 @@ fe_status fe_ctx_profile_read(fe_ctx c, int slot, int64_t *launches, double *tot
     }
     *launches = (int64_t)(p.used / 2);
     *total_ms = tot;
+    return FE_OK;
+}
+
+// ---- test hooks -----------------------------------------------------------------
+
+fe_status fe_test_one_launch(fe_mesh m, double wait_us, double last_wait_us, int32_t stopped)
+{
+    if (!m) return FE_EINVAL;
+    const auto ok = [](double us) { return us >= 0.0 && us <= 1e6; };
+    if (!ok(wait_us) || !ok(last_wait_us)) return fail(m->ctx, FE_EINVAL, "waits are 0 to 1e6 us");
+    m->waits.limit = (unsigned long long)(wait_us * 100.0);
+    m->waits.last_limit = (unsigned long long)(last_wait_us * 100.0);
+    m->waits.stopped = stopped != 0;
     return FE_OK;
 }
 

@@ -105,7 +105,15 @@ struct fe_mesh_s {
         int state = 0, G = 0, R = 0;
         feasm::ResidentPlan plan;
         unsigned long long *slots = nullptr;   // the groups' meeting slots
+        uint32_t *stop = nullptr;              // the groups' word of a solve that is given up
     } resident;
+    // longest waits of a one-launch solve's groups for each other, in 10 ns
+    // (fe_test_one_launch): 50 ms, far beyond any iteration (~10 us), short
+    // for a caller that then runs the solve in the general form
+    struct OneLaunchWaits {
+        unsigned long long limit = 5000000, last_limit = 5000000;
+        bool stopped = false;
+    } waits;
 };
 
 namespace feasm {

@@ -234,10 +234,11 @@ struct ResidentArgs {
     const void *b;               // T [N]
     void *x, *z, *x0;            // T [N]: solution (in: first guess unless x_zero), exchange, copy of the guess
     unsigned long long *slots;   // kResidentSlots
+    uint32_t *stop;              // set by a group that gives up (device)
     ResidentOut *out;            // device or pinned
     const int32_t *bad;          // nothing runs when *bad != 0 (null: no such word)
     double rtol;
-    unsigned long long limit;    // longest wait, in 10 ns
+    unsigned long long limit, last_limit;   // longest wait, at the last meeting of an FP64 solve, in 10 ns
     int N, R, max_iter, x_zero;  // R: rows per group
 };
 // Entries per row that the kernel is built for, 0 for longer rows; rows per
@@ -250,8 +251,10 @@ bool resident_shape(int elem_bytes, int64_t N, int max_row, int cus, int &G, int
 size_t resident_off_words(int G, int R, int max_row);
 // Fills the plan; *bad = 1 when a group's halo does not fit.
 hipError_t launch_resident_plan(const DevMesh &m, const ResidentPlan &P, int G, int R, int32_t *bad, hipStream_t s);
-// Before each solve: empties the slots and *out, sets *bad (or null) to 0.
-hipError_t launch_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad, hipStream_t s);
+// Before each solve: empties the slots and *out, sets *stop and *bad (or null)
+// to 0 (stopped: *stop to 1, as if a group had given up already).
+hipError_t launch_resident_init(unsigned long long *slots, uint32_t *stop, bool stopped, ResidentOut *out, int32_t *bad,
+                                hipStream_t s);
 template <class T>
 hipError_t launch_resident(const ResidentArgs &A, int max_row, int G, hipStream_t s);
 

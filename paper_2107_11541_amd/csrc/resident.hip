@@ -27,8 +27,10 @@
 //
 // Every wait is bounded.  A group that waits longer than the limit (other
 // work holds the CUs that the remaining groups need) marks the solve as
-// abandoned and leaves; the others run into the same limit.  The caller then
-// runs the solve in the general form.
+// abandoned and leaves; the others see the mark while they wait, or when they
+// start (those that had no CU until then, which would else wait out the limit
+// one CU's load after the other).  The caller then runs the solve in the
+// general form.
 #include "internal.h"
 
 namespace feasm {
@@ -92,6 +94,7 @@ __device__ inline double wave_sum63(double v)
 struct Meet {
     unsigned long long *slots;
     ResidentOut *out;
+    uint32_t *stop;              // nonzero: the solve is abandoned
     unsigned long long limit;    // 100 MHz ticks
     int G, g, phase;
     double (*sa)[kWaves];        // LDS: wave partials of the group, of the collected values
@@ -141,14 +144,14 @@ __device__ inline bool meet_sum(Meet &M, double (&v)[NV])
     if (tid < M.G) {
         unsigned long long u[NV];
         const unsigned long long t0 = wall_clock64();
-        for (;;) {
+        for (unsigned polls = 1;; ++polls) {
             bool all = true;
 #pragma unroll
             for (int q = 0; q < NV; ++q) {
                 u[q] = agent_load(buf + q * kResidentMaxGroups + tid);
                 all = all && u[q] != kEmpty;
             }
-            if (!all && wall_clock64() - t0 > M.limit) {
+            if (!all && (wall_clock64() - t0 > M.limit || (polls % 32 == 0 && agent_load(M.stop) != 0))) {
                 *M.failed = 1;
                 break;
             }
@@ -167,7 +170,10 @@ __device__ inline bool meet_sum(Meet &M, double (&v)[NV])
     }
     __syncthreads();
     if (*M.failed) {
-        if (tid == 0) agent_store(&M.out->abandoned, 1);
+        if (tid == 0) {
+            agent_store(M.stop, 1u);
+            agent_store(&M.out->abandoned, 1);
+        }
         return false;
     }
 #pragma unroll
@@ -275,11 +281,16 @@ __global__ void __launch_bounds__(kRB, 1) k_resident(ResidentArgs A)
     __shared__ double sa[2][kWaves], sb[2][kWaves];
     __shared__ int failed;
 
-    if (A.bad && agent_load(A.bad) != 0) return;   // the caller takes the general form (every group alike)
     const int tid = threadIdx.x, g = blockIdx.x;
+    const uint32_t stopped = agent_load(A.stop);
+    if (A.bad && agent_load(A.bad) != 0) return;   // the caller takes the general form (every group alike)
+    if (stopped) {                                 // abandoned before this group had a CU
+        if (tid == 0) agent_store(&A.out->abandoned, 1);
+        return;
+    }
     const int r0 = g * A.R, nr = min(A.R, A.N - r0), Sp = (A.R + kRB - 1) / kRB;
     if (tid == 0) failed = 0;
-    Meet M{A.slots, A.out, A.limit, (int)gridDim.x, g, 0, sa, sb, &failed};
+    Meet M{A.slots, A.out, A.stop, A.limit, (int)gridDim.x, g, 0, sa, sb, &failed};
 
     // 1. the rows: values and window offsets (bytes) of each thread's rows
     const int nh = A.plan.nh[g];
@@ -489,6 +500,7 @@ __global__ void __launch_bounds__(kRB, 1) k_resident(ResidentArgs A)
             const T d = (i < nr ? ((const T *)A.b)[r0 + i] : T(0)) - q[s];
             none[0] += (double)d * (double)d;
         }
+        M.limit = A.last_limit;
         if (!meet_sum(M, none)) return;
         tr = none[0];
     }
@@ -509,11 +521,13 @@ __global__ void __launch_bounds__(kRB, 1) k_resident(ResidentArgs A)
     }
 }
 
-__global__ void __launch_bounds__(256) k_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad)
+__global__ void __launch_bounds__(256) k_resident_init(unsigned long long *slots, uint32_t *stop, uint32_t stopped,
+                                                       ResidentOut *out, int32_t *bad)
 {
     for (int q = threadIdx.x; q < (int)(3 * kMeetBuffer); q += 256) slots[q] = kEmpty;
     if (threadIdx.x == 0) {
         *out = ResidentOut{};
+        *stop = stopped;
         if (bad) *bad = 0;
     }
 }
@@ -577,9 +591,10 @@ hipError_t launch_resident_plan(const DevMesh &m, const ResidentPlan &P, int G, 
     return hipGetLastError();
 }
 
-hipError_t launch_resident_init(unsigned long long *slots, ResidentOut *out, int32_t *bad, hipStream_t s)
+hipError_t launch_resident_init(unsigned long long *slots, uint32_t *stop, bool stopped, ResidentOut *out, int32_t *bad,
+                                hipStream_t s)
 {
-    hipLaunchKernelGGL(k_resident_init, dim3(1), dim3(256), 0, s, slots, out, bad);
+    hipLaunchKernelGGL(k_resident_init, dim3(1), dim3(256), 0, s, slots, stop, stopped ? 1u : 0u, out, bad);
     return hipGetLastError();
 }
 

@@ -56,3 +56,56 @@ def test_general_upload_flag_holds_in_both_precisions(fe_ctx, precision):
     x, info, launches = solve(fe, mesh, L, f, rtol=1e-10, max_iter=2000, precision=prec)
     assert info["status"] == 0 and launches >= info["iterations"] > info["outer_iterations"]
     mesh.close()
+
+
+def hooks(mesh, wait_us=50000.0, last_wait_us=50000.0, stopped=False):
+    mesh.ctx.check(mesh.ctx.lib.fe_test_one_launch(mesh.h, wait_us, last_wait_us, int(stopped)))
+
+
+def check_given_up(fe, mesh, L, f):
+    """The solve starts from the first guess as passed in, whichever form runs in
+    the end: 5 iterations agree with the general SpMV's to 1e-12 (see
+    tests/test_gpu_resident.py).  Returns its intervals of slot 0."""
+    import torch
+    g = torch.Generator().manual_seed(5)
+    x0 = torch.rand(mesh.n_nodes, generator=g, dtype=torch.float64).cuda()
+    x, info, launches = solve(fe, mesh, L, f, x=x0.clone(), rtol=0.0, max_iter=5)
+    xg, want = fe.cg_solve_noalloc(mesh, L, f, x=x0.clone(), rtol=0.0, max_iter=5)
+    assert info["iterations"] == want["iterations"] == 5
+    assert rel(host(x), host(xg)) <= 1e-12
+    assert abs(info["true_rel_residual"] - want["true_rel_residual"]) <= 1e-11 * want["true_rel_residual"]
+    return launches
+
+
+# 23^3: several groups, each with rows for every thread; 4^3: one group (no meeting:
+# only the stop word ends it early)
+@pytest.mark.parametrize("n,kw", [(23, dict(stopped=True)), (4, dict(stopped=True)), (23, dict(wait_us=0.0)),
+                                  (23, dict(last_wait_us=0.0))])
+def test_solve_that_is_given_up(fe_ctx, n, kw):
+    """Groups that start after the solve was given up leave at once; groups that
+    wait too long give it up, at the first meeting or, some of them having
+    stored x, at the last."""
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, HEX, n)
+    hooks(mesh, **kw)
+    # (at the last meeting a group gives up unless every other came before it)
+    for _ in range(20):
+        launches = check_given_up(fe, mesh, L, f)
+        if launches != 1:
+            break
+    assert launches == 1 + 5   # the one given up, then one per iteration
+    hooks(mesh)
+    check_given_up(fe, mesh, L, f)
+    mesh.close()
+
+
+@pytest.mark.parametrize("kw", [dict(stopped=True), dict(wait_us=0.0)])
+def test_mixed_solve_that_is_given_up(fe_ctx, kw):
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, HEX, 23)
+    hooks(mesh, **kw)
+    x, info, launches = solve(fe, mesh, L, f, rtol=1e-10, max_iter=5000, precision=fe.MIXED)
+    assert info["status"] == 0 and info["true_rel_residual"] <= 1e-10 and launches > info["iterations"]
+    xt, _ = fe.cg_solve_noalloc(mesh, L, f, rtol=1e-12, max_iter=5000)
+    assert rel(host(x), host(xt)) <= 1e-6
+    mesh.close()
