@@ -264,8 +264,9 @@ typedef struct {
  * FP32 solves so up to ~655,000 (~786,000) nodes.  The launch needs a plan of
  * the pattern (about 2 bytes per nonzero and 4 MB on the device, built by
  * the first such solve) and most of the device's CUs at once: when other
- * work holds them for more than 50 ms the solve runs in the general form, as
- * do this mesh's later ones.  Such solves of one process run one after the
+ * work holds them for more than 50 ms the solve runs in the general form, and
+ * so do this mesh's next 16, or twice as many each time that a later try ends
+ * so too (at most 4096).  Such solves of one process run one after the
  * other per device.
  * The forms round differently; the true residual is always computed
  * with `values` as given.  Returns FE_ENOCONV (x written) at max_iter,

@@ -819,6 +819,10 @@ static fe_status ensure_sym(fe_mesh_s *m)
 // run one after the other per device (a solve is synchronous to its caller).
 constexpr int kResidentDevices = 64;
 static std::mutex g_resident_mu[kResidentDevices];
+// Solves of a mesh that take the general form after one was given up, doubled
+// for each in a row up to 256 times as many: 50 ms lost cost no more than
+// 16 of the solves that then run (0.1 to 30 ms each), and less each time.
+constexpr int kResidentPause = 16;
 
 // The plan of the mesh's one-launch solves, built on first use.  A pattern
 // that does not fit, or a device without room for the plan, leaves state -1.
@@ -867,12 +871,17 @@ static fe_status ensure_resident(fe_mesh_s *m)
     return FE_OK;
 }
 
-// Whether a solve in precision T of this mesh fits the one-launch form.
+// Whether this mesh's next solve in precision T takes the one-launch form: it
+// fits, and is not one of those that go by after a solve was given up.
 template <class T>
-static bool resident_fits(const fe_mesh_s *m)
+static bool resident_turn(fe_mesh_s *m)
 {
+    fe_mesh_s::ResidentState &Y = m->resident;
     int G, R;
-    return m->resident.state == 1 && resident_shape(sizeof(T), m->dm.N, m->dm.max_row, m->ctx->cus, G, R);
+    if (Y.state != 1 || !resident_shape(sizeof(T), m->dm.N, m->dm.max_row, m->ctx->cus, G, R)) return false;
+    if (Y.pause == 0) return true;
+    --Y.pause;
+    return false;
 }
 
 // Empties the words of the next one-launch solve (and *bad, or null).
@@ -883,7 +892,7 @@ static hipError_t resident_init(fe_mesh_s *m, int32_t *bad)
 }
 
 // Runs the one-launch form (resident.hip) of a PCG solve of `values` in
-// precision T (resident_fits).  ran: it did, o holds its outcome; else the
+// precision T (resident_turn).  ran: it did, o holds its outcome; else the
 // general form has to run, on the x that was passed in (o.abandoned == 0:
 // the pair check behind `bad` failed).  resident_init is queued already.
 // Synchronises the stream.
@@ -910,8 +919,12 @@ static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, con
     }
     memcpy(&o, c->host, sizeof o);
     ran = o.ran != 0 && !o.abandoned;
+    if (ran) m->resident.given_up = 0;
     if (o.abandoned) {
-        m->resident.state = -1;
+        // other work's hold on the CUs may pass: the form is tried again, later each time
+        fe_mesh_s::ResidentState &S = m->resident;
+        S.pause = kResidentPause << std::min(S.given_up, 8);
+        ++S.given_up;
         if (o.wrote_x && !x_zero)
             HIPCALL(c, hipMemcpyAsync(x, x0, (size_t)d.N * sizeof(T), hipMemcpyDeviceToDevice, c->stream));
     }
@@ -955,7 +968,7 @@ fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *
         // the whole solve in one launch where the matrix fits the registers
         if ((s = ensure_sym(m)) != FE_OK) return s;
         if (m->sym.state == 1 && (s = ensure_resident(m)) != FE_OK) return s;
-        if (m->sym.state == 1 && resident_fits<double>(m)) {
+        if (m->sym.state == 1 && resident_turn<double>(m)) {
             fe_mesh_s::SymState &Y = m->sym;
             HIPCALL(c, resident_init(m, Y.bad));
             HIPCALL(c, launch_sym_pack(m->dm, Y.map, Y.mstart, values, nullptr, Y.bad, false, c->stream));
@@ -975,6 +988,7 @@ fe_status pcg_fp64(fe_mesh_s *m, CGWork &w, const double *values, const double *
                 return FE_OK;
             }
             refused = !o.abandoned;
+            if (refused) w.sym = SymSpmv();   // (an earlier solve of the general form may have left its own)
         }
     }
     if (use_sym && !refused) s = select_sym(m, w, values);
@@ -1448,7 +1462,7 @@ fe_status fe_cg_solve(fe_mesh m, const double *values, const double *rhs, double
             int32_t fl[4];
             ResidentOut o;
             bool ran = false;
-            if (resident_fits<float>(m)) {
+            if (resident_turn<float>(m)) {
                 HIPCALL(c, resident_init(m, nullptr));
                 s = resident_pcg<float>(m, w, values, w.r32, w.x32, tol_in, max_iter - used, true, nullptr, o, ran);
                 if (s != FE_OK) return s;

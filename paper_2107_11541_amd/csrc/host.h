@@ -99,10 +99,11 @@ struct fe_mesh_s {
         int64_t n_packed = 0;
     } sym;
     // one-launch solves (resident.hip): their plan of the pattern, built on
-    // first use (state 0: not built, 1: built, -1: none, or a solve was
-    // abandoned because other work held the CUs)
+    // first use (state 0: not built, 1: built, -1: none); solves given up in a
+    // row because other work held the CUs, and the solves that take the
+    // general form before the next try
     struct ResidentState {
-        int state = 0, G = 0, R = 0;
+        int state = 0, G = 0, R = 0, given_up = 0, pause = 0;
         feasm::ResidentPlan plan;
         unsigned long long *slots = nullptr;   // the groups' meeting slots
         uint32_t *stop = nullptr;              // the groups' word of a solve that is given up

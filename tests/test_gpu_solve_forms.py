@@ -109,3 +109,43 @@ def test_mixed_solve_that_is_given_up(fe_ctx, kw):
     xt, _ = fe.cg_solve_noalloc(mesh, L, f, rtol=1e-12, max_iter=5000)
     assert rel(host(x), host(xt)) <= 1e-6
     mesh.close()
+
+
+def test_one_launch_form_comes_back_after_a_give_up(fe_ctx):
+    """16 solves in the general form, then one launch again; a second give-up in
+    a row doubles them."""
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, HEX, 9)
+
+    def forms(k):
+        return [solve(fe, mesh, L, f, rtol=0.0, max_iter=3)[2] for _ in range(k)]
+    assert forms(1) == [1]
+    hooks(mesh, stopped=True)
+    assert forms(1 + 16 + 1 + 32) == [4] + 16 * [3] + [4] + 32 * [3]
+    hooks(mesh)
+    assert forms(2) == [1, 1]
+    hooks(mesh, stopped=True)
+    assert forms(1 + 16) == [4] + 16 * [3]
+    mesh.close()
+
+
+def test_refused_matrix_after_a_general_symmetric_solve(fe_ctx):
+    """A matrix that fails the pair check, on a mesh whose last solves ran the
+    symmetric SpMV in the general form: the general SpMV runs, on this matrix."""
+    import torch
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, HEX, 9)
+    hooks(mesh, stopped=True)
+    for _ in range(17):
+        assert solve(fe, mesh, L, f, rtol=0.0, max_iter=3)[1]["symmetric_spmv"]
+    hooks(mesh)
+    rp, ci = mesh.pattern_host()
+    rows = np.repeat(np.arange(mesh.n_nodes), np.diff(rp))
+    r = rows[int(np.argmax(np.where(ci != rows, np.abs(host(L)), 0.0)))]
+    off = torch.tensor([p for p in range(rp[r], rp[r + 1]) if ci[p] != r], device=L.device)
+    L2 = 3.0 * L
+    L2[off] *= 1.0 + 1e-6
+    x, info, _ = solve(fe, mesh, L2, f, rtol=0.0, max_iter=3)
+    xg, _ = fe.cg_solve_noalloc(mesh, L2, f, rtol=0.0, max_iter=3)
+    assert not info["symmetric_spmv"] and torch.equal(x, xg)
+    mesh.close()
