@@ -2,6 +2,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -819,6 +820,10 @@ static fe_status ensure_sym(fe_mesh_s *m)
 // run one after the other per device (a solve is synchronous to its caller).
 constexpr int kResidentDevices = 64;
 static std::mutex g_resident_mu[kResidentDevices];
+// Contexts of each device: where there are several, a solve lets its stream
+// run dry before it takes its turn, so that work queued before it (which may
+// be long, or wait for another thread) holds up no other context's solves.
+static std::atomic<int> g_contexts[kResidentDevices];
 // Solves of a mesh that take the general form after one was given up, doubled
 // for each in a row up to 256 times as many: 50 ms lost cost no more than
 // 16 of the solves that then run (0.1 to 30 ms each), and less each time.
@@ -908,6 +913,10 @@ static fe_status resident_pcg(fe_mesh_s *m, CGWork &w, const double *values, con
     // the outcome goes to pinned memory
     ResidentArgs A{Y.plan, d.rowptr, d.diagpos, values, b, x, z, x0, Y.slots, Y.stop, (ResidentOut *)c->host, bad, rtol,
                    m->waits.limit, m->waits.last_limit, (int)d.N, Y.R, max_iter, x_zero ? 1 : 0};
+    if (g_contexts[c->device] > 1) {
+        const fe_status s = sync(c);
+        if (s != FE_OK) return s;
+    }
     {
         std::lock_guard<std::mutex> lk(g_resident_mu[c->device]);
         {
@@ -1102,6 +1111,7 @@ fe_status fe_ctx_create(int device, void *hip_stream, fe_ctx *out)
         return FE_ENOMEM;
     }
     if (hipStreamCreateWithFlags(&c->cap_stream, hipStreamNonBlocking) != hipSuccess) c->cap_stream = nullptr;
+    if (device < kResidentDevices) ++g_contexts[device];
     *out = c;
     return FE_OK;
 }
@@ -1111,6 +1121,7 @@ void fe_ctx_destroy(fe_ctx c)
     if (!c) return;
     (void)hipSetDevice(c->device);
     (void)hipStreamSynchronize(c->stream);
+    if (c->device < kResidentDevices) --g_contexts[c->device];
     if (c->scratch) (void)hipFree(c->scratch);
     if (c->host) (void)hipHostFree(c->host);
     while (!c->meshes.empty()) fe_mesh_free(c->meshes.back());

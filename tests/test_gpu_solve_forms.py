@@ -149,3 +149,83 @@ def test_refused_matrix_after_a_general_symmetric_solve(fe_ctx):
     xg, _ = fe.cg_solve_noalloc(mesh, L2, f, rtol=0.0, max_iter=3)
     assert not info["symmetric_spmv"] and torch.equal(x, xg)
     mesh.close()
+
+
+def _contexts(fe, k, kind=HEX, n=9):
+    """k contexts on streams of their own, each with a mesh that has solved once."""
+    import torch
+    out = []
+    for _ in range(k):
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            ctx = fe.Context(0, st)
+            mesh, L, f = system(fe, ctx, kind, n)
+            x, info = fe.cg_solve(mesh, L, f, rtol=1e-9, max_iter=2000)
+            st.synchronize()
+        out.append((st, ctx, mesh, L, f, x, info))
+    return out
+
+
+def test_solves_of_several_contexts_at_once(fe_ctx):
+    """Four threads solving at a time, each on its stream: every solve in one
+    launch, with the bits of a solve alone."""
+    import threading
+    import torch
+    import paper_2107_11541_amd as fe
+    ws = _contexts(fe, 4, n=17)
+    bad = []
+
+    def go(st, ctx, mesh, L, f, x, info):
+        with torch.cuda.stream(st):
+            for _ in range(20):
+                y, i, launches = solve(fe, mesh, L, f, rtol=1e-9, max_iter=2000)
+                st.synchronize()
+                if launches != 1 or i != info or not torch.equal(x, y):
+                    bad.append((launches, i))
+    threads = [threading.Thread(target=go, args=w) for w in ws]
+    for t in threads:
+        t.start()
+    for t in threads:
+        t.join()
+    assert not bad
+    for w in ws:
+        w[2].close()
+        w[1].close()
+
+
+def test_work_queued_before_a_solve_holds_up_no_other_context(fe_ctx):
+    """A solve queued behind other work of its stream (here a kernel that spins
+    for about half a second) waits for it alone: another context solves
+    meanwhile."""
+    import threading
+    import time
+    import torch
+    import paper_2107_11541_amd as fe
+    a, b = _contexts(fe, 2)
+    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    with torch.cuda.stream(a[0]):
+        e0.record()
+        torch.cuda._sleep(1_000_000)
+        e1.record()
+        a[0].synchronize()
+    cycles = int(1_000_000 * 500.0 / e0.elapsed_time(e1))   # 500 ms
+    done = threading.Event()
+
+    def slow():
+        with torch.cuda.stream(a[0]):
+            x = torch.zeros_like(a[5])
+            torch.cuda._sleep(cycles)
+            fe.cg_solve(a[2], a[3], a[4], x=x, rtol=1e-9, max_iter=2000)
+        done.set()
+    t = threading.Thread(target=slow)
+    with torch.cuda.stream(b[0]):
+        x = torch.zeros_like(b[5])
+        t.start()
+        time.sleep(0.1)
+        y, info = fe.cg_solve(b[2], b[3], b[4], x=x, rtol=1e-9, max_iter=2000)
+        b[0].synchronize()
+        assert not done.is_set() and info["status"] == 0
+    t.join()
+    for w in (a, b):
+        w[2].close()
+        w[1].close()
