@@ -839,10 +839,8 @@ static fe_status ensure_resident(fe_mesh_s *m)
     const DevMesh &d = m->dm;
     fe_mesh_s::ResidentState N;
     N.state = -1;
-    if (c->device >= kResidentDevices || !resident_shape(4, d.N, d.max_row, c->cus, N.G, N.R)) {
-        Y = N;
-        return FE_OK;
-    }
+    // (not for good: another stream may have more CUs)
+    if (c->device >= kResidentDevices || !resident_shape(4, d.N, d.max_row, c->cus, N.G, N.R)) return FE_OK;
     const size_t ow = resident_off_words(N.G, N.R, d.max_row) * sizeof(uint32_t);
     const size_t hw = ((size_t)N.G * kResidentHalo + N.G) * sizeof(int32_t);
     const size_t sw = kResidentSlots * sizeof(unsigned long long);
@@ -882,8 +880,9 @@ template <class T>
 static bool resident_turn(fe_mesh_s *m)
 {
     fe_mesh_s::ResidentState &Y = m->resident;
-    int G, R;
-    if (Y.state != 1 || !resident_shape(sizeof(T), m->dm.N, m->dm.max_row, m->ctx->cus, G, R)) return false;
+    if (Y.state != 1 || Y.G > m->ctx->cus ||   // (the stream may have changed since the plan)
+        Y.R > resident_rows(sizeof(T), resident_width(m->dm.max_row)) * kResidentThreads)
+        return false;
     if (Y.pause == 0) return true;
     --Y.pause;
     return false;
@@ -1087,6 +1086,22 @@ size_t noalloc_layout(char *base, int64_t n, int max_iter, CGWork &w)
 
 // ---------------------------------------------------------------------------
 
+// Compute units that kernels on the context's stream may take: the device's,
+// or those of the stream's own mask.
+static int stream_cus(const fe_ctx_s *c)
+{
+    int cus = 0;
+    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, c->device) != hipSuccess) cus = 0;
+    uint32_t mask[32] = {};
+    if (hipExtStreamGetCUMask(c->stream, 32, mask) != hipSuccess) {
+        (void)hipGetLastError();
+        return cus;
+    }
+    int set = 0;
+    for (uint32_t w : mask) set += __builtin_popcount(w);
+    return set > 0 ? std::min(cus, set) : cus;
+}
+
 extern "C" {
 
 fe_status fe_ctx_create(int device, void *hip_stream, fe_ctx *out)
@@ -1098,12 +1113,10 @@ fe_status fe_ctx_create(int device, void *hip_stream, fe_ctx *out)
     if (hipSetDevice(device) != hipSuccess) return FE_EDEVICE;
     if (init_spmv_grid(device) != hipSuccess) return FE_EDEVICE;
     if (noalloc_init(device) != hipSuccess) return FE_EDEVICE;
-    int cus = 0;
-    if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess) return FE_EDEVICE;
     auto *c = new fe_ctx_s();
     c->device = device;
-    c->cus = cus;
     c->stream = (hipStream_t)hip_stream;
+    c->cus = stream_cus(c);
     if (hipMalloc((void **)&c->scratch, 2048 * sizeof(double)) != hipSuccess ||
         hipHostMalloc((void **)&c->host, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
         if (c->scratch) (void)hipFree(c->scratch);
@@ -1137,6 +1150,7 @@ fe_status fe_ctx_set_stream(fe_ctx c, void *hip_stream)
 {
     if (!c) return FE_EINVAL;
     c->stream = (hipStream_t)hip_stream;
+    c->cus = stream_cus(c);
     return FE_OK;
 }
 

@@ -52,7 +52,7 @@ struct ProfSlot {
 
 struct fe_ctx_s {
     int device = 0;
-    int cus = 0;                  // compute units of the device
+    int cus = 0;                  // compute units that the stream may take
     hipStream_t stream = nullptr;
     hipStream_t cap_stream = nullptr;   // private stream that PCG graphs are recorded on (never run on)
     std::string err;

@@ -229,3 +229,32 @@ def test_work_queued_before_a_solve_holds_up_no_other_context(fe_ctx):
     for w in (a, b):
         w[2].close()
         w[1].close()
+
+
+def test_solve_on_a_stream_with_few_cus(fe_ctx):
+    """A stream masked to 64 CUs: a matrix that needs more groups than that runs
+    in the general form, one that does not in one launch, and the mesh that was
+    planned on the masked stream in one launch on another."""
+    import ctypes
+    import torch
+    import paper_2107_11541_amd as fe
+    hip = ctypes.CDLL("libamdhip64.so")
+    h, mask = ctypes.c_void_p(), (ctypes.c_uint32 * 8)(*([0xff] * 8))
+    assert hip.hipExtStreamCreateWithCUMask(ctypes.byref(h), 8, mask) == 0
+    st = torch.cuda.ExternalStream(h.value)
+    with torch.cuda.stream(st):
+        ctx = fe.Context(0, st)
+        for n, one in ((9, True), (60, False)):   # 4 groups; 222 on the whole device
+            mesh, L, f = system(fe, ctx, HEX, n)
+            x, info, launches = solve(fe, mesh, L, f, rtol=0.0, max_iter=5)
+            assert launches == (1 if one else 5)
+            xg, _ = fe.cg_solve_noalloc(mesh, L, f, rtol=0.0, max_iter=5)
+            assert rel(host(x), host(xg)) <= 1e-12
+            st.synchronize()
+            ctx.check(ctx.lib.fe_ctx_set_stream(ctx.h, ctypes.c_void_p(fe_ctx.stream.cuda_stream)))
+            assert solve(fe, mesh, L, f, rtol=0.0, max_iter=5)[2] == 1
+            torch.cuda.synchronize()
+            ctx.check(ctx.lib.fe_ctx_set_stream(ctx.h, h))
+            mesh.close()
+        ctx.close()
+    assert hip.hipStreamDestroy(h) == 0
