@@ -258,3 +258,43 @@ def test_solve_on_a_stream_with_few_cus(fe_ctx):
             mesh.close()
         ctx.close()
     assert hip.hipStreamDestroy(h) == 0
+
+
+# rows of 27 entries: 72^3 is the last cube that fits the registers in FP64, 85^3 in
+# FP32; rows of 15: 82^3 in FP64
+@pytest.mark.parametrize("kind,n,fp64,mixed", [(HEX, 4, True, True), (HEX, 23, True, True), (HEX, 72, True, True),
+                                               (HEX, 73, False, True), (HEX, 86, False, False), (TET, 24, True, True),
+                                               (TET, 82, True, True), (TET, 83, False, True), (PEN, 12, True, True),
+                                               (PYR, 12, True, True), (HYB, 17, True, True)])
+def test_form_by_size(fe_ctx, kind, n, fp64, mixed):
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, kind, n)
+    _, info, launches = solve(fe, mesh, L, f, rtol=0.0, max_iter=5)
+    assert info["symmetric_spmv"] and launches == (1 if fp64 else 5)
+    _, info, launches = solve(fe, mesh, L, f, rtol=0.0, max_iter=5, precision=fe.MIXED)
+    assert info["iterations"] == 5 and launches == (1 if mixed else 5)
+    mesh.close()
+
+
+def test_form_of_a_halo_that_does_not_fit(fe_ctx):
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, HEX, 26, renumber=False)
+    for precision in (fe.FP64, fe.MIXED):
+        assert solve(fe, mesh, L, f, rtol=0.0, max_iter=5, precision=precision)[2] == 5
+    mesh.close()
+
+
+# the general form's symmetric SpMV on every pattern: small meshes by giving the
+# one launch up, and one too large for it
+@pytest.mark.parametrize("kind,n", [(HEX, 14), (TET, 24), (PEN, 16), (PYR, 12), (HYB, 12), (PYR, 60)])
+def test_symmetric_spmv_of_the_general_form(fe_ctx, kind, n):
+    import paper_2107_11541_amd as fe
+    mesh, L, f = system(fe, fe_ctx, kind, n)
+    hooks(mesh, stopped=True)
+    solve(fe, mesh, L, f, rtol=0.0, max_iter=1)
+    xs, info, launches = solve(fe, mesh, L, f, rtol=0.0, max_iter=5)
+    xg, want = fe.cg_solve_noalloc(mesh, L, f, rtol=0.0, max_iter=5)
+    assert info["symmetric_spmv"] and not want["symmetric_spmv"] and launches == 5
+    assert rel(host(xs), host(xg)) <= 1e-12
+    assert abs(info["rel_residual"] - want["rel_residual"]) <= 1e-12 * want["rel_residual"]
+    mesh.close()
