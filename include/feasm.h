@@ -105,7 +105,13 @@ fe_status fe_ctx_set_stream(fe_ctx ctx, void *hip_stream);
  * CSR row would hold more than 255 entries: the scatter plans store in-row
  * positions as bytes; a hexahedral node may lie in up to 36 elements, a
  * tetrahedral one in up to ~80), FE_ENOMEM, FE_EDEVICE.  The mesh owns all
- * its device memory.  The planner keeps its host temporaries on the calling
+ * its device memory.  Part of it only makes calls faster: what the gathers of
+ * the element-vector passes, and of the matrix assembly by blocks, add up (32
+ * bytes per row of every element block, about 62 bytes per HEX08 element; for
+ * the matrices 8 bytes per entry of every block's rows and 24 per row, 2.3 to
+ * 3.6 times the matrix in an order of good locality).  Without room for it,
+ * now or when a later allocation of the context finds none, it is left out or
+ * freed, and the mesh assembles colour by colour.  The planner keeps its host temporaries on the calling
  * thread for the next upload while they total at most 256 MiB (meshes up to
  * about 100^3 hexahedra); larger ones are released before the call returns.
  */
@@ -309,9 +315,7 @@ fe_status fe_cg_solve_noalloc(fe_mesh mesh, const double *values, const double *
  * applied to the velocity element by element (no matrix is formed).  All
  * arrays are device, mesh numbering, [k][n_nodes] rows, FP64.  Each call
  * synchronises the stream and fails with FE_EBADELEM on det J <= 0.  The
- * passes keep a work array on the mesh from their first call on (32 bytes
- * per row of every element block, about 62 bytes per HEX08 element; without
- * room for it they run colour by colour). */
+ * passes use a work array that fe_mesh_upload lays out (see there). */
 
 /* Scalar transport (the heat and species equations, which the paper
  * advances with the same Runge-Kutta stages and no algebraic solver,
@@ -497,6 +501,8 @@ fe_status fe_ctx_profile_read(fe_ctx ctx, int slot, int64_t *launches, double *t
  * stopped: the next solves find themselves given up when they start.  A solve
  * given up runs again in the general form. */
 fe_status fe_test_one_launch(fe_mesh mesh, double wait_us, double last_wait_us, int32_t stopped);
+/* The context's next n device allocations find no room. */
+fe_status fe_test_fail_allocs(fe_ctx ctx, int32_t n);
 
 /* ---- host-only preprocessing (no device needed; used to test the planner) --- */
 

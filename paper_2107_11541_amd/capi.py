@@ -101,6 +101,7 @@ SIGNATURES = {
     "fe_serve_destroy": (None, [P]),
     "fe_ctx_profile": (C.c_int, [P, C.c_int]),
     "fe_ctx_profile_read": (C.c_int, [P, C.c_int, C.POINTER(i64), C.POINTER(dbl)]),
+    "fe_test_fail_allocs": (C.c_int, [P, i32]),
     "fe_test_one_launch": (C.c_int, [P, dbl, dbl, i32]),
     "fe_plan_create": (C.c_int, [C.c_int, i64, P, i64, P, C.c_uint32, C.POINTER(P)]),
     "fe_plan_create_mixed": (C.c_int, [i64, P, i64, P, P, C.c_uint32, C.POINTER(P)]),

@@ -421,16 +421,49 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
     return FE_OK;
 }
 
-fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes)
+// Bytes of a mesh's gather work array: the images and their right-hand sides,
+// or the element-vector passes' sums alone.
+static size_t work_bytes(const fe_mesh_s *m)
+{
+    return m->img_work ? image_bytes(m->dm) : 4 * (size_t)m->dm.vec_T * sizeof(double);
+}
+
+// Frees the gather work arrays of the context's meshes, which then assemble
+// colour by colour (hipFree waits for the kernels that use them).
+static bool give_back_work(fe_ctx_s *c)
+{
+    bool any = false;
+    for (fe_mesh_s *m : c->meshes) {
+        if (!m->vec_work) continue;
+        m->bytes -= work_bytes(m);
+        mesh_free_ptr(m, m->vec_work);
+        m->vec_work = m->img_work = nullptr;
+        any = true;
+    }
+    return any;
+}
+
+hipError_t dev_alloc(fe_ctx_s *c, void **p, size_t bytes, bool optional)
+{
+    for (;;) {
+        *p = nullptr;
+        const hipError_t e = c->fail_allocs > 0 ? hipErrorOutOfMemory : hipMalloc(p, bytes);
+        if (e == hipSuccess) return e;
+        if (c->fail_allocs > 0) --c->fail_allocs;
+        (void)hipGetLastError();   // callers may go on without the memory
+        if (optional || !give_back_work(c)) return e;
+    }
+}
+
+fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes, bool optional)
 {
     if (bytes == 0) bytes = 8;
     if (m->arena) {
         *p = m->arena->alloc(bytes);
         if (!*p) return fail(m->ctx, FE_ENOMEM, "arena: no room for %zu bytes", bytes);
     } else {
-        hipError_t e = hipMalloc(p, bytes);
+        const hipError_t e = dev_alloc(m->ctx, p, bytes, optional);
         if (e != hipSuccess) {
-            (void)hipGetLastError();   // callers may go on without the memory
             return fail(m->ctx, FE_ENOMEM, "hipMalloc(%zu) failed: %s", bytes, hipGetErrorString(e));
         }
     }
@@ -439,7 +472,7 @@ fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes)
     return FE_OK;
 }
 
-static void mesh_free_ptr(fe_mesh_s *m, void *p)
+void mesh_free_ptr(fe_mesh_s *m, void *p)
 {
     if (!p) return;
     auto it = std::find(m->allocs.begin(), m->allocs.end(), p);
@@ -845,7 +878,7 @@ static fe_status ensure_resident(fe_mesh_s *m)
     const size_t hw = ((size_t)N.G * kResidentHalo + N.G) * sizeof(int32_t);
     const size_t sw = kResidentSlots * sizeof(unsigned long long);
     void *p = nullptr;
-    fe_status s = mesh_alloc(m, &p, ow + sw + hw + 2 * sizeof(uint32_t));
+    fe_status s = mesh_alloc(m, &p, ow + sw + hw + 2 * sizeof(uint32_t), true);
     if (s == FE_ENOMEM) {
         Y = N;
         return FE_OK;
@@ -1170,11 +1203,19 @@ static fe_status mesh_upload(fe_ctx c, int stride, const uint8_t *types, int64_t
     auto *m = new fe_mesh_s();
     m->ctx = c;
     fe_status s = mesh_commit(m, *img, c->stream);
+    if (s == FE_ENOMEM && img->d.vec_T) {   // without what the gathers need: colour by colour
+        (void)hipStreamSynchronize(c->stream);
+        mesh_release(m);
+        m->bytes = 0;
+        img->d.vec_T = img->d.img_total = 0;
+        s = mesh_commit(m, *img, c->stream);
+    }
     if (s == FE_OK && hipStreamSynchronize(c->stream) != hipSuccess) s = fail(c, FE_EDEVICE, "upload sync failed");
     // The gathers' work arrays are laid out now rather than in the first call,
-    // which they would double.  No room: colour by colour.
+    // which they would double.  No room, now or for a later allocation of the
+    // context (give_back_work): colour by colour.
     const auto work = [&](double **p, size_t bytes) {
-        s = mesh_alloc(m, (void **)p, bytes);
+        s = mesh_alloc(m, (void **)p, bytes, true);
         if (s == FE_ENOMEM) {
             *p = nullptr;
             s = FE_OK;
@@ -1791,6 +1832,13 @@ fe_status fe_test_one_launch(fe_mesh m, double wait_us, double last_wait_us, int
     m->waits.limit = (unsigned long long)(wait_us * 100.0);
     m->waits.last_limit = (unsigned long long)(last_wait_us * 100.0);
     m->waits.stopped = stopped != 0;
+    return FE_OK;
+}
+
+fe_status fe_test_fail_allocs(fe_ctx c, int32_t n)
+{
+    if (!c || n < 0) return FE_EINVAL;
+    c->fail_allocs = n;
     return FE_OK;
 }
 

@@ -59,6 +59,7 @@ struct fe_ctx_s {
     double *scratch = nullptr;    // 2048 partials
     double *host = nullptr;       // pinned read-back area (64 doubles)
     bool profiling = false;
+    int fail_allocs = 0;          // device allocations that find no room (fe_test_fail_allocs)
     std::vector<fe_mesh_s *> meshes;   // live meshes, freed by fe_ctx_destroy
     feasm::ProfSlot prof[5];      // 0 CG SpMV + p.q, 1 assembly (all colours), 2 CG vector updates, 3 Dirichlet,
                                   // 4 element-vector pass (explicit step)
@@ -165,8 +166,13 @@ inline size_t image_bytes(const DevMesh &d) { return ((size_t)d.img_total + 3 * 
 // `stream`.  img must stay alive until the copies have completed.
 fe_status mesh_commit(fe_mesh_s *m, MeshImage &img, hipStream_t stream);
 // Device memory of m (through the arena when it has one).
-fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes);
+fe_status mesh_alloc(fe_mesh_s *m, void **p, size_t bytes, bool optional = false);
 void mesh_release(fe_mesh_s *m);
+void mesh_free_ptr(fe_mesh_s *m, void *p);
+// hipMalloc; without room, again once the context's meshes have given back
+// their gather work arrays, which only make calls faster (optional: this
+// memory does too, nothing is given back for it).
+hipError_t dev_alloc(fe_ctx_s *c, void **p, size_t bytes, bool optional = false);
 // Device bytes of the FP64 PCG work buffers for n unknowns and max_iter.
 size_t cg_bytes(int64_t n, int max_iter);
 fe_status ensure_cg(fe_mesh_s *m, int max_iter, bool mixed);

@@ -689,7 +689,7 @@ fe_status fe_serve_create(fe_ctx c, size_t hbm_budget, int32_t max_slots, int32_
     };
     bool ok = hipStreamCreateWithFlags(&S->stream, hipStreamNonBlocking) == hipSuccess &&
               hipEventCreateWithFlags(&S->poll_ev, hipEventDisableTiming) == hipSuccess &&
-              hipMalloc((void **)&S->arena_base, hbm_budget) == hipSuccess &&
+              dev_alloc(c, (void **)&S->arena_base, hbm_budget) == hipSuccess &&
               hipMalloc((void **)&S->jobs_d, kMaxBatch * sizeof(BatchJob)) == hipSuccess &&
               hipMalloc((void **)&S->flags_d, kMaxBatch * 4 * sizeof(int32_t)) == hipSuccess &&
               hipMalloc((void **)&S->res_d, kMaxBatch * kResDoubles * sizeof(double)) == hipSuccess &&
