@@ -59,8 +59,9 @@ typedef enum { FE_OP_MOMENTUM = 0, FE_OP_SCALAR = 1, FE_OP_POISSON = 2 } fe_oper
 #define FE_UPLOAD_RENUMBER 1u   /* reorder elements along a Morton curve, nodes by first touch */
 #define FE_UPLOAD_COLOURED 2u   /* single-type meshes: assemble the matrix operators with the coloured
                                  * element blocks (the serving runtime's form) instead of the owner groups
-                                 * (HEX08) or the blocks with a gather (the other types; always that of
-                                 * hybrid meshes); they agree to rounding order */
+                                 * (HEX08, and other types in an order of poor locality) or the blocks
+                                 * with a gather (the other types; always that of hybrid meshes); they
+                                 * agree to rounding order */
 #define FE_UPLOAD_GENERAL_SPMV 4u   /* fe_cg_solve runs the general SpMV on this mesh, in either precision,
                                      * and builds neither the symmetric one's map nor the plan of the
                                      * one-launch solves: for a mesh solved once or a few times,
@@ -108,12 +109,15 @@ fe_status fe_ctx_set_stream(fe_ctx ctx, void *hip_stream);
  * its device memory.  Part of it only makes calls faster: what the gathers of
  * the element-vector passes, and of the matrix assembly by blocks, add up (32
  * bytes per row of every element block, about 62 bytes per HEX08 element; for
- * the matrices 8 bytes per entry of every block's rows and 24 per row, 2.3 to
- * 3.6 times the matrix in an order of good locality).  Without room for it,
- * now or when a later allocation of the context finds none, it is left out or
- * freed, and the mesh assembles colour by colour.  The planner keeps its host temporaries on the calling
- * thread for the next upload while they total at most 256 MiB (meshes up to
- * about 100^3 hexahedra); larger ones are released before the call returns.
+ * the matrices 8 bytes per entry of every block's rows and 24 per row: mostly
+ * 2 to 4 times the matrix, at most 6.5 times on a mesh of one type, whose
+ * matrices assemble by owner groups beyond, and up to 15 times on a hybrid
+ * mesh in an order of poor locality).  Without room for it, now or when a
+ * later allocation of the context finds none, it is left out or freed, and the
+ * mesh assembles colour by colour.  The planner keeps its host temporaries on
+ * the calling thread for the next upload while they total at most 256 MiB
+ * (meshes up to about 100^3 hexahedra); larger ones are released before the
+ * call returns.
  */
 fe_status fe_mesh_upload(fe_ctx ctx, fe_elem_type type, int64_t n_nodes, const double *coords,
                          int64_t n_elems, const int32_t *conn, int64_t n_dirichlet,
@@ -539,7 +543,8 @@ fe_status fe_plan_export_color_blocks(fe_plan plan, int32_t *color_blocks);
  * Owner plan of the matrix assembly of a single-type mesh (Section 4.2's
  * element loop regrouped by the CSR rows it writes; fe_assemble runs it, its
  * tasks dealt to the wavefronts of each group, for MOMENTUM, SCALAR and
- * POISSON on HEX08 meshes uploaded without FE_UPLOAD_COLOURED).  Rows, in
+ * POISSON on HEX08 meshes uploaded without FE_UPLOAD_COLOURED, and as it is on
+ * those of the other types in an order of poor locality).  Rows, in
  * mesh numbering, are
  * cut into groups of consecutive rows; a work-group owns one group and
  * computes every element contribution to its rows.  A task is one lane's

@@ -7,7 +7,8 @@
 // once.  gfx950 form:
 //
 //   * matrix operators of a HEX08 mesh: owner groups (k_own), each CSR row
-//     computed whole by one work-group and written once;
+//     computed whole by one work-group and written once (k_own_copies: those of
+//     another type's mesh in an order of poor locality);
 //   * matrix operators of the other meshes and the element-vector passes:
 //     blocks of <= 64 spatially compact elements of one type, a block's row
 //     images (or nodal sums) to its own place in a work array, and a gather
@@ -1176,6 +1177,38 @@ __device__ inline int xcd_item(int b, int G)
     return x * q + (x < rem ? x : rem) + slot;
 }
 
+// A group's smallest det J and first element with det J <= 0 (or -1), by its
+// NT threads.
+template <int NT>
+__device__ __forceinline__ void group_status(double md, bool is_bad, long long elem, double *mindet, long long *first_bad)
+{
+    constexpr long long kNone = 0x7fffffffffffffffLL;
+    __shared__ double smd[NT / 64];
+    __shared__ long long sbad[NT / 64];
+    const int tid = threadIdx.x;
+    long long bad = is_bad ? elem : kNone;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        md = fmin(md, __shfl_xor(md, o));
+        const long long ob = __shfl_xor(bad, o);
+        bad = ob < bad ? ob : bad;
+    }
+    if ((tid & 63) == 0) {
+        smd[tid >> 6] = md;
+        sbad[tid >> 6] = bad;
+    }
+    __syncthreads();
+    if (tid == 0) {
+#pragma unroll
+        for (int w = 1; w < NT / 64; ++w) {
+            md = fmin(md, smd[w]);
+            bad = sbad[w] < bad ? sbad[w] : bad;
+        }
+        *mindet = md;
+        *first_bad = bad == kNone ? -1 : bad;
+    }
+}
+
 // NS: scalars at once (mixed FE_OP_SCALAR): the staging and the points' FP64
 // geometry, half of a pass, serve all of them: five scalars as 3 + 2 on 72^3 HEX08
 // 741 -> 569 us for the call (474 MB), the same results to the bit.
@@ -1313,31 +1346,122 @@ __global__ void __launch_bounds__(kOwnTasks, 2) k_own(OArgs k)
             k.rhs[(c * NRHS + h) * N + r0 + i] = rimg[q];
         }
     }
-    // status: the group's smallest det J and first element with det J <= 0
-    __shared__ double smd[kOwnTasks / 64];
-    __shared__ long long sbad[kOwnTasks / 64];
-    double md = live ? mindet : __builtin_huge_val();
-    long long bad = (live && !(mindet > 0.0)) ? (long long)elem : (long long)0x7fffffffffffffffLL;
+    group_status<kOwnTasks>(live ? mindet : __builtin_huge_val(), live && !(mindet > 0.0), elem, k.g_mindet + gi,
+                            k.g_bad + gi);
+}
+
+// The owner assembly of the other types, for meshes in an order of poor
+// locality (plan.h, max_images): a lane takes all rows of its element.  Their
+// nodes lie in many elements (24 for a Kuhn tetrahedron's), so that phases with
+// a barrier each would be as many: each wavefront adds into its own copy of the
+// rows, phases within the wavefront, and the copies are summed in their order.
+template <class EL, int OP, class Q>
+__global__ void __launch_bounds__(kOwnTasks, 2) k_own_copies(OArgs k)
+{
+    constexpr int NEN = EL::NEN, NC = kOwnTasks / 64;
+    constexpr int NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
+    extern __shared__ double lds[];
+    const int gi = xcd_item(blockIdx.x, gridDim.x);   // this work-group's group
+    const int4 gd = k.groups[gi];   // first task, tasks, first row, rows
+    const int tid = threadIdx.x;
+    const int r0 = gd.z, nr = gd.w;
+    const int n0 = k.node_ptr[gi], T = k.node_ptr[gi + 1] - n0;
+    const int64_t v0 = k.rowptr[r0];
+    const int L = (int)(k.rowptr[r0 + nr] - v0);
+    const int64_t N = k.N;
+    using FT = Q;
+    double *nd = lds;                   // [3][T] coordinates
+    FT *nf = (FT *)(nd + 3 * T);        // [NF - 3][T] u_x, u_y, u_z, rho, mu / Y
+    double *imgs = nd + 3 * T + ((NF - 3) * T * (int)sizeof(FT) + 7) / 8;   // [NC][L] the owned rows
+    double *rimgs = imgs + NC * L;      // [NC][NRHS][nr] their right-hand sides
+    double *img = imgs + (tid >> 6) * L, *rimg = rimgs + (tid >> 6) * NRHS * nr;
+
+    const bool live = tid < gd.y;
+    const int64_t t = gd.x + (live ? tid : 0);
+    Rows<EL> rows;
+    {
+        const uint16_t *lp = k.ln + t * k.ln_stride;
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-        md = fmin(md, __shfl_xor(md, o));
-        const long long ob = __shfl_xor(bad, o);
-        bad = ob < bad ? ob : bad;
+        for (int a = 0; a < NEN; ++a) rows.v[a] = lp[a];
     }
-    if ((tid & 63) == 0) {
-        smd[tid >> 6] = md;
-        sbad[tid >> 6] = bad;
+    constexpr int kOffWords = (NEN * NEN + 3) / 4;
+    uint32_t offw[kOffWords];
+    {
+        const uint32_t *op = (const uint32_t *)(k.off + t * k.off_stride);
+#pragma unroll
+        for (int q = 0; q < kOffWords; ++q) offw[q] = op[q];
+    }
+    const int ph = live ? (int)k.phase[t] : -1;
+    for (int q = tid; q < T; q += kOwnTasks) {
+        const int g = k.nodes[n0 + q];
+        double f[NF];
+        f[0] = k.X[g];
+        f[1] = k.X[N + g];
+        f[2] = k.X[2 * N + g];
+        f[3] = k.u[g];
+        f[4] = k.u[N + g];
+        f[5] = k.u[2 * N + g];
+        f[6] = k.rho[g];
+        if constexpr (NF > 7) f[7] = OP == OP_MOM ? k.mu[g] : k.Y[g];
+#pragma unroll
+        for (int c = 0; c < 3; ++c) nd[c * T + q] = f[c];
+#pragma unroll
+        for (int c = 3; c < NF; ++c) nf[(c - 3) * T + q] = FT(f[c]);
+    }
+    for (int q = tid; q < NC * L; q += kOwnTasks) imgs[q] = 0.0;
+    for (int q = tid; q < NC * NRHS * nr; q += kOwnTasks) rimgs[q] = 0.0;
+    __syncthreads();
+
+    Q A[NEN][NEN];
+    Q B[NRHS][NEN];
+#pragma unroll
+    for (int r = 0; r < NEN; ++r) {
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) A[r][b] = Q(0);
+#pragma unroll
+        for (int q = 0; q < NRHS; ++q) B[q][r] = Q(0);
+    }
+    double mindet = __builtin_huge_val();
+    if (live) {
+        Geo<EL> GE;
+        load_geo<EL>(nd, T, rows.v, GE);
+        gauss_loop<EL, OP, Q, NEN, 0, FT>(GE, nd, nf, T, rows, A, B, mindet, 1.0 / k.dt, k.D[0], 0);
+    }
+    int base[NEN];
+#pragma unroll
+    for (int r = 0; r < NEN; ++r) base[r] = rows.v[r] < nr ? (int)(k.rowptr[r0 + rows.v[r]] - v0) : -1;
+    const int nph = k.nphase[gi];
+    for (int p = 0; p < nph; ++p) {
+        if (ph != p) continue;
+#pragma unroll
+        for (int r = 0; r < NEN; ++r) {
+            if (base[r] < 0) continue;   // a row another group owns
+#pragma unroll
+            for (int b = 0; b < NEN; ++b) {
+                const int idx = r * NEN + b;
+                const int o = (offw[idx >> 2] >> (8 * (idx & 3))) & 0xff;
+                lds_add(&img[base[r] + o], (double)A[r][b]);
+            }
+#pragma unroll
+            for (int q = 0; q < NRHS; ++q) lds_add(&rimg[q * nr + rows.v[r]], (double)B[q][r]);
+        }
     }
     __syncthreads();
-    if (tid == 0) {
+    for (int q = tid; q < L; q += kOwnTasks) {
+        double v = imgs[q];
 #pragma unroll
-        for (int w = 1; w < kOwnTasks / 64; ++w) {
-            md = fmin(md, smd[w]);
-            bad = sbad[w] < bad ? sbad[w] : bad;
-        }
-        k.g_mindet[gi] = md;
-        k.g_bad[gi] = bad == 0x7fffffffffffffffLL ? -1 : bad;
+        for (int c = 1; c < NC; ++c) v += imgs[c * L + q];
+        k.values[v0 + q] = v;
     }
+    for (int q = tid; q < NRHS * nr; q += kOwnTasks) {
+        const int h = q / nr, i = q - h * nr;
+        double v = rimgs[q];
+#pragma unroll
+        for (int c = 1; c < NC; ++c) v += rimgs[c * NRHS * nr + q];
+        k.rhs[h * N + r0 + i] = v;
+    }
+    group_status<kOwnTasks>(live ? mindet : __builtin_huge_val(), live && !(mindet > 0.0), k.elem[t], k.g_mindet + gi,
+                            k.g_bad + gi);
 }
 
 template <int OP>
@@ -1345,6 +1469,26 @@ void launch_own_op(const OArgs &k, int64_t G, size_t lds, bool mixed, hipStream_
 {
     if (mixed) hipLaunchKernelGGL((k_own<OP, float>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
     else hipLaunchKernelGGL((k_own<OP, double>), dim3((unsigned)G), dim3(kOwnTasks), lds, s, k);
+}
+
+template <class EL>
+void launch_own_copies(const OArgs &k, int op, int64_t G, size_t lds, bool mixed, hipStream_t s)
+{
+    const dim3 grid((unsigned)G), block(kOwnTasks);
+    switch (op) {
+    case OP_MOM:
+        if (mixed) hipLaunchKernelGGL((k_own_copies<EL, OP_MOM, float>), grid, block, lds, s, k);
+        else hipLaunchKernelGGL((k_own_copies<EL, OP_MOM, double>), grid, block, lds, s, k);
+        break;
+    case OP_SCA:
+        if (mixed) hipLaunchKernelGGL((k_own_copies<EL, OP_SCA, float>), grid, block, lds, s, k);
+        else hipLaunchKernelGGL((k_own_copies<EL, OP_SCA, double>), grid, block, lds, s, k);
+        break;
+    default:
+        if (mixed) hipLaunchKernelGGL((k_own_copies<EL, OP_POI, float>), grid, block, lds, s, k);
+        else hipLaunchKernelGGL((k_own_copies<EL, OP_POI, double>), grid, block, lds, s, k);
+        break;
+    }
 }
 
 void launch_own(const OArgs &k, int op, int scalars, int64_t G, size_t lds, bool mixed, hipStream_t s)
@@ -2702,10 +2846,11 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
     if (a.op < 0 || a.op >= kNumOps) return hipErrorInvalidValue;
     KArgs k = make_kargs(a);
     AsmStatus *const out = a.status_out ? a.status_out : a.status;
-    if (a.scalars != 1 && (a.scalars < 1 || a.scalars > kOwnScalars || a.op != OP_SCA || !mixed || m.own_G <= 0))
+    if (a.scalars != 1 && (a.scalars < 1 || a.scalars > kOwnScalars || a.op != OP_SCA || !mixed || m.own_G <= 0 || m.nen != 8))
         return hipErrorInvalidValue;
     if (a.op < OP_RES && m.own_G > 0) {
-        // matrix operators of a HEX08 mesh: the owner assembly, one launch
+        // matrix operators of a HEX08 mesh, or another in poor order: the owner
+        // assembly, one launch
         OArgs o{};
         o.X = m.X;
         o.rowptr = m.rowptr;
@@ -2733,12 +2878,18 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
         o.g_mindet = k.blk_mindet;
         o.g_bad = k.blk_bad;
         const int nf = a.op == OP_POI ? 7 : 8, nrhs = a.op == OP_MOM ? 3 : 1;
-        if (m.nen != 8) return hipErrorInvalidValue;   // plan and kernel disagree
+        const int copies = m.nen == 8 ? 1 : kOwnTasks / 64;
         // x, y, z in FP64, the other fields in the quadrature's precision
         const size_t fb = mixed ? sizeof(float) : sizeof(double);
         const size_t fields = 3 * (size_t)m.own_max_nodes + ((nf - 4 + a.scalars) * (size_t)m.own_max_nodes * fb + 7) / 8;
-        const size_t lds = (fields + (size_t)m.own_max_img + nrhs * m.own_max_rows) * sizeof(double);
-        launch_own(o, a.op, a.scalars, m.own_G, lds, mixed, s);
+        const size_t lds = (fields + (size_t)copies * (m.own_max_img + nrhs * m.own_max_rows)) * sizeof(double);
+        switch (m.nen) {
+        case 8: launch_own(o, a.op, a.scalars, m.own_G, lds, mixed, s); break;
+        case 6: launch_own_copies<Pen>(o, a.op, m.own_G, lds, mixed, s); break;
+        case 5: launch_own_copies<Pyr>(o, a.op, m.own_G, lds, mixed, s); break;
+        case 4: launch_own_copies<Tet>(o, a.op, m.own_G, lds, mixed, s); break;
+        default: return hipErrorInvalidValue;
+        }
         const hipError_t err = hipGetLastError();
         if (err != hipSuccess) return err;
         if (!a.want_status) return hipSuccess;
@@ -2746,7 +2897,7 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
                            StatusArgs{k.blk_mindet, k.blk_bad, m.own_G, out});
         return hipGetLastError();
     }
-    if (a.op < OP_RES && a.img_work) {
+    if (a.op < OP_RES && a.img_work && m.img_total > 0) {
         // matrix operators of the other meshes: by blocks, then the gather
         k.color_blk = m.vec_blk;
         const PartArgs pa{m.blk_img_ptr, a.img_work, a.img_work + m.img_total, m.vec_T};

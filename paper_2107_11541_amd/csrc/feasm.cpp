@@ -184,11 +184,13 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
         return FE_EINVAL;
     }
     Plan &P = I.P;
-    // HEX08 meshes assemble by owner groups, every other by element blocks
+    // HEX08 meshes assemble by owner groups, every other by element blocks, or
+    // where that takes too many (max_images) and has one type by owner groups
     bool one_type = true;
     for (int64_t e = 1; types && e < n_elems && one_type; ++e) one_type = types[e] == types[0];
     const bool hex = one_type && (types && n_elems > 0 ? types[0] : stride) == 8;
     P.want_images = images && !hex && (owner_plan || !one_type);
+    P.bounded_images = one_type;
     P.want_gather = vector_passes || P.want_images;
     int st = build_plan(stride, types, n_nodes, coords, n_elems, conn, renumber, P, err);
     if (st != FE_OK) return st;
@@ -403,12 +405,13 @@ int mesh_prepare(int stride, const uint8_t *types, int64_t n_nodes, const double
     }
     d.hybrid = !P.etype.empty();
     d.img_total = P.blk_img_ptr.empty() ? 0 : P.blk_img_ptr.back();
-    // the owner plan of the matrix assembly (HEX08 meshes)
+    // the owner plan of the matrix assembly
     I.O = OwnerPlan();
-    if (owner_plan && hex) {
+    if (owner_plan && one_type && (hex || d.img_total == 0)) {
         st = build_owner_plan(P, I.O, err);
-        if (st != FE_OK) return st;
-        arrange_waves(I.O);
+        if (st != FE_OK && hex) return st;
+        if (st != FE_OK) I.O = OwnerPlan();   // colour by colour
+        if (hex) arrange_waves(I.O);
         const OwnerPlan &O = I.O;
         d.own_G = (int64_t)O.groups.size();
         d.own_T = (int64_t)O.tk_elem.size();
@@ -587,7 +590,7 @@ fe_status assemble_queue(fe_mesh_s *m, const fe_fields *f, fe_precision prec, do
     a.status_out = host_status(c);
     a.img_work = m->img_work;
     const int passes = f->op == FE_OP_SCALAR ? f->n_scalars : 1;
-    const bool several = f->op == FE_OP_SCALAR && prec == FE_MIXED && d.own_G > 0;
+    const bool several = f->op == FE_OP_SCALAR && prec == FE_MIXED && d.own_G > 0 && d.nen == 8;
     for (int k = 0; k < passes; k += a.scalars) {
         const int left = passes - k;
         a.scalars = !several ? 1 : left == 4 ? 2 : std::min(left, kOwnScalars);

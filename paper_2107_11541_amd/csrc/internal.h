@@ -60,7 +60,7 @@ struct DevMesh {
     // sentinel); roff holds each block's row offsets relative to its first
     // nonzero, rows + 1 entries at roff[first row + b]; lidx and cols the
     // block-local column indices and column sets (see SpmvMap).
-    // Owner plan of the matrix assembly (HEX08 meshes; own_G = 0
+    // Owner plan of the matrix assembly (HEX08 meshes, and others in poor order; own_G = 0
     // otherwise): groups {first task, tasks, first row, rows}, their touched
     // nodes (owned rows first), phases, and per task the element, the local
     // node of each (rotated) element node and the in-row column positions.

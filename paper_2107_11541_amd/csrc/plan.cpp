@@ -751,7 +751,8 @@ static int build_plan_impl(int S, const uint8_t *types, int64_t N, const double 
     // 8. places of the touched rows in the blocks' images laid end to end
     int64_t images = 0;
     for (int32_t n : P.blk_img) images += n;
-    if (P.want_gather && P.want_images && images <= INT32_MAX) {
+    if (P.want_gather && P.want_images && images <= INT32_MAX &&
+        (!P.bounded_images || (double)images <= max_images(nblk) * (double)P.nnz)) {
         P.blk_img_ptr.assign(nblk + 1, 0);
         for (int64_t b = 0; b < nblk; ++b) P.blk_img_ptr[b + 1] = P.blk_img_ptr[b] + P.blk_img[b];
         std::vector<int32_t> place(P.blk_nodes.size());

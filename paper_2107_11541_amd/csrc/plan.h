@@ -55,6 +55,22 @@ struct AsmSeg {
 // groups them: HEX08, PEN06, PYR05, TET04.
 inline int type_rank(int nen) { return nen == 8 ? 0 : nen == 6 ? 1 : nen == 5 ? 2 : 3; }
 
+// Images of a single-type mesh's blocks, in matrices, up to which the mesh
+// assembles by blocks with a gather, and beyond which, elements or nodes being
+// in an order of poor locality, by owner groups (which compute an element once
+// for each group that owns one of its rows).  FP64 momentum / mixed Poisson, us
+// by blocks against owner groups, elements and nodes shuffled within windows
+// of a Morton order: TET04 40^3 cubes, 3.5 matrices 64 / 53 against 81 / 58,
+// 5.3 72 / 59 against 87 / 61, 7.8 83 / 70 against 92 / 64, 22.7 (random order)
+// 225 / 179 against 115 / 83; PEN06 36^3 6.2 85 / 74 against 104 / 81, 11.3 144 /
+// 123 against 133 / 91; PYR05 30^3 4.5 78 / 72 against 104 / 73, 6.8 98 / 91
+// against 121 / 83.  Meshes of few blocks wait for the gather's chain instead:
+// TET04 16^3 3.2 28 / 26 against 28 / 26, 4.9 30 / 28 against 30 / 27, 20.5 45 /
+// 42 against 30 / 28; PYR05 10^3 3.9 36 / 36 against 35 / 34.  Renumbered meshes
+// hold 1.2 to 4.
+constexpr int64_t kFewBlocks = 512;
+constexpr double max_images(int64_t blocks) { return blocks < kFewBlocks ? 4.1 : 6.5; }
+
 struct Plan {
     int nen = 0;          // connectivity stride: nodes of the largest element type
     int off_stride = 0;   // bytes of elem_off per element (nen * nen rounded up to 4)
@@ -90,8 +106,9 @@ struct Plan {
     std::vector<int32_t> node_slot_ptr, node_slot;
     // the matrix gather (want_images): the blocks' row images one after the
     // other, block b's at blk_img_ptr[b]; node_img parallel to node_slot, the
-    // row's place in all images.  Left empty when they exceed 2^31 entries.
-    bool want_images = false;
+    // row's place in all images.  Left empty when they exceed 2^31 entries, or
+    // max_images times the matrix (0: any number).
+    bool want_images = false, bounded_images = false;
     std::vector<int32_t> blk_img_ptr, node_img;
     int n_colors = 0, max_T = 0, max_L = 0, max_phase = 0;
 
