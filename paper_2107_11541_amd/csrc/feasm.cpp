@@ -1352,7 +1352,6 @@ fe_status fe_assemble(fe_mesh m, const fe_fields *f, fe_precision prec, double *
 }
 
 // Builds and uploads the row-owner plan of the block operator (first use).
-constexpr size_t kPackedPlan = (size_t)4 << 20;
 static fe_status ensure_rowplan(fe_mesh_s *m)
 {
     fe_ctx_s *c = m->ctx;
@@ -1360,13 +1359,22 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     if (D.n_waves > 0) return FE_OK;
     if (m->conn_m.empty()) return fail(c, FE_EINVAL, "the mesh keeps no connectivity for the block operator");
     const DevMesh &d = m->dm;
-    std::vector<int32_t> rp(d.N + 1), ci(d.nnz);
-    HIPCALL(c, hipMemcpy(rp.data(), d.rowptr, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
-    HIPCALL(c, hipMemcpy(ci.data(), d.colidx, ci.size() * sizeof(int32_t), hipMemcpyDeviceToHost));
+    UnsetVector<int32_t> rp(d.N + 1), ci(d.nnz);
+    hipError_t fetched = hipSuccess;
+    const auto fetch = [&] {
+        fetched = hipMemcpy(rp.data(), d.rowptr, rp.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
+        if (fetched == hipSuccess)
+            fetched = hipMemcpy(ci.data(), d.colidx, ci.size() * sizeof(int32_t), hipMemcpyDeviceToHost);
+        if (fetched != hipSuccess) {   // an empty pattern, which ends the plan
+            std::fill(rp.begin(), rp.end(), 0);
+            std::fill(ci.begin(), ci.end(), 0);
+        }
+    };
     RowPlan R;
     std::string err;
     const uint8_t *et = m->etype_m.empty() ? nullptr : m->etype_m.data();
-    int st = build_row_plan(m->stride_m, et, d.N, d.E, m->conn_m.data(), rp.data(), ci.data(), R, err);
+    int st = build_row_plan(m->stride_m, et, d.N, d.E, m->conn_m.data(), rp.data(), ci.data(), R, err, fetch);
+    if (fetched != hipSuccess) return fail(c, FE_EDEVICE, "block plan: %s", hipGetErrorString(fetched));
     if (st != FE_OK) return fail(c, (fe_status)st, "%s", err.c_str());
     DevRowPlan P;
     P.n_tasks = R.n_tasks;
@@ -1383,14 +1391,10 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
         const void *src;
         size_t bytes;
     } parts[] = {{(void **)&P.etype, et, P.nen == 0 ? m->etype_m.size() : 0},
-                 {(void **)&P.task_meta, R.task_meta.data(), R.task_meta.size() * sizeof(uint32_t)},
-                 {(void **)&P.task_perm, R.task_perm.data(), R.task_perm.size() * sizeof(uint32_t)},
-                 {(void **)&P.task_cols, R.task_cols.data(), R.task_cols.size()},
+                 {(void **)&P.task_meta, R.tasks.data(), R.tasks.size()},
+                 {(void **)&P.wave_ln, R.lists.data(), R.lists.size()},
                  {(void **)&P.wdesc, R.wdesc.data(), R.wdesc.size() * sizeof(RowWave)},
                  {(void **)&P.wlists, R.wlists.data(), R.wlists.size() * sizeof(RowLists)},
-                 {(void **)&P.wave_elem, R.wave_elem.data(), R.wave_elem.size() * sizeof(int32_t)},
-                 {(void **)&P.wave_node, R.wave_node.data(), R.wave_node.size() * sizeof(int32_t)},
-                 {(void **)&P.wave_ln, R.wave_ln.data(), R.wave_ln.size() * sizeof(uint16_t)},
                  {(void **)&P.w_mindet, nullptr, (size_t)P.n_waves * sizeof(double)},
                  {(void **)&P.w_bad, nullptr, (size_t)P.n_waves * sizeof(long long)}};
     size_t total = 0;
@@ -1398,19 +1402,17 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     char *base = nullptr;
     fe_status s = mesh_alloc(m, (void **)&base, total);
     if (s != FE_OK) return s;
-    // small plans in one copy (each takes ~20 us)
-    std::vector<char> packed(total <= kPackedPlan ? total : 0);
     size_t at = 0;
     hipError_t e = hipSuccess;
     for (const Part &q : parts) {
         *q.dst = base + at;
-        if (q.src && q.bytes && e == hipSuccess) {
-            if (packed.empty()) e = hipMemcpyAsync(*q.dst, q.src, q.bytes, hipMemcpyHostToDevice, c->stream);
-            else memcpy(packed.data() + at, q.src, q.bytes);
-        }
+        if (q.src && q.bytes && e == hipSuccess) e = hipMemcpyAsync(*q.dst, q.src, q.bytes, hipMemcpyHostToDevice, c->stream);
         at += DevArena::round(q.bytes);
     }
-    if (!packed.empty()) e = hipMemcpyAsync(base, packed.data(), total, hipMemcpyHostToDevice, c->stream);
+    P.task_perm = P.task_meta + R.n_tasks;
+    P.task_cols = (uint8_t *)(P.task_perm + R.n_tasks);
+    P.wave_elem = (int32_t *)(P.wave_ln + 8 * R.n_elems);
+    P.wave_node = P.wave_elem + R.n_elems;
     const hipError_t e2 = hipStreamSynchronize(c->stream);   // the host arrays end here
     if (e == hipSuccess) e = e2;
     if (e != hipSuccess) {

@@ -180,24 +180,36 @@ template <class T> struct UnsetAllocator : std::allocator<T> {
 template <class T> using UnsetVector = std::vector<T, UnsetAllocator<T>>;
 
 struct RowPlan {
-    int64_t n_tasks = 0, max_img = 0, max_items = 0, max_nodes = 0;
+    int64_t n_tasks = 0, n_elems = 0, n_nodes = 0;   // entries of the arrays below
+    int64_t max_img = 0, max_items = 0, max_nodes = 0;
     int lanes = 0;                     // of a group
     int nen = 0;                       // nodes per element, 0 for several types: then the groups of several,
     int32_t class_end[4] = {};         // HEX08, PYR05 and PEN06 alone, each to its end, before TET04's
-    UnsetVector<uint32_t> task_meta;   // [T] group's element (bits 0-7) | local row a (8-10) | group's row (11-18) | round (19-30)
-    UnsetVector<uint32_t> task_perm;   // [T] slot s adds node (perm >> 4 s) & 15, 8 = none
-    UnsetVector<uint8_t> task_cols;    // [T][8] slot s: its node's position in the row
-    std::vector<RowWave> wdesc;        // [groups]
-    std::vector<RowLists> wlists;      // [groups] places in the next three
-    UnsetVector<int32_t> wave_elem, wave_node;
-    UnsetVector<uint16_t> wave_ln;     // [listed elements][8] the group's node of each element node
+    std::vector<RowWave> wdesc;        // [groups]; between their tasks entries may be unused
+    std::vector<RowLists> wlists;      // [groups] places in the listed elements and nodes
+    // The large arrays in two pieces, as they go to the device.
+    UnsetVector<char> tasks;
+    const uint32_t *task_meta() const   // group's element (bits 0-7) | local row a (8-10) | group's row (11-18) | round (19-30)
+    {
+        return (const uint32_t *)tasks.data();
+    }
+    const uint32_t *task_perm() const { return task_meta() + n_tasks; }   // slot s adds node (perm >> 4 s) & 15, 8 = none
+    const uint8_t *task_cols() const { return (const uint8_t *)(task_perm() + n_tasks); }   // [8] slot s: its node's position in the row
+    static size_t task_bytes(int64_t n) { return 16 * (size_t)n; }
+    UnsetVector<char> lists;
+    const uint16_t *wave_ln() const { return (const uint16_t *)lists.data(); }   // [8] the group's node of each element node
+    const int32_t *wave_elem() const { return (const int32_t *)(wave_ln() + 8 * n_elems); }
+    const int32_t *wave_node() const { return wave_elem() + n_elems; }
+    static size_t list_bytes(int64_t elems, int64_t nodes) { return 20 * (size_t)elems + 4 * (size_t)nodes; }
 };
 // conn [E][stride] and rowptr/colidx in mesh numbering; etype [E] node
 // counts or NULL (every element has stride nodes).  0 or an fe_status code
 // with a message in err (FE_EBADMESH: a node in more than kRowElemsMax
-// elements).
+// elements).  fetch: fills rowptr and colidx, on the calling thread while
+// others plan what needs neither.
 int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const int32_t *conn,
-                   const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err);
+                   const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err,
+                   const std::function<void()> &fetch = nullptr);
 
 // Owner plan of the matrix assembly (rowplan.cpp): the CSR rows are cut
 // into groups of consecutive rows (mesh numbering, so spatially compact);

@@ -15,7 +15,12 @@
 //     each adds its element's nodes is an edge colouring of the bipartite
 //     graph (tasks, columns), so no two add to one column in one step.
 #include <algorithm>
+#include <array>
+#include <atomic>
+#include <climits>
+#include <cstdlib>
 #include <cstring>
+#include <memory>
 #include <string>
 #include <thread>
 #include <vector>
@@ -29,45 +34,101 @@ namespace {
 
 // The slots and rounds of one row's tasks.  Tasks are taken in order, up to D
 // to a round while no column occurs more than D times in it; D colours (slots)
-// then suffice (Koenig's theorem), found edge by edge, exchanging two colours
-// along a path where an edge's ends share no free one.
+// then suffice (Koenig's theorem).  Where every task may take its nodes in
+// their own order (a row of HEX08 elements of one orientation) it does; else
+// the slots are found edge by edge, exchanging two colours along a path where
+// an edge's ends share no free one, and kept for the next round whose tasks
+// share columns in the same way (a mesh repeats few such patterns).
 class RowSlots {
   public:
     // D: the most nodes of the row's elements; cols_of [nt][8]: the columns (positions in the row) of each task's nen nodes
-    void row(int D, int nt, const uint8_t *cols_of, const uint8_t *nen, uint32_t *perm, uint8_t *cols, uint8_t *round)
+    void row(int D, int nt, const uint8_t *cols_of, const uint8_t *nen, uint32_t *perm, uint8_t *round)
     {
-        D_ = D;
         int t0 = 0, r = 0;
         while (t0 < nt) {
-            int m = 0;
-            for (; t0 + m < nt && m < D_; ++m) {
-                const uint8_t *c = cols_of + 8 * (t0 + m);
-                int b = 0;
-                for (; b < nen[t0 + m]; ++b)
-                    if (++mult_[c[b]] > D_) break;
-                if (b < nen[t0 + m]) {
-                    for (; b >= 0; --b) --mult_[c[b]];
-                    break;
-                }
+            int m = std::min(nt - t0, D);
+            if (!in_order(m, cols_of + 8 * t0, nen + t0, perm + t0)) {
+                m = pattern(D, m, cols_of + 8 * t0, nen + t0);
+                const Known &k = known(D, m, nen + t0);
+                std::copy(k.perm, k.perm + m, perm + t0);
             }
-            colour(m, cols_of + 8 * t0, nen + t0);
-            for (int i = 0; i < m; ++i) {
-                const uint8_t *c = cols_of + 8 * (t0 + i);
-                perm[t0 + i] = 0;
-                for (int q = 0; q < 8; ++q) {
-                    const int b = q < D_ ? at_task_[i][q] : -1;
-                    perm[t0 + i] |= (uint32_t)(b < 0 ? 8 : b) << (4 * q);
-                    cols[8 * (t0 + i) + q] = b < 0 ? 0 : c[b];
-                }
-                round[t0 + i] = (uint8_t)r;
-                for (int b = 0; b < nen[t0 + i]; ++b) mult_[c[b]] = used_[c[b]] = 0;
-            }
+            std::fill_n(round + t0, m, (uint8_t)r);
             t0 += m;
             ++r;
         }
     }
 
   private:
+    // Slot b takes node b, if that gives no column twice in one slot.
+    bool in_order(int m, const uint8_t *cols_of, const uint8_t *nen, uint32_t *perm)
+    {
+        const uint32_t gen = next_gen();
+        for (int i = 0; i < m; ++i)
+            for (int b = 0; b < nen[i]; ++b) {
+                uint32_t &s = seen_[cols_of[8 * i + b]];
+                if (s >> 8 != gen) s = gen << 8;
+                if (s >> b & 1) return false;
+                s |= 1u << b;
+            }
+        for (int i = 0; i < m; ++i) perm[i] = nen[i] == 8 ? 0x76543210u : 0x76543210u | 0x88888888u << (4 * nen[i]);
+        return true;
+    }
+    // The first tasks of the m in which no column occurs more than D times
+    // (their number is returned), their columns by first appearance in key_.
+    int pattern(int D, int m, const uint8_t *cols_of, const uint8_t *nen)
+    {
+        const uint32_t gen = next_gen();
+        int labels = 0;
+        for (int i = 0; i < m; ++i) {
+            uint8_t *k = reinterpret_cast<uint8_t *>(key_) + 8 * i;
+            key_[i] = ~(uint64_t)0;
+            for (int b = 0; b < nen[i]; ++b) {
+                uint32_t &s = seen_[cols_of[8 * i + b]];
+                if (s >> 8 != gen) {
+                    s = gen << 8 | (uint32_t)labels;
+                    times_[labels++] = 0;
+                }
+                k[b] = (uint8_t)s;
+                if (++times_[k[b]] > D) return i;
+            }
+        }
+        return m;
+    }
+    uint32_t next_gen()
+    {
+        if (++gen_ == 1u << 24) {
+            std::fill(seen_, seen_ + 256, 0u);
+            gen_ = 1;
+        }
+        return gen_;
+    }
+    struct Known {
+        uint64_t key[8];
+        uint32_t perm[8];
+        int m = 0, D = 0;
+    };
+    const Known &known(int D, int m, const uint8_t *nen)
+    {
+        uint64_t h = (uint64_t)(8 * D + m);
+        for (int i = 0; i < m; ++i) h = (h ^ key_[i]) * 0x9e3779b97f4a7c15ull, h ^= h >> 29;
+        Known &k = known_[h >> 56];
+        if (k.m == m && k.D == D && memcmp(k.key, key_, m * sizeof(uint64_t)) == 0) return k;
+        D_ = D;
+        const uint8_t *cols = reinterpret_cast<const uint8_t *>(key_);
+        memset(used_, 0, sizeof used_);
+        colour(m, cols, nen);
+        for (int i = 0; i < m; ++i) {
+            k.key[i] = key_[i];
+            k.perm[i] = 0;
+            for (int q = 0; q < 8; ++q) {
+                const int b = q < D ? at_task_[i][q] : -1;
+                k.perm[i] |= (uint32_t)(b < 0 ? 8 : b) << (4 * q);
+            }
+        }
+        k.m = m;
+        k.D = D;
+        return k;
+    }
     void colour(int m, const uint8_t *cols_of, const uint8_t *nen)
     {
         const unsigned all = (1u << D_) - 1;
@@ -119,214 +180,408 @@ class RowSlots {
         }
     }
     int D_ = 8;
-    int8_t at_task_[8][8], at_col_[256][8];   // a task's node, a column's task in each slot
-    uint8_t used_[256] = {};                  // a column's slots (which at_col_ holds)
-    uint8_t mult_[256] = {};
+    int8_t at_task_[8][8], at_col_[64][8];   // a task's node, a column's task in each slot
+    uint8_t used_[64];                       // a column's slots (which at_col_ holds)
+    uint8_t times_[64];
+    uint64_t key_[8];
+    uint32_t seen_[256] = {}, gen_ = 0;      // per column: the round that saw it, then its slots or label
+    Known known_[256];
+};
+
+// nt threads that run f(w, team) together; barrier() waits for all of them.
+class Team {
+  public:
+    explicit Team(int n) : n_(n) {}
+    int size() const { return n_; }
+    void barrier()
+    {
+        const unsigned now = turn_.load(std::memory_order_acquire);
+        if (here_.fetch_add(1, std::memory_order_acq_rel) + 1 == n_) {
+            here_.store(0, std::memory_order_relaxed);
+            turn_.store(now + 1, std::memory_order_release);
+        } else {
+            while (turn_.load(std::memory_order_acquire) == now) std::this_thread::yield();
+        }
+    }
+    template <class F> static void run(int n, F f)
+    {
+        Team team(n);
+        start(0, n, team, f);
+    }
+
+  private:
+    // Threads [lo, hi): each starts the upper half of what is left to it, since
+    // starting one takes 10 us.
+    template <class F> static void start(int lo, int hi, Team &team, F &f)
+    {
+        std::vector<std::thread> th;
+        while (hi - lo > 1) {
+            const int mid = (lo + hi + 1) / 2;
+            th.emplace_back([mid, hi, &team, &f] { start(mid, hi, team, f); });
+            hi = mid;
+        }
+        f(lo, team);
+        for (auto &t : th) t.join();
+    }
+    const int n_;
+    std::atomic<int> here_{0};
+    std::atomic<unsigned> turn_{0};
+};
+
+// An element's or node's place in the lists of group `group` (counted from 1).
+struct Placed {
+    uint32_t group, place;
+};
+// n zeros, of which the pages that are never touched cost nothing.
+template <class T> class Zeros {
+  public:
+    explicit Zeros(size_t n) : p_((T *)std::calloc(std::max<size_t>(n, 1), sizeof(T)))
+    {
+        if (!p_) throw std::bad_alloc();
+    }
+    Zeros(const Zeros &) = delete;
+    ~Zeros() { std::free(p_); }
+    T &operator[](size_t i) { return p_[i]; }
+
+  private:
+    T *p_;
+};
+
+// What one thread plans: the groups of its rows, the places in their lists
+// counted from 0.  (The tasks go straight to the plan's arrays.)
+struct alignas(64) RowPart {
+    std::vector<RowWave> wdesc;
+    std::vector<RowLists> wlists;
+    std::vector<uint8_t> cls;   // a group's element type, 0 for several
+    UnsetVector<int32_t> elem, node;              // of which n_elems and n_nodes are used
+    UnsetVector<std::array<uint16_t, 8>> ln;
+    int64_t n_elems = 0, n_nodes = 0;
+    int64_t max_img = 0, max_items = 0, max_nodes = 0, too_many = -1;
+    bool failed = false;
+};
+
+// The groups of rows [r0, r1): their lanes, elements and nodes.
+struct RowGrouping {
+    int stride, lanes;
+    const uint8_t *etype;
+    const int32_t *conn, *rowptr, *colidx, *inc_ptr;
+    const uint32_t *inc;   // 8 element + local row, by row
+    uint32_t *meta, *perm;   // the plan's arrays
+    uint64_t *cols;
+    int nen_of(int64_t e) const { return etype ? (int)etype[e] : stride; }
+
+    // Lanes that the tasks of rows [r0, r1) take at most: a round of m <= 8 may
+    // leave m - 1 lanes of a wavefront idle.
+    int64_t most_lanes(int64_t r0, int64_t r1) const
+    {
+        const int64_t n = inc_ptr[r1] - inc_ptr[r0];
+        return n + 7 * (n / 57 + 1);
+    }
+
+    // first: where this range's tasks start
+    // (What a thread fills step by step it allocates itself: page faults of
+    // several threads in one mapping hold each other up.)
+    void run(int64_t N, int64_t E, int64_t r0, int64_t r1, int64_t first, RowPart &P) const
+    {
+        const auto slots = std::make_unique<RowSlots>();
+        Zeros<Placed> elems(E), nodes(N);
+        Zeros<int32_t> at(N);   // a column's position in its row
+        const size_t tasks = (size_t)(inc_ptr[r1] - inc_ptr[r0]);
+        P.elem.resize(tasks / 2 + 8);
+        P.ln.resize(tasks / 2 + 8);
+        P.node.resize(tasks / 2 + 8);
+        uint32_t gid = 1;       // the open group
+        const int64_t last = first + most_lanes(r0, r1);
+        uint8_t of[kRowElemsMax * 8], nen[kRowElemsMax], round[kRowElemsMax];
+        uint32_t slots_of[kRowElemsMax];
+        int lane[kRowElemsMax];
+        RowWave g{(int32_t)first, 0, (int32_t)r0, 0};
+        RowLists l{0, 0, 0, 0};
+        int p = 0, type = -1;   // the open group's next lane; its elements' type
+        const auto close = [&](int64_t row) {
+            if (row == g.first_row) return;
+            g.n_rows = (int32_t)(row - g.first_row);
+            g.n_tasks = p;
+            P.wdesc.push_back(g);
+            P.wlists.push_back(l);
+            P.cls.push_back((uint8_t)std::max(type, 0));
+            P.max_img = std::max<int64_t>(P.max_img, 9 * (int64_t)(rowptr[row] - rowptr[g.first_row]));
+            P.max_items = std::max<int64_t>(P.max_items, (int64_t)l.n_elems * row_points(l.n_elems, lanes));
+            P.max_nodes = std::max<int64_t>(P.max_nodes, l.n_nodes);
+            ++gid;
+            g = {g.first_task + p, 0, (int32_t)row, 0};
+            l = {(int32_t)P.n_elems, 0, (int32_t)P.n_nodes, 0};
+            p = 0;
+            type = -1;
+        };
+        for (int64_t row = r0; row < r1; ++row) {
+            const int32_t *c0 = colidx + rowptr[row];
+            const int32_t len = std::min(rowptr[row + 1] - rowptr[row], 256);
+            for (int32_t q = 0; q < len; ++q) at[c0[q]] = q;
+            const uint32_t *t0 = inc + inc_ptr[row];
+            const int nt = inc_ptr[row + 1] - inc_ptr[row];
+            int D = 1;
+            for (int t = 0; t < nt; ++t) {
+                const int64_t e = t0[t] >> 3;
+                const int32_t *ce = conn + e * stride;
+                const int n = nen_of(e);
+                nen[t] = (uint8_t)n;
+                D = std::max(D, n);
+                for (int b = 0; b < n; ++b) {
+                    const int32_t j = ce[b], q = at[j];
+                    if (q < 0 || q >= len || c0[q] != j) {
+                        P.failed = true;
+                        return;
+                    }
+                    of[8 * t + b] = (uint8_t)q;
+                }
+            }
+            if (nt > 0) slots->row(D, nt, of, nen, slots_of, round);
+            // Lanes of the row's tasks from lane q on: a round's tasks lie in one
+            // wavefront, so that they add in step.
+            const auto lanes_from = [&](int q) {
+                for (int t = 0; t < nt;) {
+                    int m = 1;
+                    while (t + m < nt && round[t + m] == round[t]) ++m;
+                    if (q % 64 + m > 64) q = (q + 63) / 64 * 64;
+                    for (int i = 0; i < m; ++i) lane[t + i] = q++;
+                    t += m;
+                }
+                return q;
+            };
+            int next = lanes_from(p);
+            const int64_t img = 9 * (int64_t)(rowptr[row + 1] - rowptr[g.first_row]);
+            if (row > g.first_row && (next > lanes || img > row_image(lanes) || row - g.first_row >= lanes)) {
+                close(row);
+                next = lanes_from(0);
+            }
+            if (g.first_task + next > last) {   // cannot happen
+                P.failed = true;
+                return;
+            }
+            for (int q = p, t = 0; q < next; ++q) {   // idle lanes between the rounds
+                if (t < nt && lane[t] == q) {
+                    ++t;
+                    continue;
+                }
+                meta[g.first_task + q] = kRowNoTask;
+                perm[g.first_task + q] = 0x88888888u;
+                cols[g.first_task + q] = 0;
+            }
+            const uint32_t row_bits = (uint32_t)(row - g.first_row) << 11;
+            for (int t = 0; t < nt; ++t) {
+                const int64_t e = t0[t] >> 3;
+                Placed &pe = elems[e];
+                if (pe.group != gid) {
+                    pe = {gid, (uint32_t)l.n_elems++};
+                    if ((size_t)P.n_elems == P.elem.size()) {
+                        P.elem.resize(2 * P.elem.size());
+                        P.ln.resize(P.elem.size());
+                    }
+                    if ((size_t)P.n_nodes + 8 > P.node.size()) P.node.resize(2 * P.node.size());
+                    const int32_t *ce = conn + e * stride;
+                    int32_t *const list = P.node.data() + P.n_nodes;
+                    std::array<uint16_t, 8> &ln = P.ln[P.n_elems];
+                    int n = 0;
+                    for (int b = 0; b < nen[t]; ++b) {   // (whether a node is new is unpredictable: no branch)
+                        Placed &pn = nodes[ce[b]];
+                        const bool is_new = pn.group != gid;
+                        list[n] = ce[b];
+                        pn = {gid, is_new ? (uint32_t)(l.n_nodes + n) : pn.place};
+                        ln[b] = (uint16_t)pn.place;
+                        n += is_new;
+                    }
+                    for (int b = nen[t]; b < 8; ++b) ln[b] = 0;
+                    P.elem[P.n_elems++] = (int32_t)e;
+                    P.n_nodes += n;
+                    l.n_nodes += n;
+                    type = type < 0 ? nen[t] : type == nen[t] ? type : 0;
+                }
+                uint64_t c;
+                if (slots_of[t] == 0x76543210u) {
+                    memcpy(&c, of + 8 * t, 8);
+                } else {
+                    c = 0;
+                    for (int q = 0; q < D; ++q) {
+                        const uint32_t b = slots_of[t] >> (4 * q) & 15;
+                        c |= (uint64_t)(b < 8 ? of[8 * t + b] : 0) << (8 * q);
+                    }
+                }
+                const size_t d = (size_t)g.first_task + lane[t];
+                meta[d] = pe.place | (t0[t] & 7) << 8 | row_bits | (uint32_t)round[t] << 19 |
+                                (t == 0 ? kRowFirstTask : 0u);
+                perm[d] = slots_of[t];
+                cols[d] = c;
+            }
+            p = next;
+        }
+        close(r1);
+    }
 };
 
 }  // namespace
 
 int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const int32_t *conn,
-                   const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err)
+                   const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err,
+                   const std::function<void()> &fetch)
 {
     R = RowPlan();
     auto nen_of = [&](int64_t e) { return etype ? (int)etype[e] : stride; };
-    // node -> element incidence, elements ascending
-    std::vector<int32_t> inc_ptr(N + 1, 0);
-    for (int64_t e = 0; e < E; ++e)
-        for (int a = 0; a < nen_of(e); ++a) ++inc_ptr[conn[e * stride + a] + 1];
-    for (int64_t i = 0; i < N; ++i) {
-        if (inc_ptr[i + 1] > kRowElemsMax) {
-            err = "node " + std::to_string(i) + " (mesh numbering) lies in " + std::to_string(inc_ptr[i + 1]) +
-                  " elements; the block operator's row-owner assembly takes at most " +
-                  std::to_string(kRowElemsMax);
-            return FE_EBADMESH;
-        }
-        inc_ptr[i + 1] += inc_ptr[i];
+    int64_t T = E * stride;
+    if (etype) {
+        T = 0;
+        for (int64_t e = 0; e < E; ++e) T += etype[e];
     }
-    const int64_t T = inc_ptr[N];
+    if (T > INT32_MAX) {
+        err = "the block operator's plan holds at most 2^31 element nodes";
+        return FE_EBADMESH;
+    }
     R.lanes = T < kRowSmallMesh ? kRowTasksSmall : kRowTasks;
-    UnsetVector<int32_t> task_elem(T);
-    UnsetVector<uint8_t> task_row(T);   // local row a
-    {
-        std::vector<int32_t> fill(inc_ptr.begin(), inc_ptr.end() - 1);
-        for (int64_t e = 0; e < E; ++e)
-            for (int a = 0; a < nen_of(e); ++a) {
-                const int32_t t = fill[conn[e * stride + a]]++;
-                task_elem[t] = (int32_t)e;
-                task_row[t] = (uint8_t)a;
-            }
-    }
-    // the rows' slots, in tasks order
-    UnsetVector<uint32_t> perm(T);
-    UnsetVector<uint8_t> cols((size_t)T * 8), round(T);
-    constexpr int64_t kRows = 512;   // per chunk
-    const int64_t CR = (N + kRows - 1) / kRows;
-    std::vector<uint8_t> missing(CR, 0);
-    std::vector<std::vector<int32_t>> place(parallel_workers(CR));   // per worker, [N]: a column's position
-    parallel_chunks_w(CR, [&](int64_t c, int wk) {
-        RowSlots slots;
-        uint8_t of[kRowElemsMax * 8], nen[kRowElemsMax];
-        std::vector<int32_t> &at = place[wk];
-        at.resize(N);
-        for (int64_t row = c * kRows; row < std::min(N, (c + 1) * kRows); ++row) {
-            const int32_t *c0 = colidx + rowptr[row];
-            const int32_t len = std::min(rowptr[row + 1] - rowptr[row], 256);
-            for (int32_t p = 0; p < len; ++p) at[c0[p]] = p;
-            const int32_t t0 = inc_ptr[row];
-            const int nt = inc_ptr[row + 1] - t0;
-            int D = 1;
-            for (int t = 0; t < nt; ++t) {
-                const int64_t e = task_elem[t0 + t];
-                nen[t] = (uint8_t)nen_of(e);
-                D = std::max<int>(D, nen[t]);
-                for (int b = 0; b < nen[t]; ++b) {
-                    const int32_t j = conn[e * stride + b], p = at[j];
-                    if (p < 0 || p >= len || c0[p] != j) missing[c] = 1;
-                    of[8 * t + b] = (uint8_t)p;
+    R.nen = !etype ? stride : std::all_of(etype, etype + E, [&](uint8_t n) { return n == etype[0]; }) ? etype[0] : 0;
+    // One team of threads for all stages (starting one takes up to 0.1 ms);
+    // each plans a range of rows on its own.  First calls with 8192 / 12288
+    // tasks to a thread at least, ms: HEX08 16^3 0.55 / 0.82, 24^3 0.95 / 1.06,
+    // TET04 13^3 cubes 0.64 / 0.74, 24^3 2.5 / 2.8.
+    constexpr int64_t kTasksPerThread = 8192, kScan = 64;
+    const int nt = (int)std::max<int64_t>(1, std::min<int64_t>(host_threads(), T / kTasksPerThread));
+    const int64_t scans = (E + kScan - 1) / kScan;
+    UnsetVector<int32_t> inc_ptr(N + 1), lo(scans), hi(scans);
+    UnsetVector<uint32_t> inc(T);
+    std::vector<RowPart> part(nt);
+    std::vector<int64_t> total(nt, 0);
+    struct Offsets {
+        int64_t group, elem, node;
+    };
+    std::vector<Offsets> off(nt + 1, Offsets{0, 0, 0});
+    std::vector<int64_t> first(nt + 1, 0);   // each thread's tasks in the plan
+    int status = FE_OK;   // set by thread 0 alone
+    Team::run(nt, [&](int w, Team &team) {
+        const auto begin = [&](int64_t n) { return n * w / nt; };
+        const auto end = [&](int64_t n) { return n * (w + 1) / nt; };
+        if (w == 0 && fetch) fetch();
+        // the nodes of every kScan elements lie in [lo, hi]
+        for (int64_t s = begin(scans); s < end(scans); ++s) {
+            int32_t a = INT32_MAX, b = -1;
+            for (int64_t e = s * kScan; e < std::min(E, (s + 1) * kScan); ++e)
+                for (int q = 0; q < nen_of(e); ++q) {
+                    a = std::min(a, conn[e * stride + q]);
+                    b = std::max(b, conn[e * stride + q]);
+                }
+            lo[s] = a;
+            hi[s] = b;
+        }
+        team.barrier();
+        // node -> (element, local row), ascending: this thread's rows, counted, then filled
+        const int64_t r0 = begin(N), r1 = end(N);
+        const uint32_t rows = (uint32_t)(r1 - r0);
+        const auto each = [&](auto f) {
+            for (int64_t s = 0; s < scans; ++s) {
+                if (hi[s] < r0 || lo[s] >= r1) continue;
+                for (int64_t e = s * kScan; e < std::min(E, (s + 1) * kScan); ++e) {
+                    const int n = nen_of(e);
+                    for (int q = 0; q < n; ++q) {
+                        const uint32_t i = (uint32_t)(conn[e * stride + q] - (int32_t)r0);
+                        if (i < rows) f(i, (uint32_t)(8 * e + q));
+                    }
                 }
             }
-            if (nt > 0 && !missing[c]) slots.row(D, nt, of, nen, &perm[t0], &cols[(size_t)t0 * 8], &round[t0]);
+        };
+        std::vector<int32_t> fill(rows, 0);
+        each([&](uint32_t i, uint32_t) { ++fill[i]; });
+        for (uint32_t i = 0; i < rows; ++i) {
+            if (fill[i] > kRowElemsMax && part[w].too_many < 0) part[w].too_many = r0 + i;
+            total[w] += fill[i];
+        }
+        team.barrier();
+        int64_t at = 0;
+        bool ok = true;
+        for (int v = 0; v < nt; ++v) {
+            if (v < w) at += total[v];
+            ok = ok && part[v].too_many < 0;
+        }
+        if (!ok) return;   // (every thread alike)
+        if (w == 0) inc_ptr[0] = 0;
+        for (uint32_t i = 0; i < rows; ++i) {
+            const int32_t n = fill[i];
+            fill[i] = (int32_t)at;
+            inc_ptr[r0 + i + 1] = (int32_t)(at += n);
+        }
+        each([&](uint32_t i, uint32_t x) { inc[fill[i]++] = x; });
+        team.barrier();
+        RowPart &P = part[w];
+        RowGrouping G{stride, R.lanes, etype, conn, rowptr, colidx, inc_ptr.data(), inc.data(), nullptr, nullptr, nullptr};
+        if (w == 0) {
+            for (int v = 0; v < nt; ++v) first[v + 1] = first[v] + G.most_lanes(N * v / nt, N * (v + 1) / nt);
+            R.n_tasks = first[nt];
+            if (R.n_tasks <= INT32_MAX) R.tasks.resize(RowPlan::task_bytes(R.n_tasks));
+            else status = FE_EBADMESH;
+        }
+        team.barrier();
+        if (status != FE_OK) return;
+        G.meta = const_cast<uint32_t *>(R.task_meta());
+        G.perm = const_cast<uint32_t *>(R.task_perm());
+        G.cols = (uint64_t *)const_cast<uint8_t *>(R.task_cols());
+        G.run(N, E, r0, r1, first[w], P);
+        team.barrier();
+        if (w == 0) {
+            for (int v = 0; v < nt; ++v) {
+                const RowPart &Q = part[v];
+                if (Q.failed) status = FE_EBADMESH;
+                off[v + 1] = {off[v].group + (int64_t)Q.wdesc.size(), off[v].elem + Q.n_elems,
+                              off[v].node + Q.n_nodes};
+                R.max_img = std::max(R.max_img, Q.max_img);
+                R.max_items = std::max(R.max_items, Q.max_items);
+                R.max_nodes = std::max(R.max_nodes, Q.max_nodes);
+            }
+            R.n_elems = off[nt].elem;
+            R.n_nodes = off[nt].node;
+            R.lists.resize(RowPlan::list_bytes(R.n_elems, R.n_nodes));
+            R.wdesc.resize(off[nt].group);
+            R.wlists.resize(off[nt].group);
+        }
+        team.barrier();
+        if (status != FE_OK) return;
+        const Offsets &o = off[w];
+        std::copy_n(P.elem.begin(), P.n_elems, const_cast<int32_t *>(R.wave_elem()) + o.elem);
+        std::copy_n(P.node.begin(), P.n_nodes, const_cast<int32_t *>(R.wave_node()) + o.node);
+        if (P.n_elems) memcpy(const_cast<uint16_t *>(R.wave_ln()) + 8 * o.elem, P.ln.data(), P.n_elems * sizeof P.ln[0]);
+        for (size_t g = 0; g < P.wdesc.size(); ++g) {
+            P.wlists[g].first_elem += (int32_t)o.elem;
+            P.wlists[g].first_node += (int32_t)o.node;
+            R.wdesc[o.group + g] = P.wdesc[g];
+            R.wlists[o.group + g] = P.wlists[g];
         }
     });
-    for (int64_t c = 0; c < CR; ++c)
-        if (missing[c]) {
-            err = "the CSR pattern lacks an element's node pair";
+    for (const RowPart &Q : part)
+        if (Q.too_many >= 0) {
+            int64_t n = 0;
+            for (int64_t e = 0; e < E; ++e)
+                for (int q = 0; q < nen_of(e); ++q) n += conn[e * stride + q] == Q.too_many;
+            err = "node " + std::to_string(Q.too_many) + " (mesh numbering) lies in " + std::to_string(n) +
+                  " elements; the block operator's row-owner assembly takes at most " + std::to_string(kRowElemsMax);
             return FE_EBADMESH;
         }
-    // Lane of each of a row's tasks in its group, from lane p on (at [0] of its
-    // tasks' lanes if given); the next free lane.  A round's tasks lie in one
-    // wavefront, so that they add in step.
-    const auto lanes_of = [&](int64_t row, int p, int *lane) {
-        for (int32_t t = inc_ptr[row]; t < inc_ptr[row + 1];) {
-            int m = 1;
-            while (t + m < inc_ptr[row + 1] && round[t + m] == round[t]) ++m;
-            if (p % 64 + m > 64) p = (p + 63) / 64 * 64;
-            for (int q = 0; q < m; ++q, ++p)
-                if (lane) *lane++ = p;
-            t += m;
-        }
-        return p;
-    };
-    // whole rows into groups
-    int64_t r = 0;
-    int32_t tasks = 0;
-    while (r < N) {
-        const int64_t r0 = r;
-        int p = 0;
-        while (r < N) {
-            const int next = lanes_of(r, p, nullptr);
-            const int64_t img = 9 * (int64_t)(rowptr[r + 1] - rowptr[r0]);
-            if (r > r0 && (next > R.lanes || img > row_image(R.lanes) || r - r0 >= R.lanes)) break;
-            p = next;
-            ++r;
-        }
-        R.wdesc.push_back({tasks, p, (int32_t)r0, (int32_t)(r - r0)});
-        tasks += p;
-        R.max_img = std::max<int64_t>(R.max_img, 9 * (int64_t)(rowptr[r] - rowptr[r0]));
+    if (status != FE_OK) {
+        err = "the CSR pattern lacks an element's node pair";
+        return status;
     }
-    R.n_tasks = tasks;
-    R.nen = !etype ? stride : std::all_of(etype, etype + E, [&](uint8_t n) { return n == etype[0]; }) ? etype[0] : 0;
-    if (R.nen == 0) {
-        std::vector<uint8_t> cls(R.wdesc.size());
-        for (size_t w = 0; w < R.wdesc.size(); ++w) {
-            const RowWave &q = R.wdesc[w];
-            const int32_t t0 = inc_ptr[q.first_row], t1 = inc_ptr[q.first_row + q.n_rows];
-            cls[w] = t0 < t1 ? etype[task_elem[t0]] : 0;
-            for (int32_t t = t0; t < t1; ++t)
-                if (etype[task_elem[t]] != cls[w]) cls[w] = 0;
-        }
-        std::vector<RowWave> by_row = std::move(R.wdesc);
+    if (R.nen == 0) {   // of several types: each type's groups together
+        std::vector<uint8_t> cls;
+        for (const RowPart &Q : part) cls.insert(cls.end(), Q.cls.begin(), Q.cls.end());
+        const std::vector<RowWave> wdesc = std::move(R.wdesc);
+        const std::vector<RowLists> wlists = std::move(R.wlists);
         R.wdesc.clear();
+        R.wlists.clear();
         const int order[5] = {0, 8, 5, 6, 4};
         for (int c = 0; c < 5; ++c) {
-            for (size_t w = 0; w < by_row.size(); ++w)
-                if (cls[w] == order[c]) R.wdesc.push_back(by_row[w]);
+            for (size_t g = 0; g < wdesc.size(); ++g)
+                if (cls[g] == order[c]) {
+                    R.wdesc.push_back(wdesc[g]);
+                    R.wlists.push_back(wlists[g]);
+                }
             if (c < 4) R.class_end[c] = (int32_t)R.wdesc.size();
         }
     }
-    // each group's elements and nodes, in the order of their first use by its
-    // tasks: counted, then listed
-    const int64_t W = (int64_t)R.wdesc.size();
-    R.task_meta.resize(tasks);
-    R.task_perm.resize(tasks);
-    R.task_cols.resize((size_t)tasks * 8);
-    R.wlists.resize(W);
-    constexpr int64_t kGroups = 32;   // per chunk
-    const int64_t C = (W + kGroups - 1) / kGroups;
-    // per worker: an element's and a node's place in its group's list, which
-    // counts if the list holds it there; the lists
-    struct Lists {
-        std::vector<int32_t> elem_at, node_at, elems, nodes;
-        std::vector<uint16_t> ln;
-    };
-    std::vector<Lists> work(parallel_workers(C));
-    const auto listed = [](std::vector<int32_t> &list, std::vector<int32_t> &at, int32_t x) {
-        const size_t p = (size_t)(uint32_t)at[x];
-        if (p < list.size() && list[p] == x) return (int32_t)p;
-        list.push_back(x);
-        return at[x] = (int32_t)list.size() - 1;
-    };
-    const auto make = [&](const RowWave &q, Lists &l) {
-        l.elem_at.resize(E);
-        l.node_at.resize(N);
-        l.elems.clear();
-        l.nodes.clear();
-        l.ln.clear();
-        for (int32_t t = inc_ptr[q.first_row]; t < inc_ptr[q.first_row + q.n_rows]; ++t)
-            (void)listed(l.elems, l.elem_at, task_elem[t]);
-        for (const int32_t e : l.elems) {
-            const int32_t *ce = conn + (int64_t)e * stride;
-            const int n = nen_of(e);
-            for (int b = 0; b < 8; ++b) l.ln.push_back(b < n ? (uint16_t)listed(l.nodes, l.node_at, ce[b]) : (uint16_t)0);
-        }
-    };
-    parallel_chunks_w(C, [&](int64_t c, int wk) {
-        for (int64_t w = c * kGroups; w < std::min(W, (c + 1) * kGroups); ++w) {
-            make(R.wdesc[w], work[wk]);
-            R.wlists[w] = {0, (int32_t)work[wk].elems.size(), 0, (int32_t)work[wk].nodes.size()};
-        }
-    });
-    int32_t ne = 0, nn = 0;
-    for (RowLists &l : R.wlists) {
-        l.first_elem = ne;
-        l.first_node = nn;
-        ne += l.n_elems;
-        nn += l.n_nodes;
-        R.max_items = std::max<int64_t>(R.max_items, (int64_t)l.n_elems * row_points(l.n_elems, R.lanes));
-        R.max_nodes = std::max<int64_t>(R.max_nodes, l.n_nodes);
-    }
-    R.wave_elem.resize(ne);
-    R.wave_node.resize(nn);
-    R.wave_ln.resize((size_t)ne * 8);
-    parallel_chunks_w(C, [&](int64_t c, int wk) {
-        Lists &l = work[wk];
-        int lane[kRowElemsMax];
-        for (int64_t w = c * kGroups; w < std::min(W, (c + 1) * kGroups); ++w) {
-            const RowWave &q = R.wdesc[w];
-            make(q, l);
-            std::copy(l.elems.begin(), l.elems.end(), R.wave_elem.begin() + R.wlists[w].first_elem);
-            std::copy(l.nodes.begin(), l.nodes.end(), R.wave_node.begin() + R.wlists[w].first_node);
-            std::copy(l.ln.begin(), l.ln.end(), R.wave_ln.begin() + (size_t)R.wlists[w].first_elem * 8);
-            const size_t t0 = (size_t)q.first_task;
-            std::fill_n(R.task_meta.begin() + t0, q.n_tasks, kRowNoTask);
-            std::fill_n(R.task_perm.begin() + t0, q.n_tasks, 0x88888888u);
-            std::fill_n(R.task_cols.begin() + t0 * 8, (size_t)q.n_tasks * 8, (uint8_t)0);
-            int p = 0;
-            for (int i = 0; i < q.n_rows; ++i) {
-                const int64_t row = q.first_row + i;
-                p = lanes_of(row, p, lane);
-                for (int32_t t = inc_ptr[row]; t < inc_ptr[row + 1]; ++t) {
-                    const int k = t - inc_ptr[row];
-                    const size_t d = t0 + lane[k];
-                    R.task_meta[d] = (uint32_t)l.elem_at[task_elem[t]] | (uint32_t)task_row[t] << 8 | (uint32_t)i << 11 |
-                                     (uint32_t)round[t] << 19 | (k == 0 ? kRowFirstTask : 0u);
-                    R.task_perm[d] = perm[t];
-                    memcpy(&R.task_cols[d * 8], &cols[(size_t)t * 8], 8);
-                }
-            }
-        }
-    });
     return FE_OK;
 }
 
