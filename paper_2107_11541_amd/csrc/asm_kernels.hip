@@ -2192,6 +2192,9 @@ struct BArgs {
     const int32_t *wave_elem, *wave_node;
     const uint16_t *wave_ln;
     int class_end[4];   // of several types: see RowPlan
+    const int32_t *conn, *alone_elem;   // each task alone
+    const uint16_t *alone_meta;
+    int stride;
     int64_t N;
     const double *u, *rho, *mu;
     double inv_dt;
@@ -2551,6 +2554,174 @@ __global__ void __launch_bounds__(NT, 2) k_block_types(BArgs k)
     }
 }
 
+// The other form (plan.h, RowForm): one lane per task, which computes its
+// element's points itself from global memory, one wavefront per group of whole
+// rows, added into LDS one task of a row after the other.  Bound by the chain
+// of those additions (8 x 75 with 8 lanes active for HEX08) and by its 390
+// registers, one wavefront a SIMD.
+// Element e's block row a: S[b] (the scalar part, times the identity) and
+// T[b][3i + k] (the full-stress coupling), and the right-hand side B[i].
+template <class EL, int FORM>
+__device__ __forceinline__ void block_row(const BArgs &k, int64_t e, int a, double (&S)[8], double (&T)[8][9],
+                                          double (&B)[3], double &mindet)
+{
+    constexpr int NEN = EL::NEN, NG = EL::NG;
+    constexpr bool FULL = (FORM & FE_FORM_FULL_STRESS) != 0, EMAC = (FORM & FE_FORM_EMAC) != 0;
+    const int64_t N = k.N;
+    int c[NEN];
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) c[b] = k.conn[e * k.stride + b];
+    double xl[3 * NEN], ul[3][NEN], rl[NEN], ml[NEN];
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            xl[i * NEN + b] = k.X[i * N + c[b]];
+            ul[i][b] = k.u[i * N + c[b]];
+        }
+        rl[b] = k.rho[c[b]];
+        ml[b] = k.mu[c[b]];
+    }
+    int ln[NEN];
+#pragma unroll
+    for (int b = 0; b < NEN; ++b) ln[b] = b;
+    Geo<EL> GE;
+    load_geo<EL>(xl, NEN, ln, GE);
+#pragma unroll 1
+    for (int g = 0; g < NG; ++g) {
+        double Ji[3][3];
+        const double det = jacobian_inverse<EL>(g, GE, Ji);
+        mindet = fmin(mindet, det);
+        double dN[NEN][3];
+#pragma unroll
+        for (int b = 0; b < NEN; ++b)
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                double s = 0.0;
+#pragma unroll
+                for (int j = 0; j < 3; ++j) s += Ji[j][i] * RefdN<EL>(g, b, j);
+                dN[b][i] = s;
+            }
+        // the task's own row a (a runtime index: read from the tables, not
+        // from the register array)
+        double dNa[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            double s = 0.0;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) s += Ji[j][i] * RefdN<EL>(g, a, j);
+            dNa[i] = s;
+        }
+        const double Na = RefN<EL>(g, a);
+        const double dV = EL::w(g) * det;
+        double rg = 0.0, mg = 0.0, ag[3] = {0.0, 0.0, 0.0}, diva = 0.0;
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) {
+            const double Nb = RefN<EL>(g, b);
+            rg += Nb * rl[b];
+            mg += Nb * ml[b];
+#pragma unroll
+            for (int i = 0; i < 3; ++i) {
+                ag[i] += Nb * ul[i][b];
+                if (EMAC) diva += dN[b][i] * ul[i][b];
+            }
+        }
+        const double w1 = dV * rg, wm = dV * mg, wa = w1 * Na;
+#pragma unroll
+        for (int b = 0; b < NEN; ++b) {
+            const double Nb = RefN<EL>(g, b);
+            const double gg = dNa[0] * dN[b][0] + dNa[1] * dN[b][1] + dNa[2] * dN[b][2];
+            const double agb = ag[0] * dN[b][0] + ag[1] * dN[b][1] + ag[2] * dN[b][2];
+            double sv = wa * (Nb * k.inv_dt + agb) + wm * gg;
+            if (EMAC) sv += wa * diva * Nb;
+            S[b] += sv;
+            if (FULL) {
+#pragma unroll
+                for (int i = 0; i < 3; ++i)
+#pragma unroll
+                    for (int kk = 0; kk < 3; ++kk) T[b][3 * i + kk] += wm * dNa[kk] * dN[b][i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i) B[i] += wa * ag[i] * k.inv_dt;
+    }
+}
+
+template <int FORM>
+__global__ void __launch_bounds__(64) k_block_alone(BArgs k)
+{
+    extern __shared__ double lds[];
+    const int wi = xcd_item(blockIdx.x, gridDim.x);   // this wave's row range
+    const int4 wd = k.wdesc[wi];   // first task, tasks, first row, rows
+    const int lane = threadIdx.x;
+    const int r0 = wd.z, nr = wd.w;
+    const int64_t v0 = k.rowptr[r0];
+    const int nimg = 9 * (int)(k.rowptr[r0 + nr] - v0);
+    double *img = lds;            // [nimg] block values of the wave's rows
+    double *rimg = lds + nimg;    // [3][64] their right-hand sides
+    for (int j = lane; j < nimg; j += 64) img[j] = 0.0;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) rimg[i * 64 + lane] = 0.0;
+
+    const bool live = lane < wd.y;
+    const int64_t t = wd.x + (live ? lane : 0);
+    const int64_t e = k.alone_elem[t];
+    const int meta = k.alone_meta[t];
+    const int a = meta & 15, ph = live ? (meta >> 4) : -1;
+    const int nen = k.etype ? (int)k.etype[e] : k.stride;
+    const uint64_t cols = *(const uint64_t *)(k.task_cols + 8 * t);
+    const int row = k.conn[e * k.stride + a];
+    const int ro = (int)(k.rowptr[row] - v0), rl = row - r0;
+    double S[8], T[8][9], B[3] = {0.0, 0.0, 0.0};
+#pragma unroll
+    for (int b = 0; b < 8; ++b) {
+        S[b] = 0.0;
+#pragma unroll
+        for (int q = 0; q < 9; ++q) T[b][q] = 0.0;
+    }
+    double mindet = __builtin_huge_val();
+    if (live) {
+        switch (nen) {
+        case 8: block_row<Hex, FORM>(k, e, a, S, T, B, mindet); break;
+        case 6: block_row<Pen, FORM>(k, e, a, S, T, B, mindet); break;
+        case 5: block_row<Pyr, FORM>(k, e, a, S, T, B, mindet); break;
+        default: block_row<Tet, FORM>(k, e, a, S, T, B, mindet); break;
+        }
+    }
+    __syncthreads();
+    // phases: a row's tasks one after the other in element order; the tasks
+    // of one phase hold distinct rows, so no two lanes add to one address
+    int nph = ph + 1;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) nph = max(nph, __shfl_xor(nph, o));
+    for (int p = 0; p < nph; ++p) {
+        if (ph == p) {
+#pragma unroll
+            for (int b = 0; b < 8; ++b) {
+                if (b < nen) {
+                    double *dst = img + 9 * (ro + (int)((cols >> (8 * b)) & 0xff));
+#pragma unroll
+                    for (int i = 0; i < 3; ++i)
+#pragma unroll
+                        for (int kk = 0; kk < 3; ++kk)
+                            lds_add(dst + 3 * i + kk, (i == kk ? S[b] : 0.0) + T[b][3 * i + kk]);
+                }
+            }
+#pragma unroll
+            for (int i = 0; i < 3; ++i) lds_add(&rimg[i * 64 + rl], B[i]);
+        }
+    }
+    __syncthreads();
+    // each value and right-hand side entry written once, contiguously
+    double *vout = k.values + 9 * v0;
+    for (int j = lane; j < nimg; j += 64) vout[j] = img[j];
+    if (lane < nr) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) k.rhs[i * k.N + r0 + lane] = rimg[i * 64 + lane];
+    }
+    group_status<64>(live ? mindet : __builtin_huge_val(), live && !(mindet > 0.0), e, k.w_mindet + wi, k.w_bad + wi);
+}
+
 template <class EL, int NT>
 void launch_block_lanes(const BArgs &k, const DevRowPlan &r, int form, hipStream_t s)
 {
@@ -2580,7 +2751,8 @@ template <class EL>
 void launch_block(const BArgs &k, const DevRowPlan &r, int form, hipStream_t s)
 {
     if (r.lanes == kRowTasks) launch_block_lanes<EL, kRowTasks>(k, r, form, s);
-    else launch_block_lanes<EL, kRowTasksSmall>(k, r, form, s);
+    // (small HEX08 meshes take each task alone)
+    else if constexpr (!std::is_same<EL, Hex>::value) launch_block_lanes<EL, kRowTasksSmall>(k, r, form, s);
 }
 
 // ---- boundary assembly: equilibrium wall model ---------------------------
@@ -2993,9 +3165,22 @@ hipError_t launch_assemble_block(const DevMesh &m, const DevRowPlan &r, int form
     k.rhs = rhs;
     k.w_mindet = r.w_mindet;
     k.w_bad = r.w_bad;
-    if (r.lanes != kRowTasks && r.lanes != kRowTasksSmall) return hipErrorInvalidValue;
+    if (r.lanes != kRowTasks && (r.lanes != kRowTasksSmall || (r.nen == 8 && !r.alone))) return hipErrorInvalidValue;
     for (int c = 0; c < 4; ++c) k.class_end[c] = r.class_end[c];
-    switch (r.nen) {
+    if (r.alone) {
+        k.conn = r.conn;
+        k.stride = r.stride;
+        k.alone_elem = r.alone_elem;
+        k.alone_meta = r.alone_meta;
+        const size_t lds = (size_t)(r.max_img + 3 * 64) * sizeof(double);
+        const dim3 grid((unsigned)r.n_waves), blk(64);
+        switch (form) {
+        case 0: hipLaunchKernelGGL(k_block_alone<0>, grid, blk, lds, s, k); break;
+        case 1: hipLaunchKernelGGL(k_block_alone<1>, grid, blk, lds, s, k); break;
+        case 2: hipLaunchKernelGGL(k_block_alone<2>, grid, blk, lds, s, k); break;
+        default: hipLaunchKernelGGL(k_block_alone<3>, grid, blk, lds, s, k); break;
+        }
+    } else switch (r.nen) {
     case 8: launch_block<Hex>(k, r, form, s); break;
     case 6: launch_block<Pen>(k, r, form, s); break;
     case 5: launch_block<Pyr>(k, r, form, s); break;

@@ -9,6 +9,7 @@
 #include <cstring>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <vector>
 
@@ -503,7 +504,7 @@ void mesh_release(fe_mesh_s *m)
     m->step_work = nullptr;
     m->scalar_work = nullptr;
     m->wall = DevWall();
-    m->rowplan = DevRowPlan();
+    m->rowplan[0] = m->rowplan[1] = DevRowPlan();
 }
 
 fe_status mesh_commit(fe_mesh_s *m, MeshImage &I, hipStream_t stream)
@@ -1351,12 +1352,22 @@ fe_status fe_assemble(fe_mesh m, const fe_fields *f, fe_precision prec, double *
     return read_asm_status(m, info);
 }
 
-// Builds and uploads the row-owner plan of the block operator (first use).
-static fe_status ensure_rowplan(fe_mesh_s *m)
+// The row-owner plan of the block operator with the form bits `form`, built and
+// uploaded on first use.
+static fe_status ensure_rowplan(fe_mesh_s *m, uint32_t form, const DevRowPlan *&plan)
 {
     fe_ctx_s *c = m->ctx;
-    DevRowPlan &D = m->rowplan;
-    if (D.n_waves > 0) return FE_OK;
+    if (m->row_tasks == 0) {
+        m->row_tasks = m->dm.E * m->stride_m;
+        if (!m->etype_m.empty()) m->row_tasks = std::accumulate(m->etype_m.begin(), m->etype_m.end(), (int64_t)0);
+    }
+    // (plan.h, RowForm)
+    RowForm want = (RowForm)m->row_form;
+    if (!m->etype_m.empty() && m->row_tasks >= kRowPlainHybrid && !(form & FE_FORM_FULL_STRESS)) want = kRowAlone;
+    if (want != kRowAuto && m->rowplan[want].n_waves > 0) {
+        plan = &m->rowplan[want];
+        return FE_OK;
+    }
     if (m->conn_m.empty()) return fail(c, FE_EINVAL, "the mesh keeps no connectivity for the block operator");
     const DevMesh &d = m->dm;
     UnsetVector<int32_t> rp(d.N + 1), ci(d.nnz);
@@ -1373,7 +1384,7 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     RowPlan R;
     std::string err;
     const uint8_t *et = m->etype_m.empty() ? nullptr : m->etype_m.data();
-    int st = build_row_plan(m->stride_m, et, d.N, d.E, m->conn_m.data(), rp.data(), ci.data(), R, err, fetch);
+    int st = build_row_plan(m->stride_m, et, d.N, d.E, m->conn_m.data(), rp.data(), ci.data(), R, err, fetch, want);
     if (fetched != hipSuccess) return fail(c, FE_EDEVICE, "block plan: %s", hipGetErrorString(fetched));
     if (st != FE_OK) return fail(c, (fe_status)st, "%s", err.c_str());
     DevRowPlan P;
@@ -1384,13 +1395,16 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
     P.max_nodes = R.max_nodes;
     P.lanes = R.lanes;
     P.nen = R.nen;
+    P.alone = R.alone;
+    P.stride = m->stride_m;
     std::copy(R.class_end, R.class_end + 4, P.class_end);
     // one allocation (~0.2 ms each) for all arrays
     struct Part {
         void **dst;
         const void *src;
         size_t bytes;
-    } parts[] = {{(void **)&P.etype, et, P.nen == 0 ? m->etype_m.size() : 0},
+    } parts[] = {{(void **)&P.etype, et, P.nen == 0 || P.alone ? m->etype_m.size() : 0},
+                 {(void **)&P.conn, m->conn_m.data(), P.alone ? m->conn_m.size() * sizeof(int32_t) : 0},
                  {(void **)&P.task_meta, R.tasks.data(), R.tasks.size()},
                  {(void **)&P.wave_ln, R.lists.data(), R.lists.size()},
                  {(void **)&P.wdesc, R.wdesc.data(), R.wdesc.size() * sizeof(RowWave)},
@@ -1409,17 +1423,28 @@ static fe_status ensure_rowplan(fe_mesh_s *m)
         if (q.src && q.bytes && e == hipSuccess) e = hipMemcpyAsync(*q.dst, q.src, q.bytes, hipMemcpyHostToDevice, c->stream);
         at += DevArena::round(q.bytes);
     }
-    P.task_perm = P.task_meta + R.n_tasks;
-    P.task_cols = (uint8_t *)(P.task_perm + R.n_tasks);
-    P.wave_elem = (int32_t *)(P.wave_ln + 8 * R.n_elems);
-    P.wave_node = P.wave_elem + R.n_elems;
+    if (P.alone) {
+        P.task_cols = (uint8_t *)P.task_meta;
+        P.alone_elem = (int32_t *)(P.task_cols + 8 * R.n_tasks);
+        P.alone_meta = (uint16_t *)(P.alone_elem + R.n_tasks);
+        P.task_meta = nullptr;
+        if (!et) P.etype = nullptr;
+    } else {
+        P.task_perm = P.task_meta + R.n_tasks;
+        P.task_cols = (uint8_t *)(P.task_perm + R.n_tasks);
+        P.wave_elem = (int32_t *)(P.wave_ln + 8 * R.n_elems);
+        P.wave_node = P.wave_elem + R.n_elems;
+    }
     const hipError_t e2 = hipStreamSynchronize(c->stream);   // the host arrays end here
     if (e == hipSuccess) e = e2;
     if (e != hipSuccess) {
         mesh_free_ptr(m, base);
         return fail(c, FE_EDEVICE, "block plan upload: %s", hipGetErrorString(e));
     }
+    if (want == kRowAuto) m->row_form = P.alone ? kRowAlone : kRowShared;
+    DevRowPlan &D = m->rowplan[P.alone ? kRowAlone : kRowShared];
     D = P;
+    plan = &D;
     return FE_OK;
 }
 
@@ -1434,11 +1459,12 @@ fe_status fe_assemble_block(fe_mesh m, uint32_t form, double dt, const double *u
     if (!(dt > 0.0) || !std::isfinite(dt)) return fail(c, FE_EINVAL, "dt must be > 0");
     RoctxRange rr("fe_assemble_block");
     HIPCALL(c, hipSetDevice(c->device));
-    fe_status s = ensure_rowplan(m);
+    const DevRowPlan *plan = nullptr;
+    fe_status s = ensure_rowplan(m, form, plan);
     if (s != FE_OK) return s;
     {
         ProfScope ps(c, 1);
-        HIPCALL(c, launch_assemble_block(m->dm, m->rowplan, (int)form, dt, u, rho, mu, values, rhs,
+        HIPCALL(c, launch_assemble_block(m->dm, *plan, (int)form, dt, u, rho, mu, values, rhs,
                                          host_status(c), c->stream));
     }
     return read_asm_status(m, info);

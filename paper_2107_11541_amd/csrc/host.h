@@ -78,7 +78,11 @@ struct fe_mesh_s {
     double *step_work = nullptr;         // explicit step: u0 [3][N], residual + mass [4][N], f [N], g [3][N]
     feasm::DevWall wall;                 // wall faces of the wall model (F = 0: none)
     double *scalar_work = nullptr;       // explicit scalar step: Y0 [N], residual + mass [2][N]
-    feasm::DevRowPlan rowplan;           // 3x3-block momentum operator (built on its first use)
+    // 3x3-block momentum operator: its plans (by feasm::RowForm, each built on its
+    // first use), the form that suits the mesh (-1: not known), element nodes
+    feasm::DevRowPlan rowplan[2];
+    int row_form = -1;
+    int64_t row_tasks = 0;
     std::vector<int32_t> conn_m;         // [E][stride_m] connectivity, mesh numbering (block operator plan)
     std::vector<uint8_t> etype_m;        // [E] node counts (hybrid meshes), else empty
     int stride_m = 0;

@@ -193,6 +193,10 @@ hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const
 struct DevRowPlan {
     int64_t n_tasks = 0, n_waves = 0, max_img = 0, max_items = 0, max_nodes = 0;
     int lanes = 0, nen = 0;          // of a group; nodes per element (0: several types)
+    bool alone = false;              // each task alone (plan.h, RowForm)
+    int stride = 0;                  // alone: conn [E][stride], mesh numbering; per task its element, row and place
+    int32_t *conn = nullptr, *alone_elem = nullptr;
+    uint16_t *alone_meta = nullptr;
     int32_t class_end[4] = {};       // see RowPlan
     uint8_t *etype = nullptr;        // [E] node counts, or null (one type)
     uint32_t *task_meta = nullptr, *task_perm = nullptr;

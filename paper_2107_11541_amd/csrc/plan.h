@@ -156,6 +156,22 @@ constexpr int row_image(int lanes) { return lanes == kRowTasks ? 8192 : 3072; }
 struct RowWave {
     int32_t first_task, n_tasks, first_row, n_rows;
 };
+// The other form, each task alone: a wavefront of whole rows, of at most 64
+// tasks, every lane computing its element's points itself.  It runs where it
+// is the faster (us by shared groups / alone):
+//   * small HEX08 meshes, whose shared groups of 64 lanes wait for a barrier
+//     per point: 10^3 39 / 34 plain, 42 / 37 with full stress; 20^3 44 / 44;
+//   * orders of poor locality, where a group's tasks share few elements (more
+//     than kRowPoor of them distinct; Morton order HEX08 0.31, TET04 0.69):
+//     HEX08 40^3 in random order 314 / 252 plain, 366 / 323 with full stress,
+//     TET04 15^3 58 / 43 and 62 / 51, hybrid 32^3 331 / 200 and 427 / 322; on
+//     small meshes as fast, but sooner planned: TET04 8^3 0.77 / 0.44 ms; not
+//     small meshes of PYR05, 10^3 38 / 41, or of several types, 10^3 45 / 52;
+//   * hybrid meshes of kRowPlainHybrid tasks without the full-stress term: 32^3
+//     200 / 175 (with it 239 / 278), 24^3 (260 k) 103 / 97, 16^3 48 / 55.
+enum RowForm { kRowAuto = -1, kRowShared = 0, kRowAlone = 1 };
+constexpr double kRowPoor = 0.85;
+constexpr int64_t kRowPlainHybrid = 1 << 18;
 struct RowLists {
     int32_t first_elem, n_elems, first_node, n_nodes;
 };
@@ -187,8 +203,14 @@ struct RowPlan {
     int32_t class_end[4] = {};         // HEX08, PYR05 and PEN06 alone, each to its end, before TET04's
     std::vector<RowWave> wdesc;        // [groups]; between their tasks entries may be unused
     std::vector<RowLists> wlists;      // [groups] places in the listed elements and nodes
+    bool alone = false;                // each task alone: wdesc's groups are wavefronts, tasks as below
     // The large arrays in two pieces, as they go to the device.
     UnsetVector<char> tasks;
+    // alone: [8] position of the element's node b in the row; element; local row (bits 0-3) | place among the row's tasks
+    const uint8_t *alone_cols() const { return (const uint8_t *)tasks.data(); }
+    const int32_t *alone_elem() const { return (const int32_t *)(alone_cols() + 8 * n_tasks); }
+    const uint16_t *alone_meta() const { return (const uint16_t *)(alone_elem() + n_tasks); }
+    static size_t alone_bytes(int64_t n) { return 14 * (size_t)n; }
     const uint32_t *task_meta() const   // group's element (bits 0-7) | local row a (8-10) | group's row (11-18) | round (19-30)
     {
         return (const uint32_t *)tasks.data();
@@ -206,10 +228,11 @@ struct RowPlan {
 // counts or NULL (every element has stride nodes).  0 or an fe_status code
 // with a message in err (FE_EBADMESH: a node in more than kRowElemsMax
 // elements).  fetch: fills rowptr and colidx, on the calling thread while
-// others plan what needs neither.
+// others plan what needs neither.  form: the form planned; kRowAuto: the one
+// that suits the mesh's size and order (R.alone says which).
 int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const int32_t *conn,
                    const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err,
-                   const std::function<void()> &fetch = nullptr);
+                   const std::function<void()> &fetch = nullptr, RowForm form = kRowShared);
 
 // Owner plan of the matrix assembly (rowplan.cpp): the CSR rows are cut
 // into groups of consecutive rows (mesh numbering, so spatially compact);

@@ -11,6 +11,7 @@
 //     its rows outright (no other adds to them) and holds their image in LDS;
 //     its distinct elements (~90 to 256 tasks of HEX08; 35 to 64) and nodes
 //     are listed, so that their data is computed and staged once;
+//     (or, see RowForm, consecutive rows into wavefronts of single tasks);
 //   * a row's tasks add in rounds of up to 8, all at once: the order in which
 //     each adds its element's nodes is an edge colouring of the bipartite
 //     graph (tasks, columns), so no two add to one column in one step.
@@ -260,6 +261,77 @@ struct alignas(64) RowPart {
     bool failed = false;
 };
 
+// The tasks of rows [r0, r1) in order of row and element, and wavefronts of
+// whole rows of them (the form of each task alone).
+struct RowTasks {
+    int stride;
+    const uint8_t *etype;
+    const int32_t *conn, *rowptr, *colidx, *inc_ptr;
+    const uint32_t *inc;
+    uint8_t *cols;   // the plan's arrays
+    int32_t *elem;
+    uint16_t *meta;
+
+    void run(int64_t N, int64_t r0, int64_t r1, RowPart &P) const
+    {
+        Zeros<int32_t> at(N);   // a column's position in its row
+        RowWave g{inc_ptr[r0], 0, (int32_t)r0, 0};
+        const auto close = [&](int64_t row) {
+            g.n_rows = (int32_t)(row - g.first_row);
+            g.n_tasks = inc_ptr[row] - g.first_task;
+            if (g.n_rows > 0) P.wdesc.push_back(g);
+            P.max_img = std::max<int64_t>(P.max_img, 9 * (int64_t)(rowptr[row] - rowptr[g.first_row]));
+            g = {inc_ptr[row], 0, (int32_t)row, 0};
+        };
+        for (int64_t row = r0; row < r1; ++row) {
+            const int64_t img = 9 * (int64_t)(rowptr[row + 1] - rowptr[g.first_row]);
+            if (row > g.first_row && (inc_ptr[row + 1] - g.first_task > kRowTasksSmall ||
+                                      img > row_image(kRowTasksSmall) || row - g.first_row >= kRowTasksSmall))
+                close(row);
+            const int32_t *c0 = colidx + rowptr[row];
+            const int32_t len = std::min(rowptr[row + 1] - rowptr[row], 256);
+            for (int32_t q = 0; q < len; ++q) at[c0[q]] = q;
+            for (int32_t t = inc_ptr[row]; t < inc_ptr[row + 1]; ++t) {
+                const int64_t e = inc[t] >> 3;
+                const int n = etype ? (int)etype[e] : stride;
+                uint8_t c[8] = {};
+                for (int b = 0; b < n; ++b) {
+                    const int32_t j = conn[e * stride + b], q = at[j];
+                    if (q < 0 || q >= len || c0[q] != j) {
+                        P.failed = true;
+                        return;
+                    }
+                    c[b] = (uint8_t)q;
+                }
+                memcpy(cols + 8 * (size_t)t, c, 8);
+                elem[t] = (int32_t)e;
+                meta[t] = (uint16_t)((inc[t] & 7) | (t - inc_ptr[row]) << 4);
+            }
+        }
+        close(r1);
+    }
+};
+
+// Tasks of rows [r0, r1), of a few groups' worth (seen), and the distinct
+// elements that those hold.
+std::pair<int64_t, int64_t> row_sharing(const int32_t *inc_ptr, const uint32_t *inc, int64_t r0, int64_t r1)
+{
+    constexpr int kWindows = 4;
+    std::pair<int64_t, int64_t> s{0, 0};
+    std::vector<uint32_t> e;
+    for (int k = 0; k < kWindows; ++k) {
+        const int64_t row = r0 + (r1 - r0) * k / kWindows;
+        int64_t end = row;
+        while (end < r1 && inc_ptr[end + 1] - inc_ptr[row] <= kRowTasks) ++end;
+        e.assign(inc + inc_ptr[row], inc + inc_ptr[end]);
+        for (uint32_t &x : e) x >>= 3;
+        std::sort(e.begin(), e.end());
+        s.first += (int64_t)e.size();
+        s.second += std::unique(e.begin(), e.end()) - e.begin();
+    }
+    return s;
+}
+
 // The groups of rows [r0, r1): their lanes, elements and nodes.
 struct RowGrouping {
     int stride, lanes;
@@ -423,7 +495,7 @@ struct RowGrouping {
 
 int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const int32_t *conn,
                    const int32_t *rowptr, const int32_t *colidx, RowPlan &R, std::string &err,
-                   const std::function<void()> &fetch)
+                   const std::function<void()> &fetch, RowForm form)
 {
     R = RowPlan();
     auto nen_of = [&](int64_t e) { return etype ? (int)etype[e] : stride; };
@@ -454,6 +526,10 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
     };
     std::vector<Offsets> off(nt + 1, Offsets{0, 0, 0});
     std::vector<int64_t> first(nt + 1, 0);   // each thread's tasks in the plan
+    std::vector<std::pair<int64_t, int64_t>> sharing(nt, {0, 0});
+    const bool small = T < kRowSmallMesh;
+    if (form == kRowAuto && small && R.nen != 4 && R.nen != 6) form = R.nen == 8 ? kRowAlone : kRowShared;
+    R.alone = form == kRowAlone;
     int status = FE_OK;   // set by thread 0 alone
     Team::run(nt, [&](int w, Team &team) {
         const auto begin = [&](int64_t n) { return n * w / nt; };
@@ -509,6 +585,31 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
         each([&](uint32_t i, uint32_t x) { inc[fill[i]++] = x; });
         team.barrier();
         RowPart &P = part[w];
+        if (form == kRowAuto) {
+            sharing[w] = row_sharing(inc_ptr.data(), inc.data(), r0, r1);
+            team.barrier();
+            if (w == 0) {
+                int64_t seen = 0, distinct = 0;
+                for (const auto &q : sharing) {
+                    seen += q.first;
+                    distinct += q.second;
+                }
+                R.alone = (double)distinct > kRowPoor * (double)seen;
+            }
+            team.barrier();
+        }
+        if (R.alone) {
+            if (w == 0) {
+                R.lanes = kRowTasksSmall;
+                R.n_tasks = T;
+                R.tasks.resize(RowPlan::alone_bytes(T));
+            }
+            team.barrier();
+            RowTasks{stride, etype, conn, rowptr, colidx, inc_ptr.data(), inc.data(), const_cast<uint8_t *>(R.alone_cols()),
+                     const_cast<int32_t *>(R.alone_elem()), const_cast<uint16_t *>(R.alone_meta())}
+                .run(N, r0, r1, P);
+            return;
+        }
         RowGrouping G{stride, R.lanes, etype, conn, rowptr, colidx, inc_ptr.data(), inc.data(), nullptr, nullptr, nullptr};
         if (w == 0) {
             for (int v = 0; v < nt; ++v) first[v + 1] = first[v] + G.most_lanes(N * v / nt, N * (v + 1) / nt);
@@ -561,11 +662,17 @@ int build_row_plan(int stride, const uint8_t *etype, int64_t N, int64_t E, const
                   " elements; the block operator's row-owner assembly takes at most " + std::to_string(kRowElemsMax);
             return FE_EBADMESH;
         }
+    if (R.alone)
+        for (const RowPart &Q : part) {
+            if (Q.failed) status = FE_EBADMESH;
+            R.max_img = std::max(R.max_img, Q.max_img);
+            R.wdesc.insert(R.wdesc.end(), Q.wdesc.begin(), Q.wdesc.end());
+        }
     if (status != FE_OK) {
         err = "the CSR pattern lacks an element's node pair";
         return status;
     }
-    if (R.nen == 0) {   // of several types: each type's groups together
+    if (R.nen == 0 && !R.alone) {   // of several types: each type's groups together
         std::vector<uint8_t> cls;
         for (const RowPart &Q : part) cls.insert(cls.end(), Q.cls.begin(), Q.cls.end());
         const std::vector<RowWave> wdesc = std::move(R.wdesc);

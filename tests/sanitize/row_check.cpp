@@ -123,6 +123,46 @@ static Order check_rows(const Plan &P, const RowPlan &R)
     return order;
 }
 
+// The plan of each task alone: every (element, local row) once, by row and
+// element, whole rows to wavefronts of at most 64.
+static void check_alone(const Plan &P, const RowPlan &R)
+{
+    const uint8_t *et = P.etype.empty() ? nullptr : P.etype.data();
+    auto nen_of = [&](int64_t e) { return et ? (int)et[e] : P.nen; };
+    int64_t tasks = 0, next_row = 0, next_task = 0, max_img = 0;
+    for (int64_t e = 0; e < P.E; ++e) tasks += nen_of(e);
+    CHECK(R.alone && R.n_tasks == tasks);
+    std::set<std::pair<int64_t, int>> seen;
+    for (const RowWave &w : R.wdesc) {
+        CHECK(w.first_row == next_row && w.first_task == next_task && w.n_rows >= 1 && w.n_rows <= 64);
+        CHECK(w.n_tasks >= 1 && w.n_tasks <= 64);
+        const int64_t img = 9 * (int64_t)(P.rowptr[w.first_row + w.n_rows] - P.rowptr[w.first_row]);
+        CHECK(img <= row_image(kRowTasksSmall));
+        max_img = std::max(max_img, img);
+        int32_t row = -1, last = -1;
+        int place = 0;
+        for (int64_t t = w.first_task; t < w.first_task + w.n_tasks; ++t) {
+            const int32_t e = R.alone_elem()[t];
+            const int a = R.alone_meta()[t] & 15;
+            CHECK(a < nen_of(e) && seen.insert({e, a}).second);
+            const int32_t i = P.conn[(size_t)e * P.nen + a];
+            CHECK(i >= w.first_row && i < w.first_row + w.n_rows && i >= row);
+            place = i == row ? place + 1 : 0;
+            CHECK(R.alone_meta()[t] >> 4 == place && (i != row || e >= last));
+            row = i;
+            last = e;
+            for (int b = 0; b < nen_of(e); ++b) {
+                const int col = R.alone_cols()[8 * (size_t)t + b];
+                CHECK(P.rowptr[i] + col < P.rowptr[i + 1] &&
+                      P.colidx[P.rowptr[i] + col] == P.conn[(size_t)e * P.nen + b]);
+            }
+        }
+        next_row += w.n_rows;
+        next_task += w.n_tasks;
+    }
+    CHECK(next_row == P.N && next_task == tasks && max_img <= R.max_img && (int64_t)seen.size() == tasks);
+}
+
 // The HEX08 owner plan dealt to wavefronts: the same tasks, and in one step of
 // a wavefront each owned row at most once per local place.
 static void check_waves(const Plan &P)
@@ -183,6 +223,19 @@ static void check(int kind, int n, bool renumber, bool collapse)
                              P.rowptr.data(), P.colidx.data(), R, err) == 0);
         set_thread_budget(0);
         const Order o = check_rows(P, R);
+        RowPlan S, A;
+        set_thread_budget(threads);
+        for (RowPlan *Q : {&S, &A})
+            CHECK(build_row_plan(P.nen, P.etype.empty() ? nullptr : P.etype.data(), P.N, P.E, P.conn.data(),
+                                 P.rowptr.data(), P.colidx.data(), *Q, err, nullptr, Q == &S ? kRowAlone : kRowAuto) == 0);
+        set_thread_budget(0);
+        check_alone(P, S);
+        // the form for the mesh: small ones by type, the others by their order
+        int64_t tasks = 0;
+        for (int64_t e = 0; e < P.E; ++e) tasks += P.etype.empty() ? P.nen : P.etype[e];
+        if (tasks >= kRowSmallMesh) CHECK(A.alone == !renumber);
+        else if (!P.etype.empty() || P.nen == 8 || P.nen == 5) CHECK(A.alone == (P.etype.empty() && P.nen == 8));
+        else CHECK(!A.alone || !renumber);
         // the order of every sum is the same for any number of threads
         if (threads == 1) first = o;
         CHECK(o == first);
@@ -200,7 +253,7 @@ int main()
     // several threads; groups of 256 lanes (from 2^16 element nodes on), and of 64
     check(0, 21, true, true);
     check(0, 14, false, false);
-    check(1, 14, true, false);
+    check(1, 15, true, false);
     check(2, 16, false, false);
     // a node in more than kRowElemsMax elements is refused, with its number of elements
     {
