@@ -201,14 +201,33 @@ def test_work_queued_before_a_solve_holds_up_no_other_context(fe_ctx):
     import time
     import torch
     import paper_2107_11541_amd as fe
-    a, b = _contexts(fe, 2)
+    ws = _contexts(fe, 5)
+    a = ws[0]
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
     with torch.cuda.stream(a[0]):
+        torch.cuda._sleep(1000)   # (the kernel is loaded)
+        a[0].synchronize()
         e0.record()
-        torch.cuda._sleep(1_000_000)
+        torch.cuda._sleep(10_000_000)
         e1.record()
         a[0].synchronize()
-    cycles = int(1_000_000 * 500.0 / e0.elapsed_time(e1))   # 500 ms
+    cycles = int(10_000_000 * 500.0 / e0.elapsed_time(e1))   # 500 ms
+    print(f"500 ms are {cycles} cycles", flush=True)
+
+    def beside(w):
+        # whether w's stream runs beside a's (streams may share a hardware queue)
+        with torch.cuda.stream(a[0]):
+            torch.cuda._sleep(cycles // 5)
+        t = time.perf_counter()
+        with torch.cuda.stream(w[0]):
+            w[5].add(1.0)
+            w[0].synchronize()
+        t = time.perf_counter() - t
+        a[0].synchronize()
+        return t < 0.05
+    b = next((w for w in ws[1:] if beside(w)), None)
+    if b is None:
+        pytest.skip("no stream beside the first")
     done = threading.Event()
 
     def slow():
@@ -226,7 +245,7 @@ def test_work_queued_before_a_solve_holds_up_no_other_context(fe_ctx):
         b[0].synchronize()
         assert not done.is_set() and info["status"] == 0
     t.join()
-    for w in (a, b):
+    for w in ws:
         w[2].close()
         w[1].close()
 
