@@ -809,7 +809,10 @@ struct AsmBatch {
     int first[kMaxBatch];
     int wgs[kMaxBatch + 1];
 };
-static_assert(sizeof(KArgs) <= kKArgsBytes, "the device table's slot size");
+// The device table's slot: KArgs, then (meshes that assemble by blocks with a
+// gather) GatherArgs.
+constexpr size_t kGatherArgsAt = 256;
+static_assert(sizeof(KArgs) <= kGatherArgsAt);
 
 template <class EL, int OP>
 __global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_bat_assemble(const KArgs *__restrict__ ks, AsmBatch B)
@@ -1591,12 +1594,11 @@ struct PartArgs {
 };
 
 template <class EL, int OP, class Q, class FT>
-__global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_part(KArgs k, PartArgs pa)
+__device__ __forceinline__ void part_block(const KArgs &k, const PartArgs &pa, int blk)
 {
     constexpr int NEN = EL::NEN, W = Split<EL>::W, RA = NEN / W, NT = 64 * W;
     constexpr int NF = OpTraits<OP>::NF, NRHS = OpTraits<OP>::NRHS;
     extern __shared__ double lds[];
-    const int blk = k.color_blk[k.blk_offset + xcd_item(blockIdx.x, gridDim.x)];
     const int e0 = k.blk_elem_ptr[blk], ne = k.blk_elem_ptr[blk + 1] - e0;
     const int n0 = k.blk_node_ptr[blk], T = k.blk_node_ptr[blk + 1] - n0;
     const int i0 = pa.img_ptr[blk], L = pa.img_ptr[blk + 1] - i0;
@@ -1712,6 +1714,12 @@ __global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_part(KArgs k, PartArgs
         for (int r = 0; r < NRHS; ++r) pa.sums[r * pa.VT + n0 + t] = rimg[r * T + t];
 }
 
+template <class EL, int OP, class Q, class FT>
+__global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_part(KArgs k, PartArgs pa)
+{
+    part_block<EL, OP, Q, FT>(k, pa, k.color_blk[k.blk_offset + xcd_item(blockIdx.x, gridDim.x)]);
+}
+
 // 8 lanes per CSR row: lane l adds entries l, l + 8, l + 16 and l + 24 of two
 // of the row's images at a time (8 loads in flight), in block order, lane r
 // right-hand side r.  The places of eight images are read by the eight lanes
@@ -1722,20 +1730,24 @@ __global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_part(KArgs k, PartArgs
 // meanwhile (the seven after it only keep the XCDs' ranges).
 constexpr int kGatherLanes = 8;
 constexpr int kGatherStatus = 8;   // leading groups
+constexpr int kGatherRows = 256 / kGatherLanes;
+inline int64_t gather_groups(int64_t N) { return (N + kGatherRows - 1) / kGatherRows + kGatherStatus; }
+struct GatherArgs {
+    int64_t N;
+    const int32_t *rowptr, *ptr, *slot, *place;
+    PartArgs pa;
+    double *values, *rhs;
+    StatusArgs st;
+};
+
+// Group `item` of the rows.
 template <int NRHS>
-__global__ void __launch_bounds__(256) k_part_gather(int64_t N, const int32_t *__restrict__ rowptr,
-                                                     const int32_t *__restrict__ ptr,
-                                                     const int32_t *__restrict__ slot,
-                                                     const int32_t *__restrict__ place, PartArgs pa,
-                                                     double *__restrict__ values, double *__restrict__ rhs,
-                                                     StatusArgs st)
+__device__ __forceinline__ void part_gather(int item, int64_t N, const int32_t *__restrict__ rowptr,
+                                            const int32_t *__restrict__ ptr, const int32_t *__restrict__ slot,
+                                            const int32_t *__restrict__ place, const PartArgs &pa,
+                                            double *__restrict__ values, double *__restrict__ rhs)
 {
-    if (blockIdx.x < kGatherStatus) {
-        if (blockIdx.x == 0) reduce_status<256>(st);
-        return;
-    }
-    const int64_t i = (int64_t)xcd_item(blockIdx.x - kGatherStatus, gridDim.x - kGatherStatus) *
-                          (256 / kGatherLanes) + threadIdx.x / kGatherLanes;
+    const int64_t i = (int64_t)item * kGatherRows + threadIdx.x / kGatherLanes;
     const int lane = threadIdx.x % kGatherLanes;
     if (i >= N) return;
     const int r0 = rowptr[i], len = rowptr[i + 1] - r0;
@@ -1782,6 +1794,50 @@ __global__ void __launch_bounds__(256) k_part_gather(int64_t N, const int32_t *_
             if (j0 + v * kGatherLanes + lane < len) values[r0 + j0 + v * kGatherLanes + lane] = s[v];
     }
     if (lane < NRHS) rhs[lane * N + i] = b;
+}
+
+template <int NRHS>
+__global__ void __launch_bounds__(256) k_part_gather(GatherArgs g)
+{
+    if (blockIdx.x < kGatherStatus) {
+        if (blockIdx.x == 0) reduce_status<256>(g.st);
+        return;
+    }
+    part_gather<NRHS>(xcd_item(blockIdx.x - kGatherStatus, gridDim.x - kGatherStatus), g.N, g.rowptr, g.ptr, g.slot,
+                      g.place, g.pa, g.values, g.rhs);
+}
+
+// The same for several meshes at once (the serving runtime's hybrid requests):
+// one launch per element type and one for the gathers, as k_bat_assemble.  Each
+// request's sums are those of its launches alone.  A launch per request and
+// type leaves most of the chip idle on small meshes: a saturated server then
+// spent 0.27 / 0.39 / 0.58 ms per request of 4^3 / 8^3 / 12^3 cells, in these
+// common launches 0.20 / 0.30 / 0.48 (colour by colour 0.19 / 0.32-0.39 / 0.56).
+// The momentum kernel of hexahedra holds its arguments by pointer and spills 43
+// registers, the one alone none; the times are with that.
+template <class EL, int OP>
+__global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_bat_part(const char *__restrict__ table, AsmBatch B)
+{
+    int j = 0;
+    while (j + 1 < B.n && (int)blockIdx.x >= B.wgs[j + 1]) ++j;
+    const char *const entry = table + (size_t)B.slot[j] * kKArgsBytes;
+    const KArgs &k = *(const KArgs *)entry;
+    const GatherArgs &g = *(const GatherArgs *)(entry + kGatherArgsAt);
+    part_block<EL, OP, double, double>(k, g.pa, k.color_blk[B.first[j] + (int)blockIdx.x - B.wgs[j]]);
+}
+
+template <int NRHS>
+__global__ void __launch_bounds__(256) k_bat_part_gather(const char *__restrict__ table, AsmBatch B)
+{
+    int j = 0;
+    while (j + 1 < B.n && (int)blockIdx.x >= B.wgs[j + 1]) ++j;
+    const GatherArgs &g = *(const GatherArgs *)(table + (size_t)B.slot[j] * kKArgsBytes + kGatherArgsAt);
+    const int item = (int)blockIdx.x - B.wgs[j] - kGatherStatus;
+    if (item < 0) {
+        if (item == -kGatherStatus) reduce_status<256>(g.st);
+        return;
+    }
+    part_gather<NRHS>(item, g.N, g.rowptr, g.ptr, g.slot, g.place, g.pa, g.values, g.rhs);
 }
 
 template <class EL, int OP>
@@ -2949,6 +3005,15 @@ KArgs make_kargs(const AsmArgs &a)
 }
 
 template <class EL>
+void launch_bat_part(int op, const AsmBatch &B, const char *table, size_t lds, hipStream_t s)
+{
+    if (op == OP_MOM)
+        hipLaunchKernelGGL((k_bat_part<EL, OP_MOM>), dim3(B.wgs[B.n]), dim3(64 * Split<EL>::W), lds, s, table, B);
+    else
+        hipLaunchKernelGGL((k_bat_part<EL, OP_POI>), dim3(B.wgs[B.n]), dim3(64 * Split<EL>::W), lds, s, table, B);
+}
+
+template <class EL>
 void launch_bat(int op, const AsmBatch &B, const KArgs *ks, size_t lds, hipStream_t s)
 {
     if (op == OP_MOM)
@@ -2959,11 +3024,63 @@ void launch_bat(int op, const AsmBatch &B, const KArgs *ks, size_t lds, hipStrea
 
 }  // namespace
 
+// The gather of one operator pass by blocks.
+static GatherArgs make_gather(const AsmArgs &a, const KArgs &k)
+{
+    const DevMesh &m = *a.m;
+    return GatherArgs{m.N, m.rowptr, m.node_slot_ptr, m.node_slot, m.node_img,
+                      PartArgs{m.blk_img_ptr, a.img_work, a.img_work + m.img_total, m.vec_T}, a.values, a.rhs,
+                      StatusArgs{k.blk_mindet, k.blk_bad, m.nblk, a.status_out ? a.status_out : a.status}};
+}
+
 void fill_kargs(const AsmArgs &a, void *out)
 {
-    const KArgs k = make_kargs(a);
+    KArgs k = make_kargs(a);
     memset(out, 0, kKArgsBytes);
+    if (a.img_work) {
+        k.color_blk = a.m->vec_blk;
+        const GatherArgs g = make_gather(a, k);
+        memcpy((char *)out + kGatherArgsAt, &g, sizeof g);
+    }
     memcpy(out, &k, sizeof(KArgs));
+}
+
+// launch_assemble_batch of meshes that assemble by blocks with a gather.
+static hipError_t launch_part_batch(const AsmArgs *a, const int *slot, int n, const char *table, hipStream_t s)
+{
+    static_assert(kGatherArgsAt + sizeof(GatherArgs) <= kKArgsBytes, "the device table's slot size");
+    const int op = a[0].op;
+    for (int nen : {8, 6, 5, 4}) {
+        AsmBatch B{};
+        size_t lds = 0;
+        for (int i = 0; i < n; ++i)
+            for (const AsmLaunch &L : a[i].m->vec_launches) {
+                if (L.nen != nen) continue;
+                B.slot[B.n] = slot[i];
+                B.first[B.n] = L.first;
+                B.wgs[B.n + 1] = B.wgs[B.n] + L.count;
+                lds = std::max(lds, L.lds[op]);
+                ++B.n;
+            }
+        if (B.n == 0) continue;
+        switch (nen) {
+        case 8: launch_bat_part<Hex>(op, B, table, lds, s); break;
+        case 6: launch_bat_part<Pen>(op, B, table, lds, s); break;
+        case 5: launch_bat_part<Pyr>(op, B, table, lds, s); break;
+        default: launch_bat_part<Tet>(op, B, table, lds, s); break;
+        }
+        const hipError_t err = hipGetLastError();
+        if (err != hipSuccess) return err;
+    }
+    AsmBatch B{};
+    for (int i = 0; i < n; ++i) {
+        B.slot[i] = slot[i];
+        B.wgs[i + 1] = B.wgs[i] + (int)gather_groups(a[i].m->N);
+    }
+    B.n = n;
+    if (op == OP_MOM) hipLaunchKernelGGL(k_bat_part_gather<3>, dim3(B.wgs[n]), dim3(256), 0, s, table, B);
+    else hipLaunchKernelGGL(k_bat_part_gather<1>, dim3(B.wgs[n]), dim3(256), 0, s, table, B);
+    return hipGetLastError();
 }
 
 hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const void *kargs_d, hipStream_t s)
@@ -2973,9 +3090,11 @@ hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const
     if (op != OP_MOM && op != OP_POI) return hipErrorInvalidValue;
     size_t nl = 0;
     for (int i = 0; i < n; ++i) {
-        if (a[i].op != op || a[i].m->own_G > 0) return hipErrorInvalidValue;
+        if (a[i].op != op || a[i].m->own_G > 0 || (a[i].img_work != nullptr) != (a[0].img_work != nullptr))
+            return hipErrorInvalidValue;
         nl = std::max(nl, a[i].m->launches.size());
     }
+    if (a[0].img_work) return launch_part_batch(a, slot, n, (const char *)kargs_d, s);
     const KArgs *ks = (const KArgs *)kargs_d;
     // launch li of every mesh, one launch per element type; launch li + 1
     // after it, so each mesh keeps its own colour order
@@ -3073,27 +3192,21 @@ hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s)
     if (a.op < OP_RES && a.img_work && m.img_total > 0) {
         // matrix operators of the other meshes: by blocks, then the gather
         k.color_blk = m.vec_blk;
-        const PartArgs pa{m.blk_img_ptr, a.img_work, a.img_work + m.img_total, m.vec_T};
+        const GatherArgs g = make_gather(a, k);
         for (const AsmLaunch &L : m.vec_launches) {
             switch (L.nen) {
-            case 8: launch_part<Hex>(L, k, pa, a.op, mixed, m.hybrid, s); break;
-            case 6: launch_part<Pen>(L, k, pa, a.op, mixed, m.hybrid, s); break;
-            case 5: launch_part<Pyr>(L, k, pa, a.op, mixed, m.hybrid, s); break;
-            case 4: launch_part<Tet>(L, k, pa, a.op, mixed, m.hybrid, s); break;
+            case 8: launch_part<Hex>(L, k, g.pa, a.op, mixed, m.hybrid, s); break;
+            case 6: launch_part<Pen>(L, k, g.pa, a.op, mixed, m.hybrid, s); break;
+            case 5: launch_part<Pyr>(L, k, g.pa, a.op, mixed, m.hybrid, s); break;
+            case 4: launch_part<Tet>(L, k, g.pa, a.op, mixed, m.hybrid, s); break;
             default: return hipErrorInvalidValue;
             }
             const hipError_t err = hipGetLastError();
             if (err != hipSuccess) return err;
         }
-        const int rows = 256 / kGatherLanes;
-        const dim3 grid((unsigned)((m.N + rows - 1) / rows) + kGatherStatus), block(256);
-        const StatusArgs st{k.blk_mindet, k.blk_bad, m.nblk, out};
-        if (a.op == OP_MOM)
-            hipLaunchKernelGGL(k_part_gather<3>, grid, block, 0, s, m.N, m.rowptr, m.node_slot_ptr, m.node_slot,
-                               m.node_img, pa, a.values, a.rhs, st);
-        else
-            hipLaunchKernelGGL(k_part_gather<1>, grid, block, 0, s, m.N, m.rowptr, m.node_slot_ptr, m.node_slot,
-                               m.node_img, pa, a.values, a.rhs, st);
+        const dim3 grid((unsigned)gather_groups(m.N)), block(256);
+        if (a.op == OP_MOM) hipLaunchKernelGGL(k_part_gather<3>, grid, block, 0, s, g);
+        else hipLaunchKernelGGL(k_part_gather<1>, grid, block, 0, s, g);
         return hipGetLastError();
     }
     if (a.op >= OP_RES && a.vec_work) {

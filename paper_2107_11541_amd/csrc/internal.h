@@ -179,12 +179,14 @@ struct AsmArgs {
 // Launchers (asm_kernels.hip).
 hipError_t launch_assemble(const AsmArgs &a, bool mixed, hipStream_t s);
 // Batched coloured assembly of one operator (MOMENTUM or POISSON, FP64) over
-// n meshes that carry the coloured plan only (the serving runtime): launch li
-// of every mesh's (colour, type) list runs as one launch per element type,
-// launch li + 1 after it, then each mesh's status word.  Request i's kernel
+// n meshes without an owner plan (the serving runtime), all with img_work or
+// all without.  Without: launch li of every mesh's (colour, type) list runs as
+// one launch per element type, launch li + 1 after it, then each mesh's status
+// word.  With: the blocks of all meshes in one launch per element type, then
+// their gathers and status words in one.  Request i's kernel
 // arguments must sit in the device table kargs_d at slot[i] * kKArgsBytes,
 // written from fill_kargs(a[i]) before the launches run.
-constexpr size_t kKArgsBytes = 256;
+constexpr size_t kKArgsBytes = 512;
 void fill_kargs(const AsmArgs &a, void *out);   // out: kKArgsBytes bytes
 hipError_t launch_assemble_batch(const AsmArgs *a, const int *slot, int n, const void *kargs_d, hipStream_t s);
 

@@ -331,7 +331,7 @@ fe_status admit(fe_server_s *S, Job *j)
 // dispatcher pass: one launch per (colour, type) launch index and element
 // type over all of them, each request's blocks running the code of its own
 // coloured launch (its results do not depend on the batch).  Hybrid meshes
-// assemble by blocks, each on its own.
+// assemble by blocks with a gather, likewise one launch per element type.
 fe_status assemble_admitted(fe_server_s *S, const std::vector<Job *> &js)
 {
     fe_ctx_s *c = &S->sctx;
@@ -340,17 +340,15 @@ fe_status assemble_admitted(fe_server_s *S, const std::vector<Job *> &js)
     if (js.size() < 1 || js.size() > (size_t)kMaxBatch)
         return fail(c, FE_EINVAL, "internal: %d admissions in one pass", (int)js.size());
     for (int o = 0; o < 2; ++o) {
-        int n = 0;
-        for (Job *j : js) {
-            const AsmArgs x = job_asm_args(j, o == 0 ? FE_OP_MOMENTUM : FE_OP_POISSON);
-            if (x.img_work) {
-                HIPCALL(c, launch_assemble(x, false, S->stream));
-                continue;
+        for (const bool gather : {false, true}) {
+            int n = 0;
+            for (Job *j : js) {
+                if ((j->mesh->img_work != nullptr) != gather) continue;
+                a[n] = job_asm_args(j, o == 0 ? FE_OP_MOMENTUM : FE_OP_POISSON);
+                slot[n++] = 2 * j->slot + o;
             }
-            a[n] = x;
-            slot[n++] = 2 * j->slot + o;
+            if (n) HIPCALL(c, launch_assemble_batch(a, slot, n, S->kargs_d, S->stream));
         }
-        if (n) HIPCALL(c, launch_assemble_batch(a, slot, n, S->kargs_d, S->stream));
     }
     return FE_OK;
 }
