@@ -359,9 +359,9 @@ struct RowGrouping {
         Zeros<Placed> elems(E), nodes(N);
         Zeros<int32_t> at(N);   // a column's position in its row
         const size_t tasks = (size_t)(inc_ptr[r1] - inc_ptr[r0]);
-        P.elem.resize(tasks / 2 + 8);
-        P.ln.resize(tasks / 2 + 8);
-        P.node.resize(tasks / 2 + 8);
+        P.elem.resize(tasks + 8);   // at most one to a task; pages that stay unused are never touched
+        P.ln.resize(tasks + 8);
+        P.node.resize(tasks + 8);
         uint32_t gid = 1;       // the open group
         const int64_t last = first + most_lanes(r0, r1);
         uint8_t of[kRowElemsMax * 8], nen[kRowElemsMax], round[kRowElemsMax];
@@ -446,10 +446,6 @@ struct RowGrouping {
                 Placed &pe = elems[e];
                 if (pe.group != gid) {
                     pe = {gid, (uint32_t)l.n_elems++};
-                    if ((size_t)P.n_elems == P.elem.size()) {
-                        P.elem.resize(2 * P.elem.size());
-                        P.ln.resize(P.elem.size());
-                    }
                     if ((size_t)P.n_nodes + 8 > P.node.size()) P.node.resize(2 * P.node.size());
                     const int32_t *ce = conn + e * stride;
                     int32_t *const list = P.node.data() + P.n_nodes;
