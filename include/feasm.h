@@ -222,7 +222,10 @@ fe_status fe_assemble(fe_mesh mesh, const fe_fields *fields, fe_precision prec, 
  * terms cancel).  Every CSR block row is written once (no
  * read-back); the sums run in a fixed order, so the result is bitwise
  * reproducible.  The first call on a mesh plans the row-owner assembly on the
- * host and keeps the plan on the device (about 25 bytes per element node).
+ * host and keeps the plan on the device (16 bytes per element node, and the
+ * groups' lists, 20 bytes per element and 4 per node of each group: about 28 bytes
+ * per element node on HEX08 meshes, 33 on TET04; where each node's task
+ * runs alone, 14 bytes per element node and the connectivity).
  * Errors: FE_EINVAL, FE_EBADELEM (element in *info), FE_EBADMESH if a node
  * lies in more than 64 elements, FE_ENOMEM, FE_EDEVICE.
  */
@@ -264,12 +267,14 @@ typedef struct {
  * each pair a_ij, a_ji whose rows fall in one SpMV row block is read once,
  * from the upper entry.  The call checks every such pair first (|a_ij -
  * a_ji| <= 2^-40 max(|a_ij|, |a_ji|, sqrt|a_ii a_jj|), both finite) and
- * otherwise runs the general SpMV; info->symmetric_spmv says which ran.
+ * otherwise runs the general SpMV; info->symmetric_spmv says whether it
+ * passed (a solve in one launch, see below, multiplies whole rows).
  * The first FP64 solve on a mesh builds the symmetric map on the host and
  * keeps it, with a packed copy of the values, on the device (about 8
  * bytes per nonzero; without room for them the general SpMV runs).
- * A matrix that passed the check and fits the device's registers (rows of
- * at most 27 entries: up to ~393,000 nodes, ~590,000 where rows hold at most
+ * A matrix that passed the check and fits the device's registers (no row of
+ * more than 27 entries, which a node of an unstructured tetrahedral mesh
+ * often has: up to ~393,000 nodes, ~590,000 where rows hold at most
  * 16) is solved in one launch that reads each value once; FE_MIXED runs its
  * FP32 solves so up to ~655,000 (~786,000) nodes.  The launch needs a plan of
  * the pattern (about 2 bytes per nonzero and 4 MB on the device, built by

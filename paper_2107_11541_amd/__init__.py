@@ -132,8 +132,8 @@ class Mesh:
                  types=None, coloured: bool = False, symmetric_spmv: bool = True):
         """elem_type: HEX08, PEN06, PYR05, TET04 (conn [E, nen]) or HYBRID with
         types [E] node counts and conn [E, 8] (fe_mesh_upload_mixed).
-        coloured: HEX08 matrix assembly by coloured element blocks (the
-        serving runtime's form) instead of owner groups.
+        coloured: matrix assembly of a mesh of one type by coloured element
+        blocks (the serving runtime's form), FE_UPLOAD_COLOURED.
         symmetric_spmv=False: FE_UPLOAD_GENERAL_SPMV (a mesh solved once)."""
         self.ctx = ctx
         lib = ctx.lib

@@ -1581,10 +1581,11 @@ __device__ __forceinline__ void reduce_status(const StatusArgs &st)
 // Bound by latency, in the blocks (a 64-TET04 momentum block: staging 5 us, sums
 // 4 us, of 11) as in the gather, with 8-12 blocks to a CU; PEN06 half by FP64
 // arithmetic.  Whole calls, owner groups (each element computed by every group
-// that owns one of its rows: 1.6x) -> blocks: TET04 45^3 cubes momentum 110 -> 79
-// us, 90^3 695 -> 498; PEN06 57^3 momentum 183 -> 134, Poisson 150 -> 104; PYR05
-// 40^3 184 -> 120.  Coloured blocks (40 launches) -> blocks: hybrid 64^3 momentum
-// 816 -> 218, 20^3 680 -> 76.  A HEX08 mesh stays with owner
+// that owns one of its rows: 1.6x) -> blocks, momentum / Poisson: TET04 45^3
+// cubes 114 / 88 -> 91 / 76 us, 90^3 657 / 467 -> 525 / 428; PEN06 57^3 194 / 164
+// -> 156 / 121; PYR05 40^3 189 / 158 -> 130 / 118.  Coloured blocks (40 launches)
+// -> blocks: hybrid 64^3 816 / 750 -> 223 / 184, 20^3 745 / 700 -> 83 / 74 (outputs
+// allocated by the call; into given ones 5 to 30 us less, before as after).  A HEX08 mesh stays with owner
 // groups: k_part takes 0.42 ns per HEX08 element (65 k of the hybrid mesh) before
 // its gather, k_own as much in all (101^3).
 struct PartArgs {

@@ -41,6 +41,8 @@ constexpr int kWaves = kRB / 64;
 constexpr int kHaloCap = kResidentHalo;        // halo columns of a group
 constexpr int kHash = 2 * kHaloCap;            // slots of the planning kernel's table
 template <int W> constexpr int kBatch = W == 27 ? 7 : 8;   // window reads of one row in flight together
+// (4, 7, 9 and 14 of 27, and 4, 6 and 8 of 16, are within 0.3 us per iteration of
+// each other at 10^3 to 80^3; 16 of 16 spills, TET04 80^3 cubes 12.6 -> 14.3 us)
 constexpr unsigned long long kEmpty = 0xfff8dead00000001ull;   // no arithmetic result (bits() below)
 constexpr unsigned long long kNaN = 0x7ff8000000000000ull;
 constexpr int kMaxProbe = 64, kLine = 8;
