@@ -1815,7 +1815,7 @@ __global__ void __launch_bounds__(256) k_part_gather(GatherArgs g)
 // spent 0.27 / 0.39 / 0.58 ms per request of 4^3 / 8^3 / 12^3 cells, in these
 // common launches 0.20 / 0.30 / 0.48 (colour by colour 0.19 / 0.32-0.39 / 0.56).
 // The momentum kernel of hexahedra holds its arguments by pointer and spills 43
-// registers, the one alone none; the times are with that.
+// registers, the one alone 16; the times are with that.
 template <class EL, int OP>
 __global__ void __launch_bounds__(64 * Split<EL>::W, 2) k_bat_part(const char *__restrict__ table, AsmBatch B)
 {
